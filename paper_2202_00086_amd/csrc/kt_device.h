@@ -17,6 +17,14 @@ namespace kt {
 // Elementary functions
 // ---------------------------------------------------------------------------
 
+// A constant of a rarely run function, set up in scalar registers where it is
+// used: the volatile asm keeps it from being lifted out of the step loop into
+// registers that the loop needs.
+__device__ __forceinline__ double rare_k(double k) {
+    asm volatile("" : "+s"(k));
+    return k;
+}
+
 // sin and cos of x for |x| < ~1e5.  Cody-Waite reduction by pi/2 with a
 // two-part constant, then the Taylor series of sin through r^15 and of cos
 // through r^16 on |r| <= pi/4 (truncation below 1e-16), and a quadrant swap.
@@ -24,26 +32,26 @@ __device__ __forceinline__ void sincos_fast(double x, double* s_out, double* c_o
     constexpr double TWO_OVER_PI = 0.63661977236758134308;
     constexpr double PIO2_HI = 1.5707963267948965580e+00;  // pi/2 rounded to double
     constexpr double PIO2_LO = 6.1232339957367658e-17;     // pi/2 - PIO2_HI
-    const double n = __builtin_rint(x * TWO_OVER_PI);
-    double r = fma(-n, PIO2_HI, x);
-    r = fma(-n, PIO2_LO, r);
+    const double n = __builtin_rint(x * rare_k(TWO_OVER_PI));
+    double r = fma(-n, rare_k(PIO2_HI), x);
+    r = fma(-n, rare_k(PIO2_LO), r);
     const double r2 = r * r;
     // sin r = r (1 - r^2/3! + r^4/5! - ...), cos r = 1 - r^2/2! + r^4/4! - ...
-    double ps = -1.0 / 1307674368000.0;        // -1/15!
-    ps = fma(ps, r2, 1.0 / 6227020800.0);      //  1/13!
-    ps = fma(ps, r2, -1.0 / 39916800.0);       // -1/11!
-    ps = fma(ps, r2, 1.0 / 362880.0);          //  1/9!
-    ps = fma(ps, r2, -1.0 / 5040.0);           // -1/7!
-    ps = fma(ps, r2, 1.0 / 120.0);             //  1/5!
-    ps = fma(ps, r2, -1.0 / 6.0);              // -1/3!
+    double ps = rare_k(-1.0 / 1307674368000.0);        // -1/15!
+    ps = fma(ps, r2, rare_k(1.0 / 6227020800.0));      //  1/13!
+    ps = fma(ps, r2, rare_k(-1.0 / 39916800.0));       // -1/11!
+    ps = fma(ps, r2, rare_k(1.0 / 362880.0));          //  1/9!
+    ps = fma(ps, r2, rare_k(-1.0 / 5040.0));           // -1/7!
+    ps = fma(ps, r2, rare_k(1.0 / 120.0));             //  1/5!
+    ps = fma(ps, r2, rare_k(-1.0 / 6.0));              // -1/3!
     const double sr = fma(ps * r2, r, r);
-    double pc = 1.0 / 20922789888000.0;        //  1/16!
-    pc = fma(pc, r2, -1.0 / 87178291200.0);    // -1/14!
-    pc = fma(pc, r2, 1.0 / 479001600.0);       //  1/12!
-    pc = fma(pc, r2, -1.0 / 3628800.0);        // -1/10!
-    pc = fma(pc, r2, 1.0 / 40320.0);           //  1/8!
-    pc = fma(pc, r2, -1.0 / 720.0);            // -1/6!
-    pc = fma(pc, r2, 1.0 / 24.0);              //  1/4!
+    double pc = rare_k(1.0 / 20922789888000.0);        //  1/16!
+    pc = fma(pc, r2, rare_k(-1.0 / 87178291200.0));    // -1/14!
+    pc = fma(pc, r2, rare_k(1.0 / 479001600.0));       //  1/12!
+    pc = fma(pc, r2, rare_k(-1.0 / 3628800.0));        // -1/10!
+    pc = fma(pc, r2, rare_k(1.0 / 40320.0));           //  1/8!
+    pc = fma(pc, r2, rare_k(-1.0 / 720.0));            // -1/6!
+    pc = fma(pc, r2, rare_k(1.0 / 24.0));              //  1/4!
     pc = fma(pc, r2, -0.5);                    // -1/2!
     const double cr = fma(pc, r2, 1.0);
     const int q = static_cast<int>(n) & 3;
@@ -69,17 +77,17 @@ __device__ __forceinline__ double atan_unit(double t) {
     t = t / (1.0 + sqrt(fma(t, t, 1.0)));
     t = t / (1.0 + sqrt(fma(t, t, 1.0)));
     const double t2 = t * t;
-    double p = -1.0 / 23;
-    p = fma(p, t2, 1.0 / 21);
-    p = fma(p, t2, -1.0 / 19);
-    p = fma(p, t2, 1.0 / 17);
-    p = fma(p, t2, -1.0 / 15);
-    p = fma(p, t2, 1.0 / 13);
-    p = fma(p, t2, -1.0 / 11);
-    p = fma(p, t2, 1.0 / 9);
-    p = fma(p, t2, -1.0 / 7);
-    p = fma(p, t2, 1.0 / 5);
-    p = fma(p, t2, -1.0 / 3);
+    double p = rare_k(-1.0 / 23);
+    p = fma(p, t2, rare_k(1.0 / 21));
+    p = fma(p, t2, rare_k(-1.0 / 19));
+    p = fma(p, t2, rare_k(1.0 / 17));
+    p = fma(p, t2, rare_k(-1.0 / 15));
+    p = fma(p, t2, rare_k(1.0 / 13));
+    p = fma(p, t2, rare_k(-1.0 / 11));
+    p = fma(p, t2, rare_k(1.0 / 9));
+    p = fma(p, t2, rare_k(-1.0 / 7));
+    p = fma(p, t2, rare_k(1.0 / 5));
+    p = fma(p, t2, rare_k(-1.0 / 3));
     return 4.0 * fma(p * t2, t, t);
 }
 
@@ -107,11 +115,11 @@ __device__ __forceinline__ double asin_small(double x) {
                      C5 = asin_coef(5), C6 = asin_coef(6);
     const double x2 = x * x;
     double p = C6;
-    p = fma(p, x2, C5);
-    p = fma(p, x2, C4);
-    p = fma(p, x2, C3);
-    p = fma(p, x2, C2);
-    p = fma(p, x2, C1);
+    p = fma_k(p, x2, C5);
+    p = fma_k(p, x2, C4);
+    p = fma_k(p, x2, C3);
+    p = fma_k(p, x2, C2);
+    p = fma_k(p, x2, C1);
     return fma(p * x2, x, x);
 }
 
@@ -143,7 +151,7 @@ __device__ __forceinline__ RayConst make_ray_const(const Spacetime& st, double E
 
 // By-products of an RHS evaluation used at accepted states.
 struct Diag {
-    double H;       // Hamiltonian
+    double H2;      // twice the Hamiltonian
     double Kabs;    // |2 Sigma H| (|2H| for the q-metric)
     double D;       // the sum of the magnitudes of its terms: |H|_rel = Kabs / D
     double s, c;    // sin, cos of theta
@@ -207,7 +215,7 @@ __device__ __forceinline__ void rhs_sc(const Spacetime& st, const RayConst& rc, 
     dz[4] = d4;
     if (WANT_DIAG) {
         const double D = fma(Del, pr2, fma(pth, pth, fma(T, T, WWd)));
-        dg->H = 0.5 * H2;
+        dg->H2 = H2;
         dg->Kabs = fabs(K);
         dg->D = D;
         dg->s = s;
@@ -353,7 +361,7 @@ __device__ __forceinline__ void rhs_q(const QSpacetime& st, const RayConst& rc, 
     dz[4] = -0.5 * Hth2;
     if (WANT_DIAG) {
         const double K = (tA - tG) + (tB + tC);
-        dg->H = 0.5 * K;
+        dg->H2 = K;
         dg->Kabs = fabs(K);
         dg->D = tG + tA + tB + tC;
         dg->s = s;
@@ -481,7 +489,7 @@ __device__ __forceinline__ void rhs_split(const Spacetime& st, const Spacetime32
         const double WWd = W * W * rcp(Del);
         const double K = fma(Del, pr2, fma(pth, pth, fma(T, T, -WWd)));
         const double D = fma(Del, pr2, fma(pth, pth, fma(T, T, WWd)));
-        dg->H = 0.5 * K * inv_Sig;
+        dg->H2 = K * inv_Sig;
         dg->Kabs = fabs(K);
         dg->D = D;
         dg->s = s;

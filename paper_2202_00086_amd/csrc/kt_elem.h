@@ -21,6 +21,22 @@ __device__ __forceinline__ double rcp(double x) {
 }
 __host__ inline double rcp(double x) { return 1.0 / x; }
 
+// a b + k for a constant k.  In the 3-wave build of the trace kernels k goes
+// into the FMA as its scalar operand (set up by the scalar unit): left to
+// itself the compiler takes the two-operand form, whose addend is overwritten,
+// and moves k into a vector register pair before each use, two vector
+// instructions that the kernel's bottleneck has to issue.
+__device__ __forceinline__ double fma_k(double a, double b, double k) {
+#if defined(KT_WAVES_PER_EU) && KT_WAVES_PER_EU == 3
+    double r;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(k));
+    return r;
+#else
+    return fma(a, b, k);
+#endif
+}
+__host__ inline double fma_k(double a, double b, double k) { return fma(a, b, k); }
+
 // sin and cos of the polar angle theta.  theta is folded to t in [-pi, pi]
 // by t = theta - 2 pi rint(theta / 2 pi) (t = theta exactly on [0, pi), the
 // range of every ray that does not pass over the polar axis); then with
@@ -43,6 +59,7 @@ __host__ __device__ inline __attribute__((always_inline)) void sincos_theta(doub
     t = fma(-n, TWO_PI_LO, t);
     const double u = (fabs(t) - PIO2_HI) - PIO2_LO;
     const double u2 = u * u;
+    const auto fma = [](double a, double b, double k) { return fma_k(a, b, k); };
     double pc = 4.616135051438568e-14;
     pc = fma(pc, u2, -1.1463635437491283e-11);
     pc = fma(pc, u2, 2.0876592592498227e-09);
@@ -60,7 +77,7 @@ __host__ __device__ inline __attribute__((always_inline)) void sincos_theta(doub
     ps = fma(ps, u2, 0.00019841269841185962);
     ps = fma(ps, u2, -0.008333333333333115);
     ps = fma(ps, u2, 0.16666666666666666);
-    *c_out = fma(ps * u2, u, -u);  // cos theta = -sin u
+    *c_out = __builtin_fma(ps * u2, u, -u);  // cos theta = -sin u
 }
 
 }  // namespace kt

@@ -133,10 +133,12 @@ constexpr int32_t image_features(const Image& im) {
 // For batch renders the per-image ones become per-lane values.
 struct Hot {
     double M, a, a2, two_a2;
-    double rtol, atol, r_cap, r_esc, r_src, r_in, r_out;
+    double rtol, atol, r_cap, r_esc;
     double h_budget, r_switch;  // KT_MIXED
     int32_t feat;               // FEAT_* bits of the image's disk, source and sky
     int32_t max_steps, max_evals;
+    uint32_t first;             // ray ids of a persistent wave's first fetch, 1..64
+    unsigned long long* acc;    // the evaluation counters
     const Params* cold;         // the workspace copy of Params
 };
 

@@ -97,6 +97,22 @@ __device__ __forceinline__ double accept_factor(double msq) {
         return static_cast<double>(fminf(5.0f, fmaxf(0.2f, step_factor<METHOD>(msq))));
 }
 
+// The factor after either outcome, given the growth limit (5, or 1 after a
+// rejection): reject_factor where msq > 1, else accept_factor capped at the
+// limit.  The same numbers without a branch: a rejected step's factor lies
+// below 0.9 and so below either limit, and a negligible error's is the limit
+// itself (0.9 err^-0.2 is above 90 there, and infinite at 0).
+template <int METHOD>
+__device__ __forceinline__ double step_scale(double msq, float limit) {
+    if constexpr (fp64_control<METHOD>()) {
+        double f = fmax(0.2, step_factor64<METHOD>(msq));
+        if (!(msq >= 1e-20)) f = 5.0;
+        return fmin(f, static_cast<double>(limit));
+    } else {
+        return static_cast<double>(__builtin_amdgcn_fmed3f(step_factor<METHOD>(msq), 0.2f, limit));
+    }
+}
+
 // Mean square of err_i / sc_i over the five components.  The five
 // reciprocals come from one reciprocal of the product of the scales: the
 // hardware estimate (relative error ~5e-8: this number only steers the step

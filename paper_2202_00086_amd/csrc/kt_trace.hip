@@ -57,23 +57,23 @@ __device__ __forceinline__ double arc_angle(double s1, double c1, double s2, dou
 // The same angle for the short arcs of single steps: 2 asin(|n2 - n1| / 2)
 // with the small-angle series, where
 // |n2 - n1|^2 = (s2 - s1)^2 + (c2 - c1)^2 + 4 s1 s2 sin^2(dphi / 2).
-// Returns a negative value when the arc is outside the range of the series
+// *in_range is false when the arc is outside the range of the series
 // (|dphi| > 1/2 or chord/2 > 1/16); the caller then takes arc_angle.
-__device__ __forceinline__ double arc_angle_short(double s1, double c1, double s2, double c2,
-                                                  double dphi) {
-    if (!(fabs(dphi) <= 0.5)) return -1.0;
+__device__ __forceinline__ double arc_angle_short(double s1, double c1, double s2, double c2, double dphi,
+                                                  bool* in_range) {
     // sin x, |x| <= 1/4, through x^11 (truncation below 1e-17 relative)
     const double x = 0.5 * dphi, x2 = x * x;
     double p = -1.0 / 39916800.0;
-    p = fma(p, x2, 1.0 / 362880.0);
-    p = fma(p, x2, -1.0 / 5040.0);
-    p = fma(p, x2, 1.0 / 120.0);
-    p = fma(p, x2, -1.0 / 6.0);
+    p = fma_k(p, x2, 1.0 / 362880.0);
+    p = fma_k(p, x2, -1.0 / 5040.0);
+    p = fma_k(p, x2, 1.0 / 120.0);
+    p = fma_k(p, x2, -1.0 / 6.0);
     const double sh = fma(p * x2, x, x);
     const double ds = s2 - s1, dc = c2 - c1;
     const double q = (4.0 * s1) * s2;
     const double h = 0.5 * sqrt_fast(fma(q * sh, sh, fma(ds, ds, dc * dc)));
-    return h <= 0.0625 ? 2.0 * asin_small(h) : -1.0;
+    *in_range = (fabs(dphi) <= 0.5) & (h <= 0.0625);
+    return 2.0 * asin_small(h);
 }
 
 // Celestial-sphere code of the direction (theta, phi) (Sect. 4.1).  theta is
@@ -114,11 +114,22 @@ __device__ __forceinline__ int find_image(const Params& P, int64_t ray) {
     return lo;
 }
 
+// The cold parameters, in constant address space so that uniform reads are
+// scalar loads (the copy is written before the launch and not during it).
+// The empty asm keeps the compiler from moving those loads out of the rare
+// paths that need them into scalar registers that live across the step loop.
+__device__ __forceinline__ const Params& cold_params(const Params* p) {
+    using Const = const __attribute__((address_space(4))) Params;
+    Const* q = (Const*)p;
+    asm volatile("" : "+s"(q));
+    return *(const Params*)q;
+}
+
 // The per-image values the step loop needs.  For a single image they come
 // from kernel arguments (wave-uniform); for a batch they are loaded per ray.
+// The radii of events are read where an event is looked at: event_radii.
 struct LaneImg {
     Spacetime st;
-    double r_cap, r_esc, r_src, r_in, r_out;
     int32_t feat;  // FEAT_* bits
     int32_t k;     // image index
 };
@@ -126,22 +137,25 @@ struct LaneImg {
 __device__ __forceinline__ LaneImg lane_img(const Image& im, int k) {
     LaneImg li;
     li.st = Spacetime{im.M, im.a, im.a2, im.two_a2};
-    li.r_cap = im.r_cap;
-    li.r_esc = im.r_esc;
-    li.r_src = im.r_src;
-    li.r_in = im.r_in;
-    li.r_out = im.r_out;
     li.feat = image_features(im);
     li.k = k;
     return li;
 }
 
+struct Radii {
+    double r_cap, r_esc, r_src, r_in, r_out;
+};
+
+template <bool BATCH>
+__device__ __forceinline__ Radii event_radii(const Params* cold, int k) {
+    const Params& P = cold_params(cold);
+    const Image& im = BATCH ? P.images[k] : P.img0;
+    return Radii{im.r_cap, im.r_esc, im.r_src, im.r_in, im.r_out};
+}
+
 // Lane flags, packed in one int.
 enum : int {
-    F_VALID = 1 << 0,     // pixel has a real initial p_r
-    F_FRESH = 1 << 1,     // k1 = f(y0) not evaluated yet
     F_LOCATE = 1 << 2,    // taking trial steps to locate an event
-    F_REJECTED = 1 << 3,  // previous attempt was rejected (no step growth)
     F_RETAKE = 1 << 4,    // re-taking an accepted step after locating an event in it
     F_SKIPDISK = 1 << 5,  // disk crossing of the re-taken step already handled
     F_SRCDONE = 1 << 6,   // source sphere crossed
@@ -154,14 +168,11 @@ enum : int {
 constexpr int NCROSS_SHIFT = 8;   // 8 bits: equatorial crossings outside the disk
 constexpr int EVIT_SHIFT = 16;    // 8 bits: trial steps of the current event
 
-// Per-lane state that is touched at most once per step lives in LDS,
-// laid out [field][thread] so a wave's accesses are consecutive words.
-// C_PSI accumulates the swept angle and, once the source sphere is crossed,
-// holds the deflection; C_SRCPSI holds the angle to the source.
-enum : int {
-    C_MAXABS = 0, C_MAXREL, C_LAM, C_PSI, C_SRCPSI, C_CS, C_CC, C_EVA, C_EVFA, C_EVB, C_EVFB, C_EVC,
-    N_COLD
-};
+// Per-lane state that only events touch lives in LDS, laid out
+// [field][thread] so a wave's accesses are consecutive words: the size of
+// the step an event lies in, the regula falsi's bracket, and once the source
+// sphere is crossed the deflection and the angle to the source.
+enum : int { C_H = 0, C_EVA, C_EVFA, C_EVB, C_EVFB, C_DEFL, C_SRCPSI, C_LAM, C_SWEPT, C_MAXH2, C_RELK, C_RELD, N_COLD };
 constexpr int BLOCK_MAX = 256;
 
 template <int METHOD, class ST>
@@ -185,11 +196,80 @@ __device__ __forceinline__ void take_step(const ST& st, const RayConst& rc, cons
     }
 }
 
+// The number of lanes below this one in a mask of the wave.
+__device__ __forceinline__ uint32_t lanes_below(unsigned long long m) {
+    return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
+                                     __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u));
+}
+
+// The sum over the wave's lanes (all of them active), lane by lane: run once
+// at a wave's end, where shuffles would hold their address registers through
+// the step loop.
+__device__ __forceinline__ unsigned long long wave_sum(unsigned long long v) {
+    unsigned long long sum = 0ull;
+    for (int l = 0; l < 64; ++l) {
+        const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), l));
+        const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v >> 32), l));
+        sum += (static_cast<unsigned long long>(hi) << 32) | lo;
+    }
+    return sum;
+}
+
+// max(|a|, |b|) in one instruction (fmax makes each operand canonical first,
+// a vector instruction apiece); the other operand where one is NaN.
+__device__ __forceinline__ double max_abs(double a, double b) {
+    double r;
+    asm("v_max_f64 %0, |%1|, |%2|" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
+// A ray's state (r, theta, phi, p_r, p_theta), or the field, as it is kept
+// across steps: named members, so that each lives in a register pair of its
+// own.  (An array that lives across the loop becomes one 16-register vector,
+// three pairs of it unused and all of it copied at every commit.)
+struct Vec5 {
+    double r, th, ph, pr, pth;
+    static __device__ __forceinline__ Vec5 of(const double z[5]) { return Vec5{z[0], z[1], z[2], z[3], z[4]}; }
+    __device__ __forceinline__ void to(double z[5]) const {
+        z[0] = r;
+        z[1] = th;
+        z[2] = ph;
+        z[3] = pr;
+        z[4] = pth;
+    }
+};
+
+// The running maxima of |2H| and of |H|_rel = Kabs / D, the latter as its
+// two parts (ratios compared by cross products): no quotient per step.
+__device__ __forceinline__ void keep_max(const Diag& dg, double* max_h2, double* rel_k, double* rel_d) {
+    *max_h2 = max_abs(dg.H2, *max_h2);
+    if (dg.Kabs * *rel_d > *rel_k * dg.D) {
+        *rel_k = dg.Kabs;
+        *rel_d = dg.D;
+    }
+}
+
 // FEAT >= 0 fixes the image's features (FEAT_* bits) at compile time, so the
 // event tests of absent features vanish from the step loop; FEAT_DYN reads
 // them from the launch (single images) or the lane's image (batches).
 constexpr int FEAT_DYN = -1;
 
+// The step loop has one straight path that every busy lane of the wave takes
+// together: the step, its error and step-size factor, and one predicate that
+// names the lanes for which anything else than an ordinary accepted or
+// rejected step may have happened (a window of r, the disk plane, the source
+// arc's range, a non-finite error, event location under way, the step
+// budget).  Ordinary lanes commit or shrink their step there; the others go
+// through the long form of the same decisions after it, and only then does
+// the wave look for ended rays to replace.  What the predicate may not miss
+// is listed at each test; a lane it names without need takes the long form
+// and ends up with the same bits.
+//
+// The kernel is bound by the FP64 vector issue rate (the step alone is ~570
+// FP64 instructions), so everything that is not that arithmetic counts:
+// with each test in a branch of its own, and the per-ray scalars in LDS, an
+// attempt took ~830 vector and ~215 scalar instructions, and a wave alone on
+// its SIMD, as in small images, needed 2.5 us for it.
 template <int METHOD, int PREC, bool BATCH, bool QMET = false, int FEAT = FEAT_DYN>
 __global__ void __launch_bounds__(BLOCK_MAX) __attribute__((amdgpu_waves_per_eu(KT_WAVES_PER_EU)))
 trace_kernel(const Hot hp) {
@@ -200,34 +280,34 @@ trace_kernel(const Hot hp) {
     constexpr bool ADAPTIVE = (METHOD != KT_RK4_S);
     constexpr bool S_TIME = (METHOD == KT_RK4_S);
     constexpr bool MIXED = (PREC == KT_MIXED) && (METHOD == KT_DP45) && !QMET;
+    constexpr bool MAY_DISK = FEAT < 0 ? !QMET : (FEAT & FEAT_DISK) != 0;
+    constexpr bool MAY_SRC = FEAT < 0 || (FEAT & FEAT_SRC) != 0;
     __shared__ double cold[N_COLD][BLOCK_MAX];
     const int tid = threadIdx.x;
 #define COLD(f) cold[f][tid]
-    // cold parameters are read from the workspace copy where needed
-    const Params& P = *hp.cold;
 
     LaneImg li;
     li.st = Spacetime{hp.M, hp.a, hp.a2, hp.two_a2};
-    li.r_cap = hp.r_cap;
-    li.r_esc = hp.r_esc;
-    li.r_src = hp.r_src;
-    li.r_in = hp.r_in;
-    li.r_out = hp.r_out;
     li.feat = hp.feat;
     li.k = 0;
     const uint32_t lane = __lane_id();
-    const uint32_t n_total = P.from_list ? *P.fb_count : static_cast<uint32_t>(P.n_rays);
+    uint32_t n_total;
 
     // this wave's queue of ray ids [q_next, q_end).  A persistent wave's
-    // first fetch takes 64 ids, one per lane, in one atomic; later fetches
-    // take P.batch.  Taken in batch-sized pieces, the start of the launch was
-    // a burst of 64 / batch serial round trips per wave on one address, and
-    // the wave's first rays came from interleaved places in the dispatch
-    // order instead of one run of similar cost.
+    // first fetch takes hp.first ids, up to one per lane, in one atomic;
+    // later fetches take P.batch.  Taken in batch-sized pieces, the start of
+    // the launch was a burst of 64 / batch serial round trips per wave on one
+    // address, and the wave's first rays came from interleaved places in the
+    // dispatch order instead of one run of similar cost.
     uint32_t q_next, q_end;
     bool exhausted;
-    bool first_fetch = P.persistent != 0;
-    if (P.persistent) {
+    bool first_fetch;
+    {
+        const Params& P = cold_params(hp.cold);
+        n_total = P.from_list ? *P.fb_count : static_cast<uint32_t>(P.n_rays);
+        first_fetch = P.persistent != 0;
+    }
+    if (first_fetch) {
         q_next = q_end = 0;
         exhausted = false;
     } else {
@@ -239,41 +319,92 @@ trace_kernel(const Hot hp) {
 
     int32_t ray = -1;
     int fl = 0;
-    double y[5], k1[5];
-    double E = 0.0, L = 0.0, h = 0.0;
-    int nsteps = 0, nevals = 0;
+    Vec5 ys{}, ks{};  // the state and the field there
+    RayConst rc{};
+    double h = 0.0;             // the step to try (while locating: the trial step)
+    double s0 = 0.0, c0 = 1.0;  // sin, cos of theta at y
+    // The swept angle up to y, the largest |2H|, and the |2 Sigma H| and D of
+    // the largest |H|_rel.  With 3 waves per SIMD there are no registers left
+    // for them, but the other waves hide the LDS reads; a wave alone on its
+    // SIMD, the common case of the 2-wave build, would wait for them.
+    constexpr bool IN_LDS = KT_WAVES_PER_EU == 3 || MIXED || BATCH;
+    double reg_swept, reg_max_h2, reg_rel_k, reg_rel_d;
+    double& swept = IN_LDS ? COLD(C_SWEPT) : reg_swept;
+    double& max_h2 = IN_LDS ? COLD(C_MAXH2) : reg_max_h2;
+    double& rel_k = IN_LDS ? COLD(C_RELK) : reg_rel_k;
+    double& rel_d = IN_LDS ? COLD(C_RELD) : reg_rel_d;
+    swept = max_h2 = rel_k = 0.0;
+    rel_d = 1.0;
+    double r_lo = 0.0, r_hi = 0.0;  // MAY_SRC: the window of r without an event
+    float fac_max = 5.0f;           // growth limit: 1 after a rejection
+    int misses = 0;                 // attempts that were not accepted steps
     unsigned long long evals_acc = 0, evals32_acc = 0;
-#pragma unroll
-    for (int i = 0; i < 5; ++i) y[i] = k1[i] = 0.0;
+    // Attempts are counted for the wave: a lane's are it - it0, its accepted
+    // steps those less its misses.  From it_limit on, some lane may have
+    // used up its step budget.
+    uint32_t it = 0, it0 = 0;
+    const uint32_t budget = static_cast<uint32_t>(
+        min(hp.max_steps, (hp.max_evals - 1 + EVALS_PER_STEP - 1) / EVALS_PER_STEP));
+    uint32_t it_limit = budget;
+    // lanes with a ray, and those whose next attempt is part of an event
+    // (F_LOCATE or F_RETAKE)
+    unsigned long long busy, in_event = 0ull;
 
-#if KT_WAVES_PER_EU == 3
-    // With three waves per SIMD the issue arbiter's preference for the
-    // oldest wave runs the three generations of blocks at very different
-    // speeds, and the rays a slow wave holds end the launch late.  Each wave
-    // steps its priority down from 3 to 0 and round again, one level per
-    // loop iteration; the waves' cycles are out of phase, so the highest
-    // priority moves from wave to wave and their shares of the issue slots
-    // even out.
-    uint32_t prio_it = 0;
-#endif
-    for (;;) {
-#if KT_WAVES_PER_EU == 3
-        switch (prio_it & 3u) {
-            case 0: __builtin_amdgcn_s_setprio(3); break;
-            case 1: __builtin_amdgcn_s_setprio(2); break;
-            case 2: __builtin_amdgcn_s_setprio(1); break;
-            default: __builtin_amdgcn_s_setprio(0); break;
+    // the q-metric carries (q, q(2+q)) in the spacetime's (a, a^2) slots
+    const auto spacetime = [&]() {
+        if constexpr (QMET)
+            return QSpacetime{li.st.M, li.st.a, li.st.a2};
+        else
+            return li.st;
+    };
+    // The window of r inside which no radial event can happen: capture below
+    // it, escape above it, and with a source still ahead its sphere, from
+    // the side the ray is on.
+    const auto set_window = [&](const Radii& rd, double r) {
+        if constexpr (MAY_SRC) {
+            r_lo = rd.r_cap;
+            r_hi = rd.r_esc;
+            const int32_t feat = FEAT >= 0 ? FEAT : li.feat;
+            if ((feat & FEAT_SRC) && !(fl & F_SRCDONE)) {
+                if (r < rd.r_src)
+                    r_hi = fmin(r_hi, rd.r_src);
+                else
+                    r_lo = fmax(r_lo, rd.r_src);
+            }
         }
-        ++prio_it;
-#endif
+    };
+    const auto write_outputs = [&](int fate, double r_c, double psi, double defl, double thf, double phf, int nsteps,
+                                   int nevals) {
+        const Params& P = cold_params(hp.cold);
+        const Outputs& o = P.out;
+        o.fate[ray] = static_cast<uint8_t>(fate);
+        P.rc_buf[ray] = r_c;
+        if (o.max_abs_h) o.max_abs_h[ray] = 0.5 * max_h2;
+        const double max_rel = rel_k * rcp(rel_d);
+        if (o.max_rel_h) o.max_rel_h[ray] = max_rel;
+        if (o.psi) o.psi[ray] = psi;
+        if (o.deflection) o.deflection[ray] = defl;
+        if (o.theta_f) o.theta_f[ray] = thf;
+        if (o.phi_f) o.phi_f[ray] = phf;
+        if (o.n_cross) o.n_cross[ray] = static_cast<uint8_t>((fl >> NCROSS_SHIFT) & 0xff);
+        if (o.used_fp64) o.used_fp64[ray] = static_cast<uint8_t>(P.from_list ? 1 : 0);
+        if (o.n_steps) o.n_steps[ray] = nsteps;
+        if (o.n_evals) o.n_evals[ray] = nevals;
+        if constexpr (MIXED) P.need_fb[ray] = ((fl & F_USED32) && !(max_rel <= hp.h_budget)) ? 1 : 0;
+        evals_acc += static_cast<unsigned long long>(nevals);
+        ray = -1;
+    };
+
+    for (;;) {
         // ---- refill idle lanes from the wave queue -------------------------
         unsigned long long idle = __ballot(ray < 0);
         while (idle != 0ull) {
             if (q_next >= q_end) {
                 if (exhausted) break;
+                const Params& P = cold_params(hp.cold);
                 const int leader = __ffsll(idle) - 1;
                 uint32_t base = 0;
-                const uint32_t take = first_fetch ? 64u : static_cast<uint32_t>(P.batch);
+                const uint32_t take = first_fetch ? hp.first : static_cast<uint32_t>(P.batch);
                 first_fetch = false;
                 if (static_cast<int>(lane) == leader) base = atomicAdd(P.ticket, take);
                 base = static_cast<uint32_t>(__shfl(static_cast<int>(base), leader));
@@ -284,146 +415,235 @@ trace_kernel(const Hot hp) {
                 q_next = base;
                 q_end = min(base + take, n_total);
             }
-            const uint32_t rank = static_cast<uint32_t>(__popcll(idle & ((1ull << lane) - 1ull)));
+            const uint32_t rank = lanes_below(idle);
             const uint32_t avail = q_end - q_next;
             if (ray < 0 && rank < avail) {
+                const Params& P = cold_params(hp.cold);
                 const uint32_t slot = q_next + rank;
                 ray = P.from_list ? static_cast<int32_t>(P.fb_list[slot])
                       : P.perm    ? static_cast<int32_t>(P.perm[slot])
                                   : static_cast<int32_t>(slot);
+                double y[5], E, L;
+                bool valid;
                 if constexpr (BATCH) {
                     const int k = find_image(P, ray);
                     const Image& im = P.images[k];
                     li = lane_img(im, k);
-                    fl = camera_state(im, ray - static_cast<int32_t>(im.first), y, &E, &L) ? (F_VALID | F_FRESH) : 0;
+                    valid = camera_state(im, ray - static_cast<int32_t>(im.first), y, &E, &L);
                 } else {
-                    fl = camera_state(P.img0, ray, y, &E, &L) ? (F_VALID | F_FRESH) : 0;
+                    valid = camera_state(P.img0, ray, y, &E, &L);
                 }
-                h = ADAPTIVE ? P.h_init : P.h_fixed;
-                nsteps = 0;
-                nevals = 0;
+                fl = 0;
+                if (!valid) {
+                    const double NaN = __builtin_nan("");
+                    max_h2 = rel_k = NaN;
+                    write_outputs(KT_FATE_INVALID, NaN, NaN, NaN, y[1], y[2], 0, 0);
+                } else {
+                    // k1 = f(y0) (FSAL seed) and H at lambda = 0
+                    const auto st = spacetime();
+                    rc = make_ray_const(st, E, L);
+                    Diag dg;
+                    double k1[5];
+                    rhs<true, S_TIME>(st, rc, y, k1, &dg);
+                    ys = Vec5::of(y);
+                    ks = Vec5::of(k1);
+                    max_h2 = fabs(dg.H2);
+                    rel_k = dg.Kabs;
+                    rel_d = dg.D;
+                    s0 = dg.s;
+                    c0 = dg.c;
+                    COLD(C_LAM) = 0.0;
+                    swept = 0.0;
+                    h = ADAPTIVE ? P.h_init : P.h_fixed;
+                    fac_max = 5.0f;
+                    misses = 0;
+                    it0 = it;
+                    set_window(event_radii<BATCH>(hp.cold, li.k), y[0]);
+                }
             }
             q_next += min(static_cast<uint32_t>(__popcll(idle)), avail);
             idle = __ballot(ray < 0);
         }
-        if (__ballot(ray >= 0) == 0ull) break;
-        if (ray < 0) continue;
+        busy = __ballot(ray >= 0);
+        if (busy == 0ull) break;
 
-        // ---- one step per busy lane ----------------------------------------
-        // the q-metric carries (q, q(2+q)) in the spacetime's (a, a^2) slots
-        const auto st = [&]() {
-            if constexpr (QMET)
-                return QSpacetime{li.st.M, li.st.a, li.st.a2};
-            else
-                return li.st;
-        }();
-        const RayConst rc = make_ray_const(st, E, L);
-        const double NaN = __builtin_nan("");
-        int fate = -1;  // >= 0 once the ray ends
-        double thf = y[1], phf = y[2], r_c = NaN, psi = NaN, defl = NaN;
-
-        if (!(fl & F_VALID)) {
-            fate = KT_FATE_INVALID;
-            COLD(C_MAXABS) = NaN;
-            COLD(C_MAXREL) = NaN;
-        } else if (fl & F_FRESH) {
-            // first evaluation: k1 = f(y0) (FSAL seed) and H at lambda = 0
-            Diag dg;
-            rhs<true, S_TIME>(st, rc, y, k1, &dg);
-            nevals = 1;
-            COLD(C_MAXABS) = fabs(dg.H);
-            COLD(C_MAXREL) = dg.rel();
-            COLD(C_LAM) = 0.0;
-            COLD(C_PSI) = 0.0;
-            COLD(C_CS) = dg.s;
-            COLD(C_CC) = dg.c;
-            fl &= ~F_FRESH;
-        } else if (!(fl & (F_LOCATE | F_RETAKE)) && (nsteps >= hp.max_steps || nevals >= hp.max_evals)) {
-            fate = KT_FATE_MAXSTEPS;
-        } else {
-            const bool locating = (fl & F_LOCATE) != 0;
-            bool use32 = false;
+        // ---- the step loop: until some lane needs the long form ------------
+        // Idle lanes go along on their last state and change nothing.
+        Diag dg;
+        Vec5 ye{}, ke{};  // the step's end and the field there
+        double msq = 0.0, fac = 1.0;
+        bool use32 = false, fits = true, odd;
+        for (;;) {
+#if KT_WAVES_PER_EU == 3
+            // With three waves per SIMD the issue arbiter's preference for
+            // the oldest wave runs the three generations of blocks at very
+            // different speeds, and the rays a slow wave holds end the
+            // launch late.  Each wave steps its priority down from 3 to 0
+            // and round again, one level per attempt; the waves' cycles
+            // are out of phase, so the highest priority moves from wave to
+            // wave and their shares of the issue slots even out.
+            switch (it & 3u) {
+                case 0: __builtin_amdgcn_s_setprio(3); break;
+                case 1: __builtin_amdgcn_s_setprio(2); break;
+                case 2: __builtin_amdgcn_s_setprio(1); break;
+                default: __builtin_amdgcn_s_setprio(0); break;
+            }
+#endif
+            ++it;
+            const auto st = spacetime();
+            double y[5], k1[5], yn[5], kn[5], er[5];
+            ys.to(y);
+            ks.to(k1);
             if constexpr (MIXED) {
-                // The FP32 mass part runs wave-uniformly.  A lane locating an
-                // event, or retaking the step it lay in, must use the
-                // precision of that accepted step (its trial steps are steps
-                // of the same stepper, and the retake must reproduce the
-                // step bit for bit).  The lowest such lane sets the wave's
-                // precision and lanes that cannot use it sit this pass out;
-                // with no such lane the FP32 part runs when every stepping
-                // lane is beyond r_switch.
+                // The FP32 mass part runs wave-uniformly.  A lane locating
+                // an event, or retaking the step it lay in, must use the
+                // precision of that accepted step (its trial steps are
+                // steps of the same stepper, and the retake must reproduce
+                // the step bit for bit).  The lowest such lane sets the
+                // wave's precision and lanes that cannot use it sit this
+                // attempt out; with no such lane the FP32 part runs when
+                // every stepping lane is beyond r_switch.
                 const bool pinned = (fl & (F_LOCATE | F_RETAKE)) != 0;
                 const bool ev32 = (fl & F_EV32) != 0;
-                const unsigned long long pin = __ballot(pinned);
-                if (pin != 0ull) {
-                    const int lead = __ffsll(pin) - 1;
-                    use32 = ((__ballot(pinned && ev32) >> lead) & 1ull) != 0ull;
+                if (in_event != 0ull) {
+                    const int lead = __ffsll(in_event) - 1;
+                    use32 = ((__ballot(ev32) >> lead) & 1ull) != 0ull;
                 } else {
-                    use32 = __all(y[0] >= hp.r_switch);
+                    use32 = (__ballot(y[0] >= hp.r_switch) & busy) == busy;
                 }
-                const bool fits = pinned ? (ev32 == use32) : (!use32 || y[0] >= hp.r_switch);
-                if (!fits) continue;
-            }
-            const double hs = locating ? COLD(C_EVC) : h;
-            double yn[5], kn[5], er[5];
-            Diag dg;
-            // sin/cos of theta at the step start (from the last evaluation there)
-            const double s0 = COLD(C_CS), c0 = COLD(C_CC);
-            if constexpr (MIXED) {
+                fits = pinned ? (ev32 == use32) : (!use32 || y[0] >= hp.r_switch);
                 const Spacetime32 sf{static_cast<float>(st.M), static_cast<float>(st.a), static_cast<float>(st.a2)};
                 if (use32) {
-                    dp45_step<true>(st, rc, y, k1, s0, c0, hs, yn, kn, er, &dg, &sf);
-                    fl |= F_USED32;
-                    evals32_acc += EVALS_PER_STEP;
+                    dp45_step<true>(st, rc, y, k1, s0, c0, h, yn, kn, er, &dg, &sf);
+                    if (fits && ray >= 0) {
+                        fl |= F_USED32;
+                        evals32_acc += EVALS_PER_STEP;
+                    }
                 } else {
-                    dp45_step<false>(st, rc, y, k1, s0, c0, hs, yn, kn, er, &dg);
+                    dp45_step<false>(st, rc, y, k1, s0, c0, h, yn, kn, er, &dg);
                 }
+                if (!fits) ++it0;
             } else {
-                take_step<METHOD>(st, rc, y, k1, s0, c0, hs, yn, kn, er, &dg);
+                take_step<METHOD>(st, rc, y, k1, s0, c0, h, yn, kn, er, &dg);
             }
-            nevals += EVALS_PER_STEP;
-            if (locating) {
+            ye = Vec5::of(yn);
+            ke = Vec5::of(kn);
+            bool accept = true;
+            odd = false;
+            if constexpr (ADAPTIVE) {
+                // mean square of err_i / (atol + rtol max(|y_i|, |yn_i|))
+                double sc[5];
+#pragma unroll
+                for (int i = 0; i < 5; ++i) sc[i] = fma(hp.rtol, max_abs(y[i], yn[i]), hp.atol);
+                msq = error_msq<fp64_control<METHOD>()>(er, sc);
+                fac = step_scale<METHOD>(msq, fac_max);
+                accept = msq <= 1.0;
+                // A non-finite r, theta, p_r or p_theta makes kn and with
+                // it the error NaN or infinite, an infinite scale makes
+                // the norm NaN; phi enters no evaluation and is tested.
+                odd = !(msq < 1e20) | !isfinite(yn[2]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 5; ++i) odd = odd | !isfinite(yn[i]);
+            }
+            // events that an accepted step may hold (each test is at least
+            // as wide as the event's own condition in the long form)
+            const int32_t feat = FEAT >= 0 ? FEAT : li.feat;
+            bool ev = MAY_SRC ? !(yn[0] >= r_lo) | !(yn[0] < r_hi) : !(yn[0] >= hp.r_cap) | !(yn[0] <= hp.r_esc);
+            if constexpr (MAY_DISK) {
+                const bool cross = (y[1] - HALF_PI) * (yn[1] - HALF_PI) <= 0.0;
+                ev = ev | (cross & ((feat & FEAT_DISK) != 0));
+            }
+            double arc = 0.0;
+            if constexpr (MAY_SRC) {
+                if (FEAT >= 0 || (feat & FEAT_SRC)) {
+                    bool in_range;
+                    arc = arc_angle_short(s0, c0, dg.s, dg.c, yn[2] - y[2], &in_range);
+                    ev = ev | !in_range;
+                }
+            }
+            odd = odd | (accept & ev) | __builtin_amdgcn_inverse_ballot_w64(in_event) | (it == it_limit);
+            const bool mine = __builtin_amdgcn_inverse_ballot_w64(busy) & fits;
+            odd = odd & mine;
+            if (!odd & mine) {
+                if (accept) {
+                    // commit
+                    keep_max(dg, &max_h2, &rel_k, &rel_d);
+                    unsafeAtomicAdd(&COLD(C_LAM), h);  // one LDS add, no result
+                    if constexpr (MAY_SRC) swept += arc;
+                    ys = ye;
+                    ks = ke;
+                    s0 = dg.s;
+                    c0 = dg.c;
+                    if constexpr (ADAPTIVE) {
+                        h *= fac;
+                        fac_max = 5.0f;
+                    }
+                } else {
+                    // reject, unless the step underflows
+                    const double hn = h * fac;
+                    odd = hn < 1e-12 * fmax(1.0, fabs(COLD(C_LAM)));
+                    if (!odd) {
+                        h = hn;
+                        fac_max = 1.0f;
+                        ++misses;
+                    }
+                }
+            }
+            if (__ballot(odd) != 0ull) break;
+        }
+
+        // ---- the long form, for the lanes that need it -----------------
+        if (odd) {
+            const int32_t feat = FEAT >= 0 ? FEAT : li.feat;
+            const Radii rd = event_radii<BATCH>(hp.cold, li.k);
+            const double NaN = __builtin_nan("");
+            int fate = -1;  // >= 0 once the ray ends
+            double thf = ys.th, phf = ys.ph, r_c = NaN, psi = NaN, defl = NaN;
+            if (fl & F_LOCATE) {
                 // Illinois regula falsi on the event function
+                ++misses;
                 const bool src = (fl & F_EVSRC) != 0;
                 const bool esc = (fl & F_EVESC) != 0;
+                const Params& P = cold_params(hp.cold);
                 const Image& im = BATCH ? P.images[li.k] : P.img0;
-                const double fc = esc ? yn[0] - li.r_esc : src ? yn[0] - li.r_src : yn[1] - HALF_PI;
+                const double fc = esc ? ye.r - rd.r_esc : src ? ye.r - rd.r_src : ye.th - HALF_PI;
                 const double tol = esc ? im.esc_tol : src ? im.src_tol : 1e-14;
-                const int it = ((fl >> EVIT_SHIFT) & 0xff) + 1;
-                fl = (fl & ~(0xff << EVIT_SHIFT)) | (it << EVIT_SHIFT);
-                if ((fabs(fc) <= tol || it >= 64) && esc) {
+                const int n_it = ((fl >> EVIT_SHIFT) & 0xff) + 1;
+                fl = (fl & ~(0xff << EVIT_SHIFT)) | (n_it << EVIT_SHIFT);
+                if ((fabs(fc) <= tol || n_it >= 64) && esc) {
                     // the ray meets the celestial sphere here
                     fate = KT_FATE_ESCAPED;
-                    thf = yn[1];
-                    phf = yn[2];
-                } else if (fabs(fc) <= tol || it >= 64) {
+                    thf = ye.th;
+                    phf = ye.ph;
+                } else if (fabs(fc) <= tol || n_it >= 64) {
                     if (!src) {
-                        if (yn[0] >= li.r_in && yn[0] <= li.r_out) {
+                        if (ye.r >= rd.r_in && ye.r <= rd.r_out) {
                             fate = KT_FATE_DISK;
-                            r_c = yn[0];
-                            thf = yn[1];
-                            phf = yn[2];
+                            r_c = ye.r;
+                            thf = ye.th;
+                            phf = ye.ph;
                         } else {
                             const int nc = min(((fl >> NCROSS_SHIFT) & 0xff) + 1, 255);
                             fl = (fl & ~(0xff << NCROSS_SHIFT)) | (nc << NCROSS_SHIFT) | F_SKIPDISK;
                         }
                     } else {
-                        defl = COLD(C_PSI) + arc_angle(s0, c0, dg.s, dg.c, yn[2] - y[2]);
+                        const double sw = swept + arc_angle(s0, c0, dg.s, dg.c, ye.ph - ys.ph);
                         double sp, cp;
-                        sincos_fast(yn[2], &sp, &cp);
+                        sincos_fast(ye.ph, &sp, &cp);
                         const double* sn = im.src_n;
                         const double nx = dg.s * cp, ny = dg.s * sp, nz = dg.c;
                         const double cx = ny * sn[2] - nz * sn[1];
                         const double cy = nz * sn[0] - nx * sn[2];
                         const double cz = nx * sn[1] - ny * sn[0];
-                        psi = atan2_upper(sqrt(fma(cx, cx, fma(cy, cy, cz * cz))),
-                                          fma(nx, sn[0], fma(ny, sn[1], nz * sn[2])));
-                        COLD(C_PSI) = defl;  // parked until the ray ends
-                        COLD(C_SRCPSI) = psi;
+                        COLD(C_SRCPSI) = atan2_upper(sqrt(fma(cx, cx, fma(cy, cy, cz * cz))),
+                                                     fma(nx, sn[0], fma(ny, sn[1], nz * sn[2])));
+                        COLD(C_DEFL) = sw;  // parked until the ray ends
                         fl |= F_SRCDONE;
                     }
                     // continue from the end of the accepted step: retake it (bit-identical)
                     fl = (fl & ~F_LOCATE) | F_RETAKE;
+                    h = COLD(C_H);
                 } else {
                     double a = COLD(C_EVA), fa = COLD(C_EVFA), b = COLD(C_EVB), fb = COLD(C_EVFB);
                     if (fc * fb < 0.0) {
@@ -432,72 +652,48 @@ trace_kernel(const Hot hp) {
                     } else {
                         fa *= 0.5;
                     }
-                    b = COLD(C_EVC);
+                    b = h;
                     fb = fc;
                     COLD(C_EVA) = a;
                     COLD(C_EVFA) = fa;
                     COLD(C_EVB) = b;
                     COLD(C_EVFB) = fb;
-                    COLD(C_EVC) = b - fb * (b - a) / (fb - fa);
+                    h = b - fb * (b - a) / (fb - fa);
                 }
             } else {
-                bool finite = true;
-#pragma unroll
-                for (int i = 0; i < 5; ++i) finite = finite && isfinite(yn[i]);
-                double h_next = h;
-                bool accept = true;
-                if (!finite) {
+                const bool finite = isfinite(ye.r) && isfinite(ye.th) && isfinite(ye.ph) && isfinite(ye.pr) &&
+                                    isfinite(ye.pth);
+                if (!finite || (ADAPTIVE && isnan(msq))) {
                     fate = KT_FATE_STEPFAIL;
-                    accept = false;
-                } else if constexpr (ADAPTIVE) {
-                    // mean square of err_i / (atol + rtol max(|y_i|, |yn_i|))
-                    double sc[5];
-#pragma unroll
-                    for (int i = 0; i < 5; ++i) sc[i] = fma(hp.rtol, fmax(fabs(y[i]), fabs(yn[i])), hp.atol);
-                    const double msq = error_msq<fp64_control<METHOD>()>(er, sc);
-                    if (isnan(msq)) {
-                        fate = KT_FATE_STEPFAIL;
-                        accept = false;
-                    } else if (msq > 1.0) {
-                        h *= reject_factor<METHOD>(msq);
-                        fl |= F_REJECTED;
-                        accept = false;
-                        if (h < 1e-12 * fmax(1.0, fabs(COLD(C_LAM)))) fate = KT_FATE_STEPFAIL;
-                    } else {
-                        double fac = accept_factor<METHOD>(msq);
-                        if (fl & F_REJECTED) fac = fmin(fac, 1.0);
-                        h_next = h * fac;
-                    }
-                }
-                if (accept) {
+                    ++misses;
+                } else if (ADAPTIVE && msq > 1.0) {
+                    h *= fac;
+                    fac_max = 1.0f;
+                    ++misses;
+                    if (h < 1e-12 * fmax(1.0, fabs(COLD(C_LAM)))) fate = KT_FATE_STEPFAIL;
+                } else {
                     if (!(fl & F_RETAKE)) {
-                        ++nsteps;
-                        COLD(C_MAXABS) = fmax(COLD(C_MAXABS), fabs(dg.H));
-                        // |H|_rel = Kabs / D: the quotient is taken only when
-                        // it raises the running maximum (Kabs > max D)
-                        const double mr = COLD(C_MAXREL);
-                        if (dg.Kabs > mr * dg.D) COLD(C_MAXREL) = dg.rel();
+                        keep_max(dg, &max_h2, &rel_k, &rel_d);
+                    } else {
+                        ++misses;
                     }
                     fl &= ~F_RETAKE;
-                    bool locate = false;
+                    // an event inside the step: its function at both ends
+                    int locate = 0;  // its F_EV* kind, or F_LOCATE for the disk
+                    double fa = 0.0, fb = 0.0;
                     // thin disk: sign change of theta - pi/2 over the step
-                    const int32_t feat = FEAT >= 0 ? FEAT : li.feat;
                     if ((feat & FEAT_DISK) && !(fl & F_SKIPDISK)) {
-                        const double ga = y[1] - HALF_PI, gb = yn[1] - HALF_PI;
+                        const double ga = ys.th - HALF_PI, gb = ye.th - HALF_PI;
                         if (ga * gb < 0.0) {
-                            fl = (fl & ~(F_EVSRC | F_EV32 | (0xff << EVIT_SHIFT))) | F_LOCATE | (use32 ? F_EV32 : 0);
-                            COLD(C_EVA) = 0.0;
-                            COLD(C_EVFA) = ga;
-                            COLD(C_EVB) = h;
-                            COLD(C_EVFB) = gb;
-                            COLD(C_EVC) = h - gb * h / (gb - ga);
-                            locate = true;
+                            locate = F_LOCATE;
+                            fa = ga;
+                            fb = gb;
                         } else if (gb == 0.0) {
-                            if (yn[0] >= li.r_in && yn[0] <= li.r_out) {
+                            if (ye.r >= rd.r_in && ye.r <= rd.r_out) {
                                 fate = KT_FATE_DISK;
-                                r_c = yn[0];
-                                thf = yn[1];
-                                phf = yn[2];
+                                r_c = ye.r;
+                                thf = ye.th;
+                                phf = ye.ph;
                             } else {
                                 const int nc = min(((fl >> NCROSS_SHIFT) & 0xff) + 1, 255);
                                 fl = (fl & ~(0xff << NCROSS_SHIFT)) | (nc << NCROSS_SHIFT);
@@ -505,96 +701,98 @@ trace_kernel(const Hot hp) {
                         }
                     }
                     if (!locate && fate < 0) {
-                        if (yn[0] < li.r_cap) {
+                        if (ye.r < rd.r_cap) {
                             fate = KT_FATE_CAPTURED;
-                            thf = yn[1];
-                            phf = yn[2];
+                            thf = ye.th;
+                            phf = ye.ph;
                         } else {
                             if ((feat & FEAT_SRC) && !(fl & F_SRCDONE)) {
-                                if (y[0] < li.r_src && yn[0] >= li.r_src) {
-                                    const double fa = y[0] - li.r_src, fb = yn[0] - li.r_src;
-                                    fl = (fl & ~(F_EV32 | (0xff << EVIT_SHIFT))) | F_EVSRC | F_LOCATE | (use32 ? F_EV32 : 0);
-                                    COLD(C_EVA) = 0.0;
-                                    COLD(C_EVFA) = fa;
-                                    COLD(C_EVB) = h;
-                                    COLD(C_EVFB) = fb;
-                                    COLD(C_EVC) = h - fb * h / (fb - fa);
-                                    locate = true;
+                                if (ys.r < rd.r_src && ye.r >= rd.r_src) {
+                                    locate = F_LOCATE | F_EVSRC;
+                                    fa = ys.r - rd.r_src;
+                                    fb = ye.r - rd.r_src;
                                 } else {
-                                    const double dphi = yn[2] - y[2];
-                                    double arc = arc_angle_short(s0, c0, dg.s, dg.c, dphi);
-                                    if (arc < 0.0) arc = arc_angle(s0, c0, dg.s, dg.c, dphi);
-                                    COLD(C_PSI) += arc;
+                                    const double dphi = ye.ph - ys.ph;
+                                    bool in_range;
+                                    double arc = arc_angle_short(s0, c0, dg.s, dg.c, dphi, &in_range);
+                                    if (!in_range) arc = arc_angle(s0, c0, dg.s, dg.c, dphi);
+                                    swept += arc;
                                 }
                             }
                             if (!locate) {
-                                if (yn[0] > li.r_esc && (feat & FEAT_SKY)) {
+                                if (ye.r > rd.r_esc && (feat & FEAT_SKY)) {
                                     // locate the crossing of the celestial sphere
-                                    const double fa = y[0] - li.r_esc, fb = yn[0] - li.r_esc;
-                                    fl = (fl & ~(F_EVSRC | F_EV32 | (0xff << EVIT_SHIFT))) | F_EVESC | F_LOCATE | (use32 ? F_EV32 : 0);
-                                    COLD(C_EVA) = 0.0;
-                                    COLD(C_EVFA) = fa;
-                                    COLD(C_EVB) = h;
-                                    COLD(C_EVFB) = fb;
-                                    COLD(C_EVC) = h - fb * h / (fb - fa);
-                                } else if (yn[0] > li.r_esc) {
+                                    locate = F_LOCATE | F_EVESC;
+                                    fa = ys.r - rd.r_esc;
+                                    fb = ye.r - rd.r_esc;
+                                } else if (ye.r > rd.r_esc) {
                                     fate = KT_FATE_ESCAPED;
-                                    thf = yn[1];
-                                    phf = yn[2];
+                                    thf = ye.th;
+                                    phf = ye.ph;
                                 } else {
                                     // commit the step
-#pragma unroll
-                                    for (int i = 0; i < 5; ++i) {
-                                        y[i] = yn[i];
-                                        k1[i] = kn[i];
-                                    }
-                                    COLD(C_LAM) += h;
-                                    h = h_next;
-                                    fl &= ~(F_REJECTED | F_SKIPDISK);
-                                    COLD(C_CS) = dg.s;
-                                    COLD(C_CC) = dg.c;
+                                    ys = ye;
+                                    ks = ke;
+                                    unsafeAtomicAdd(&COLD(C_LAM), h);  // one LDS add, no result
+                                    if constexpr (ADAPTIVE) h *= fac;
+                                    fac_max = 5.0f;
+                                    fl &= ~F_SKIPDISK;
+                                    s0 = dg.s;
+                                    c0 = dg.c;
                                 }
                             }
                         }
                     }
+                    if (locate) {
+                        fl = (fl & ~(F_EVSRC | F_EVESC | F_EV32 | (0xff << EVIT_SHIFT))) | locate |
+                             (use32 ? F_EV32 : 0);
+                        COLD(C_H) = h;
+                        COLD(C_EVA) = 0.0;
+                        COLD(C_EVFA) = fa;
+                        COLD(C_EVB) = h;
+                        COLD(C_EVFB) = fb;
+                        h = h - fb * h / (fb - fa);
+                    }
                 }
             }
+            const int attempts = static_cast<int>(it - it0);
+            const int nevals = 1 + attempts * EVALS_PER_STEP, nsteps = attempts - misses;
+            if (fate < 0 && !(fl & (F_LOCATE | F_RETAKE)) && (nsteps >= hp.max_steps || nevals >= hp.max_evals)) {
+                fate = KT_FATE_MAXSTEPS;
+                thf = ys.th;
+                phf = ys.ph;
+            }
+            if (fate >= 0) {
+                if (fl & F_SRCDONE) {
+                    defl = COLD(C_DEFL);
+                    psi = COLD(C_SRCPSI);
+                }
+                fl &= ~(F_LOCATE | F_RETAKE);
+                write_outputs(fate, r_c, psi, defl, thf, phf, nsteps, nevals);
+            }
+            set_window(rd, ys.r);
         }
-
-        if (fate >= 0) {
-            const Outputs& o = P.out;
-            if (fl & F_SRCDONE) {
-                defl = COLD(C_PSI);
-                psi = COLD(C_SRCPSI);
-            }
-            o.fate[ray] = static_cast<uint8_t>(fate);
-            P.rc_buf[ray] = r_c;
-            if (o.max_abs_h) o.max_abs_h[ray] = COLD(C_MAXABS);
-            if (o.max_rel_h) o.max_rel_h[ray] = COLD(C_MAXREL);
-            if (o.psi) o.psi[ray] = psi;
-            if (o.deflection) o.deflection[ray] = defl;
-            if (o.theta_f) o.theta_f[ray] = thf;
-            if (o.phi_f) o.phi_f[ray] = phf;
-            if (o.n_cross) o.n_cross[ray] = static_cast<uint8_t>((fl >> NCROSS_SHIFT) & 0xff);
-            if (o.used_fp64) o.used_fp64[ray] = static_cast<uint8_t>(P.from_list ? 1 : 0);
-            if (o.n_steps) o.n_steps[ray] = nsteps;
-            if (o.n_evals) o.n_evals[ray] = nevals;
-            if constexpr (MIXED) {
-                const double mr = COLD(C_MAXREL);
-                P.need_fb[ray] = ((fl & F_USED32) && !(mr <= hp.h_budget)) ? 1 : 0;
-            }
-            evals_acc += static_cast<unsigned long long>(nevals);
-            ray = -1;
+        in_event = __ballot(ray >= 0 && (fl & (F_LOCATE | F_RETAKE)) != 0);
+        if (it == it_limit) {
+            // the next attempt at which a lane's budget may end
+            const int attempts = static_cast<int>(it - it0);
+            const int evals_left = hp.max_evals - (1 + attempts * EVALS_PER_STEP);
+            int left = max(1, min(hp.max_steps - (attempts - misses),
+                                  (evals_left + EVALS_PER_STEP - 1) / EVALS_PER_STEP));
+            int least = static_cast<int>(budget);
+            for (unsigned long long m = __ballot(ray >= 0); m != 0ull; m &= m - 1ull)
+                least = min(least, __builtin_amdgcn_readlane(left, __ffsll(m) - 1));
+            it_limit = it + static_cast<uint32_t>(least);
         }
     }
 #undef COLD
 
     // one atomic per wave for each evaluation counter
-    for (int off = 32; off > 0; off >>= 1) evals_acc += __shfl_down(evals_acc, off);
-    if (lane == 0 && evals_acc != 0ull) atomicAdd(P.acc + ACC_EVALS, evals_acc);
+    const unsigned long long evals = wave_sum(evals_acc);
+    if (lane == 0 && evals != 0ull) atomicAdd(hp.acc + ACC_EVALS, evals);
     if constexpr (MIXED) {
-        for (int off = 32; off > 0; off >>= 1) evals32_acc += __shfl_down(evals32_acc, off);
-        if (lane == 0 && evals32_acc != 0ull) atomicAdd(P.acc + ACC_EVALS_FP32, evals32_acc);
+        const unsigned long long evals32 = wave_sum(evals32_acc);
+        if (lane == 0 && evals32 != 0ull) atomicAdd(hp.acc + ACC_EVALS_FP32, evals32);
     }
 }
 
@@ -922,14 +1120,13 @@ static Hot make_hot(const Params& p) {
     hp.atol = p.atol;
     hp.r_cap = im.r_cap;
     hp.r_esc = im.r_esc;
-    hp.r_src = im.r_src;
-    hp.r_in = im.r_in;
-    hp.r_out = im.r_out;
     hp.h_budget = p.h_budget;
     hp.r_switch = p.r_switch;
     hp.feat = image_features(im);
     hp.max_steps = static_cast<int32_t>(p.max_steps);
     hp.max_evals = static_cast<int32_t>(p.max_evals);
+    hp.first = 64;
+    hp.acc = p.acc;
     hp.cold = p.ws_params;
     return hp;
 }
