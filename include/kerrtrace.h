@@ -165,17 +165,18 @@ typedef struct kt_integrator {
    wave's first fetch from the ticket takes 64 ids (one per lane); batch
    applies to the fetches after it.
    The trace kernels exist in two builds with bit-identical outputs: one for
-   2 waves per SIMD and one for 3 (fewer registers, a few more instructions
-   per step).  A persistent launch runs the 3-wave build when its shape asks
-   for 3 or more waves per SIMD (blocks_per_cu * block >= 768), or, with
-   blocks_per_cu 0, when the render has at least 4 rays per lane of a
-   3-wave grid (about 790k rays on 256 CUs); then blocks_per_cu 0 means the
-   3-wave build's occupancy.  Other launches run the 2-wave build. */
+   up to 2 waves per SIMD and one for 3 (fewer registers, more scalar
+   instructions per step).  A persistent launch runs the 3-wave build when its
+   shape asks for 3 or more waves per SIMD (blocks_per_cu * block >= 768).
+   blocks_per_cu 0 picks the waves per SIMD from the number of rays: 1 up to 4
+   rays per lane of a one-wave grid (262144 rays on 256 CUs), 3 from 12 rays
+   per lane (786432), 2 between; for the Bulirsch-Stoer schemes 1 up to 10
+   rays per lane, then 3.  Other launches run the 2-wave build. */
 typedef struct kt_launch {
     int32_t persistent;     /* 1: persistent waves refill lanes from a global ticket;
                                0: one ray per lane, no refill */
     int32_t block;          /* threads per workgroup: 64, 128 or 256 */
-    int32_t blocks_per_cu;  /* persistent grid = CUs * blocks_per_cu; 0 = occupancy */
+    int32_t blocks_per_cu;  /* persistent grid = CUs * blocks_per_cu; 0 = by the number of rays */
     int32_t batch;          /* ray ids taken per ticket fetch after a wave's first, 1..4096 */
     int32_t order;          /* KT_ORDER_RING (0) or KT_ORDER_ROWS: the order rays go out in */
 } kt_launch;

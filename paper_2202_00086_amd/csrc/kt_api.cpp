@@ -76,25 +76,32 @@ double device_wall_khz() {
     return cache[dev] > 0 ? static_cast<double>(cache[dev]) : 0.0;
 }
 
-// Which build of the trace kernels a launch runs (both give the same
-// outputs bit for bit).  The 3-wave form (kt_trace_w3.hip) keeps the VALU
-// busier, but each ray takes longer in wall time, so the end of a persistent
-// launch, which waits for the last rays, grows; it pays once every lane of a
-// 3-wave grid has enough rays to trace, and it is the only form that can run
-// a launch shape of 3 or more waves per SIMD.  With the priority cycle of
-// the 3-wave kernels, at 1024x1024 (5.3 rays per lane) it was 1-3% faster
-// on ring, lensing, disk and q-metric images; at 724x724 (2.7 per lane) 5%
-// faster on a ring image but 4-11% slower on lensing, disk and q-metric ones.
-constexpr int64_t W3_MIN_RAYS_PER_LANE = 4;
+// Waves per SIMD of a persistent launch without a shape of its own, and with
+// them which build of the trace kernels runs (both give the same outputs bit
+// for bit): 3 waves mean the 3-wave form (kt_trace_w3.hip).  More waves keep
+// the VALU busier, but each ray then takes longer in wall time, and the
+// launch ends with its longest rays, so the choice goes by the rays per lane
+// of a one-wave grid (65536 lanes on 256 CUs).  Measured, ms per image at
+// 1 / 2 / 3 waves, on ring, lensing, disk and q-metric images:
+//   362x362 (2 rays per lane)    3.56/4.30/4.72  3.04/3.49/4.01  2.42/2.64/2.49  5.62/7.02/7.22
+//   512x512 (4)                  6.01/5.82/7.03  3.65/3.88/5.17  3.93/4.09/4.41  7.31/8.04/9.51
+//   600x600 (5.5)                7.65/7.05/7.76  4.76/4.62/6.19  5.15/4.89/5.35  9.68/9.67/11.2
+//   900x900 (12.4)               16.6/13.9/13.9  10.2/8.62/8.80  11.0/9.24/9.39  20.7/18.2/18.5
+//   1024x1024 (16)               21.3/17.5/16.8  13.1/10.8/10.7  14.1/11.6/11.7  26.6/22.8/23.0
+// and 3 waves are 2-4% ahead of 2 on images of 2M rays and more.  A
+// Bulirsch-Stoer step is 26 evaluations without the registers' worth of
+// staged values, and two waves never lead: 724x724 5.99/7.02/6.24, 900x900
+// 8.94/9.43/8.46, 1024x1024 11.4/11.1/10.5.
+constexpr int64_t ONE_WAVE_MAX_RAYS_PER_LANE = 4, THREE_WAVE_MIN_RAYS_PER_LANE = 12, BS_ONE_WAVE_MAX_RAYS_PER_LANE = 10;
+
+int waves_per_simd(int32_t method, int64_t n_rays) {
+    const int64_t lanes = static_cast<int64_t>(device_cus()) * 4 * 64;
+    if (method == KT_BS || method == KT_BS_RAT) return n_rays <= BS_ONE_WAVE_MAX_RAYS_PER_LANE * lanes ? 1 : 3;
+    if (n_rays <= ONE_WAVE_MAX_RAYS_PER_LANE * lanes) return 1;
+    return n_rays >= THREE_WAVE_MIN_RAYS_PER_LANE * lanes ? 3 : 2;
+}
 
 constexpr int32_t DEFAULT_BATCH = 4;  // ids per ticket fetch after a wave's first
-
-bool three_wave_form(const kt_launch& ln, int64_t n_rays) {
-    if (!ln.persistent) return false;
-    if (ln.blocks_per_cu > 0) return static_cast<int64_t>(ln.blocks_per_cu) * ln.block >= 3 * 256;
-    const int64_t lanes = static_cast<int64_t>(device_cus()) * 4 * 3 * 64;
-    return n_rays >= W3_MIN_RAYS_PER_LANE * lanes;
-}
 
 double horizon(const kt_spacetime* st) {
     if (st->metric == KT_METRIC_Q) return 2.0 * st->M;
@@ -397,12 +404,16 @@ int render_images(const kt::Image* table, int32_t n_images, int64_t n_rays, cons
     p.from_list = 0;
     p.wall_khz = out->stats ? device_wall_khz() : 0.0;
     const int64_t lane_grid = (n_rays + ln.block - 1) / ln.block;
-    const bool w3 = three_wave_form(ln, n_rays);
+    // a shape that asks for 3 or more waves per SIMD runs the 3-wave form
+    const int waves = ln.blocks_per_cu > 0 ? (ln.blocks_per_cu * ln.block) / 256 : waves_per_simd(p.method, n_rays);
+    const bool w3 = p.persistent && waves >= 3;
     int grid;
     if (p.persistent) {
-        const int per_cu = ln.blocks_per_cu > 0 ? ln.blocks_per_cu
-                           : w3                 ? kt_w3::trace_max_blocks_per_cu(p, ln.block)
-                                                : kt::trace_max_blocks_per_cu(p, ln.block);
+        int per_cu = ln.blocks_per_cu;
+        if (per_cu == 0) {
+            const int fit = w3 ? kt_w3::trace_max_blocks_per_cu(p, ln.block) : kt::trace_max_blocks_per_cu(p, ln.block);
+            per_cu = std::min(fit, waves * 256 / ln.block);
+        }
         grid = device_cus() * per_cu;
         if (grid > lane_grid) grid = static_cast<int>(lane_grid);
     } else {
