@@ -2,33 +2,33 @@
 // per pixel) with respect to the spin a, the inclination and the disk's
 // inner radius.
 //
-// Per ray (one per lane; lanes take rays from an atomic ticket over a list of
-// the differentiated rays sorted by forward step count):
+// Per ray:
 //   1. re-integrate from the camera with the trace kernel's own stepper and
-//      controller (bit-identical steps), keeping a checkpoint (state, trial
-//      step) every 2^ck_shift accepted steps (64 by default), up to the
-//      located disk crossing;
+//      controller (bit-identical steps) up to the located disk crossing;
 //   2. seed the cotangent of the crossing state from the intensity's
 //      derivatives, with the crossing-time correction that keeps theta on
 //      the equatorial plane;
 //   3. run the vector-Jacobian products of the Dormand-Prince steps backward
-//      with the accepted step sizes frozen: the located partial step first,
-//      then each segment between checkpoints, recomputed forward from its
-//      checkpoint;
+//      with the accepted step sizes frozen, the located partial step first;
 //   4. chain the cotangents of the initial state and of (E, L) through the
 //      camera's dependence on (a, inclination).
-// With the forward step counts, the longest rays (the head of the list) can
-// have their step 3 split over several lanes instead: step 1 stores every
-// accepted step, then each 64-step segment is swept backward from four
-// basis cotangents at once, one lane each (the segment's transposed
-// Jacobian, a linear map since the steps are frozen), and a last pass
-// applies the segments' maps to the ray's seeded cotangent in order.  The
-// backward sweep of a ray is otherwise one lane's sequential work, and the
-// longest ray's sets the run time of the whole adjoint.
+// With the forward step counts these are kernels of their own.  Step 1 is the
+// trace kernel itself (its STORE form) with every accepted step written to a
+// store; step 3 reads the steps back, one item per lane at two waves per
+// SIMD.  A long ray's sweep is split: each 64-step segment is swept backward
+// from four basis cotangents (its transposed Jacobian, a linear map since the
+// steps are frozen), one lane each, and the last kernel applies the segments'
+// maps to the ray's seeded cotangent in order.  A sweep is otherwise one
+// lane's sequential work, and the longest would set the run time.
+// Rays beyond the store, and all of them without step counts or with split
+// sweeps off, take the one-lane path (adjoint_kernel): checkpoints every
+// 2^ck_shift accepted steps and each segment between them recomputed.
 // The results are the per-pixel products cot_I * dI/d(a, incl, r_in) and,
 // on request, their three sums over the image (a fixed-order block-then-grid
 // reduction, so the sums do not depend on which lane ran which ray).
 #include <hip/hip_runtime.h>
+
+#include <cstring>
 
 #include "kt_adjoint_math.h"
 #include "kt_device.h"
@@ -38,15 +38,12 @@
 
 namespace kt {
 
-enum : int { ADJ_OK = 0, ADJ_FAIL = 1, ADJ_OVERFLOW = 2, ADJ_MISMATCH = 3 };
-
 // Where the forward pass keeps states: entry idx at p + idx * istride, its
 // field f (0..4 the state, 5 a step size) at + f * fstride, at most cap
 // entries.  With shift > 0 entry c is the state after c * 2^shift accepted
 // steps and the trial size of the next step (entry 0 the start); with shift
 // 0 entry j is the start state of accepted step j and its accepted size.
-// A lane's checkpoints and segment slots sit in [index][field][lane]
-// arrays; a split ray's steps in its own range of the split-ray store.
+// A lane's checkpoints and segment slots sit in [index][field][lane] arrays.
 struct StepStore {
     double* p;
     size_t istride, fstride;
@@ -192,20 +189,19 @@ __device__ __forceinline__ int forward_to_hit(const AdjParams& P, const Spacetim
     return ADJ_OK;
 }
 
-// 2. Seeds from the intensity with the crossing-time correction, then the
-// vector-Jacobian product of the located partial step.
-__device__ __forceinline__ void seed_partial(const AdjParams& P, const Fwd& f, double w, double zb[5],
-                                             adj::ParBar* pb, double* gr) {
+// 2. Seeds from the intensity at crossing radius r_c with the crossing-time
+// correction; (dr_c, dth_c) are r' and theta' there.
+__device__ __forceinline__ void seed(const AdjParams& P, double r_c, double dr_c, double dth_c, double E, double L,
+                                     double w, double zb[5], adj::ParBar* pb, double* gr) {
     const Image& im = P.im;
-    const Dual<5> I = adj::disk_intensity(P.dm, f.zs[0], f.E, f.L, im.a, im.r_in);
+    const Dual<5> I = adj::disk_intensity(P.dm, r_c, E, L, im.a, im.r_in);
     *pb = adj::ParBar{w * I.d[1], w * I.d[2], w * I.d[3]};
     *gr = w * I.d[4];
     const double rbar = w * I.d[0];
     // r_c = r(lambda*) with theta(lambda*) = pi/2: dr_c = dr - (r' / theta') dtheta
     zb[0] = rbar;
-    zb[1] = -rbar * f.ks[0] / f.ks[1];
+    zb[1] = -rbar * dr_c / dth_c;
     zb[2] = zb[3] = zb[4] = 0.0;
-    adj::dp_step_vjp(im.M, im.a, f.E, f.L, f.y, f.hstar, zb, pb);
 }
 
 // 3. The rest of the reverse sweep with frozen steps, from the lane's own
@@ -222,7 +218,7 @@ __device__ __forceinline__ int sweep_lane(const AdjParams& P, const Spacetime& s
         for (int j = n - 1; j >= 0; --j) {
             double yj[5], hj;
             get6(P.ckpt + j * is + lane, fs, yj, &hj);
-            adj::dp_step_vjp(im.M, im.a, f.E, f.L, yj, hj, zb, pb);
+            adj::dp_step_vjp<false>(im.M, im.a, f.E, f.L, yj, hj, zb, pb);
         }
         return ADJ_OK;
     }
@@ -262,7 +258,7 @@ __device__ __forceinline__ int sweep_lane(const AdjParams& P, const Spacetime& s
         for (int j = last - 1; j >= first; --j) {
             double yj[5], hj;
             get6(P.seg + (j - first) * is + lane, fs, yj, &hj);
-            adj::dp_step_vjp(im.M, im.a, f.E, f.L, yj, hj, zb, pb);
+            adj::dp_step_vjp<false>(im.M, im.a, f.E, f.L, yj, hj, zb, pb);
         }
     }
     return ADJ_OK;
@@ -299,146 +295,49 @@ __device__ __forceinline__ void put_grads(const AdjParams& P, int32_t ray, int s
     if (P.grad_rin) P.grad_rin[ray] = gr;
 }
 
-// One entry t of the work list on this lane.  An entry among the first
-// n_long (the split rays) that fits the split-ray store runs the forward
-// pass into the store, seeds its cotangent, reserves its segment items and
-// leaves the rest to the segment and combine kernels; every other entry
-// runs the whole adjoint of its ray on this lane.
-__device__ __forceinline__ void adjoint_entry(const AdjParams& P, const Spacetime& st, int lane, uint32_t t,
-                                              uint32_t n_long) {
+// One entry t of the work list, the whole adjoint of its ray on this lane.
+__device__ __forceinline__ void adjoint_entry(const AdjParams& P, const Spacetime& st, int lane, uint32_t t) {
+    const Image& im = P.im;
     const int32_t ray = static_cast<int32_t>(P.list[t]);
     const size_t fs = static_cast<size_t>(P.n_lanes);
-    StepStore sto{P.ckpt + lane, 6u * fs, fs, P.max_ckpt, P.ck_shift};
-    bool split = false;
-    if (t < n_long) {
-        // a split ray: every step into its own range of the store
-        AdjLong& rec = P.longs[t];
-        rec.ray = ray;
-        rec.status = ADJ_LONG_DONE;
-        const int32_t steps = P.n_steps[ray];
-        const uint32_t cap = steps >= 0 ? static_cast<uint32_t>(steps) + 2u : 0u;
-        if (cap > 2u && cap <= static_cast<uint32_t>(ADJ_SEG * ADJ_SEG_MAX)) {
-            const uint32_t base = atomicAdd(P.counters + 1, cap);
-            if (static_cast<uint64_t>(base) + cap <= P.long_cap) {
-                sto = StepStore{P.long_store + static_cast<size_t>(base) * 6u, 6u, 1u, static_cast<int32_t>(cap), 0};
-                rec.base = base;
-                split = true;
-            }
-        }
-    }
+    const StepStore sto{P.ckpt + lane, 6u * fs, fs, P.max_ckpt, P.ck_shift};
     Fwd f;
     double zb[5], ga = 0.0, gi = 0.0, gr = 0.0;
     adj::ParBar pb;
     int status = forward_to_hit(P, st, ray, sto, &f);
-    if (status == ADJ_OK) seed_partial(P, f, P.cot[ray], zb, &pb, &gr);
-    if (split && status == ADJ_OK) {
-        AdjLong& rec = P.longs[t];
-        const int n_seg = (f.n + ADJ_SEG - 1) / ADJ_SEG;
-        const uint32_t n_items = 4u * static_cast<uint32_t>(n_seg);
-        const uint32_t ib = atomicAdd(P.counters + 2, n_items);
-        if (static_cast<uint64_t>(ib) + n_items <= P.item_cap) {
-            for (uint32_t i = 0; i < n_items; ++i) P.owner[ib + i] = t;
-            rec.n = f.n;
-            rec.n_seg = n_seg;
-            rec.item_base = ib;
-            rec.zb[0] = zb[0];
-            rec.zb[1] = zb[1];
-            rec.zb[2] = zb[3];
-            rec.zb[3] = zb[4];
-            rec.pb[0] = pb.E;
-            rec.pb[1] = pb.L;
-            rec.pb[2] = pb.a;
-            rec.gr = gr;
-            rec.E = f.E;
-            rec.L = f.L;
-            rec.status = ADJ_LONG_SPLIT;
-            return;  // the combine kernel finishes this ray
-        }
-        status = ADJ_OVERFLOW;  // cannot happen: the item space covers the store
+    if (status == ADJ_OK) {
+        seed(P, f.zs[0], f.ks[0], f.ks[1], f.E, f.L, P.cot[ray], zb, &pb, &gr);
+        adj::dp_step_vjp<false>(im.M, im.a, f.E, f.L, f.y, f.hstar, zb, &pb);
+        status = sweep_lane(P, st, lane, f, zb, &pb);
     }
-    if (!split && status == ADJ_OK) status = sweep_lane(P, st, lane, f, zb, &pb);
     if (status == ADJ_OK) camera_chain(P, ray, zb, pb, &ga, &gi);
     put_grads(P, ray, status, ga, gi, gr);
 }
 
-// One wave per SIMD: the unrolled step VJP wants about 500 VGPRs, and a
-// two-wave budget (256) spills enough to run 1.6x slower.
-#ifndef KT_ADJ_WAVES_PER_EU
-#define KT_ADJ_WAVES_PER_EU 1
-#endif
-// Lanes take entries of the work list from an atomic ticket.
-__global__ void __launch_bounds__(ADJ_BLOCK) __attribute__((amdgpu_waves_per_eu(KT_ADJ_WAVES_PER_EU)))
+// Lanes take the entries of the work list that are not stored from an atomic
+// ticket.  One wave per SIMD: the forward pass, its recomputation and the
+// step VJP in one kernel want more than a two-wave budget.
+__global__ void __launch_bounds__(ADJ_BLOCK) __attribute__((amdgpu_waves_per_eu(1)))
 adjoint_kernel(const AdjParams P) {
     const int lane = blockIdx.x * blockDim.x + threadIdx.x;
     if (lane >= P.n_lanes) return;
     const Spacetime st{P.im.M, P.im.a, P.im.a2, P.im.two_a2};
-    const uint32_t n_list = P.hist[SORT_BINS];
-    const uint32_t n_long = P.max_long > 0 ? P.counters[0] : 0u;
+    const bool stored = P.max_long > 0;
+    const uint32_t first = stored ? P.counters[ADJ_C_FIRST] : 0u, end = stored ? P.counters[ADJ_C_END] : 0u;
+    const uint32_t n = P.hist[SORT_BINS] - (end - first);
     for (;;) {
-        const uint32_t t = atomicAdd(P.ticket, 1u);
-        if (t >= n_list) break;
-        adjoint_entry(P, st, lane, t, n_long);
+        uint32_t t = atomicAdd(P.ticket, 1u);
+        if (t >= n) break;
+        if (t >= first) t += end - first;
+        adjoint_entry(P, st, lane, t);
     }
 }
 
-// The split threshold and n_long, from the sorted work list's bins (one
-// block, after the sort: hist[k] is then the end of bin k, and bin k holds
-// the rays of 4 v to 4 v + 3 forward steps, v = SORT_BINS - 1 - k, bin 0
-// also every longer ray).  The automatic threshold is 0.85 times the mean
-// step count per lane of the grid: rays near that length or longer would
-// outlast the rest of the list.  The split rays are whole bins, longest
-// first, as many as the records and the split-ray store hold for certain (a
-// ray of bin v takes at most 4 v + 5 entries of the store; rays beyond
-// ADJ_SEG * ADJ_SEG_MAX - 2 steps are never split): which rays are split
-// then does not depend on the order in which lanes take them, and neither
-// do the gradients.  The store's size (ADJ_LONG_STEPS_PER_LANE steps per
-// lane) thereby bounds the extra work of the basis sweeps, four step VJPs
-// per stored step.
-__global__ void __launch_bounds__(SORT_BLOCK) adjoint_split_kernel(const AdjParams P) {
-    constexpr int PER = SORT_BINS / SORT_BLOCK;  // consecutive bins per thread
-    static_assert(SORT_BINS % SORT_BLOCK == 0, "bins must split evenly over the block");
-    __shared__ unsigned long long part[SORT_BLOCK];
-    __shared__ long long thr;
-    __shared__ int stop;
+// Inclusive sums over the block's threads (Hillis-Steele).
+__device__ __forceinline__ unsigned long long block_scan(unsigned long long v, unsigned long long* part) {
     const int t = threadIdx.x;
-    uint32_t cnt[PER];
-    unsigned long long steps = 0;
-    for (int i = 0; i < PER; ++i) {
-        const int k = t * PER + i;
-        cnt[i] = P.hist[k] - (k > 0 ? P.hist[k - 1] : 0u);
-        steps += static_cast<unsigned long long>(cnt[i]) * static_cast<unsigned long long>(4 * (SORT_BINS - 1 - k) + 2);
-    }
-    part[t] = steps;
-    if (t == 0) stop = SORT_BINS;
     __syncthreads();
-    for (int w = SORT_BLOCK / 2; w > 0; w >>= 1) {
-        if (t < w) part[t] += part[t + w];
-        __syncthreads();
-    }
-    if (t == 0) {
-        long long T = P.split_above;
-        if (T <= 0) {
-            T = static_cast<long long>((17ull * part[0]) / (20ull * static_cast<unsigned long long>(P.n_lanes)));
-            if (T < ADJ_SPLIT_MIN) T = ADJ_SPLIT_MIN;
-        }
-        thr = T;
-    }
-    __syncthreads();
-    // bins above the threshold's: keys below kT; their store demand, at
-    // most 4 v + 5 entries per ray of bin v, for bins that can hold a ray
-    // short enough to split
-    const long long kT = SORT_BINS - 1 - (thr >> 2);
-    unsigned long long demand = 0;
-    for (int i = 0; i < PER; ++i) {
-        const int k = t * PER + i;
-        const long long v = SORT_BINS - 1 - k;
-        if (k < kT && 4 * v + 2 <= ADJ_SEG * ADJ_SEG_MAX)
-            demand += static_cast<unsigned long long>(cnt[i]) *
-                      static_cast<unsigned long long>(4 * v + 5 < ADJ_SEG * ADJ_SEG_MAX ? 4 * v + 5 : ADJ_SEG * ADJ_SEG_MAX);
-    }
-    // exclusive scan of the threads' demands (Hillis-Steele)
-    __syncthreads();
-    part[t] = demand;
+    part[t] = v;
     __syncthreads();
     for (int off = 1; off < SORT_BLOCK; off <<= 1) {
         const unsigned long long add = t >= off ? part[t - off] : 0ull;
@@ -446,110 +345,263 @@ __global__ void __launch_bounds__(SORT_BLOCK) adjoint_split_kernel(const AdjPara
         part[t] += add;
         __syncthreads();
     }
-    unsigned long long run = part[t] - demand;
-    // the first bin that is past the threshold, or whose end passes the
-    // records or whose demand passes the store
+    return part[t];
+}
+
+// Which rays are stored and which of them split, from the sorted work list's
+// bins (one block, after the sort: hist[k] is then the end of bin k, and bin
+// k holds the rays of 4 v to 4 v + 3 forward steps, v = SORT_BINS - 1 - k, bin
+// 0 also every longer ray).  Both are whole bins, longest first, so that the
+// sets, and with them the gradients, do not depend on which lanes take the
+// rays: stored are bins 1, 2, ... as long as the store and the records hold
+// them for certain (a ray of bin v takes at most 4 v + 5 entries); bin 0 has
+// no such bound and is left to the one-lane path.
+// A split sweep takes four step VJPs per step instead of one, in pieces of
+// ADJ_SEG steps instead of the ray's length.  The longest bins are split until
+// the longest sweep left is no longer than the sweep kernel's work per lane,
+// (all steps + 3 times the split ones) / lanes: splitting fewer would leave
+// that sweep running alone at the end, splitting more only adds work.  With a
+// threshold of the caller's, the rays above it are split.
+__global__ void __launch_bounds__(SORT_BLOCK) adjoint_split_kernel(const AdjParams P) {
+    constexpr int PER = SORT_BINS / SORT_BLOCK;  // consecutive bins per thread
+    static_assert(SORT_BINS % SORT_BLOCK == 0, "bins must split evenly over the block");
+    __shared__ unsigned long long part[SORT_BLOCK];
+    __shared__ unsigned long long all_steps;
+    __shared__ int stop_store, stop_split;
+    const int t = threadIdx.x;
+    const uint32_t first = P.hist[0];
+    if (t == 0) stop_store = stop_split = SORT_BINS;
+    uint32_t cnt[PER];
+    unsigned long long need = 0;
     for (int i = 0; i < PER; ++i) {
         const int k = t * PER + i;
-        const long long v = SORT_BINS - 1 - k;
-        if (k < kT && 4 * v + 2 <= ADJ_SEG * ADJ_SEG_MAX)
-            run += static_cast<unsigned long long>(cnt[i]) *
-                   static_cast<unsigned long long>(4 * v + 5 < ADJ_SEG * ADJ_SEG_MAX ? 4 * v + 5 : ADJ_SEG * ADJ_SEG_MAX);
-        if (k >= kT || P.hist[k] > static_cast<uint32_t>(P.max_long) || run > P.long_cap) {
-            atomicMin(&stop, k);
+        cnt[i] = k > 0 ? P.hist[k] - P.hist[k - 1] : 0u;
+        need += static_cast<unsigned long long>(cnt[i]) * static_cast<unsigned long long>(4 * (SORT_BINS - 1 - k) + 5);
+    }
+    unsigned long long run = block_scan(need, part) - need;
+    const unsigned long long entries = static_cast<unsigned long long>(P.long_cap) * 6ull / ADJ_ENTRY;
+    for (int i = 0; i < PER; ++i) {
+        const int k = t * PER + i;
+        run += static_cast<unsigned long long>(cnt[i]) * static_cast<unsigned long long>(4 * (SORT_BINS - 1 - k) + 5);
+        if (cnt[i] != 0u && (run > entries || P.hist[k] - first > static_cast<uint32_t>(P.max_long))) {
+            atomicMin(&stop_store, k);
             break;
         }
     }
     __syncthreads();
-    if (t == 0) P.counters[0] = stop > 0 ? P.hist[stop - 1] : 0u;
-}
-
-// The segments of the split rays: item w sweeps segment s of its ray
-// backward from the basis cotangent e_b (b over r, theta, p_r, p_theta)
-// with zero parameter cotangents, and stores the resulting cotangents of
-// (r, theta, p_r, p_theta, E, L, a, phi): column b of the segment's
-// transposed Jacobian.  Every item of a wave sweeps the same number of
-// steps, and the four of a segment the same states.
-__global__ void __launch_bounds__(ADJ_BLOCK) __attribute__((amdgpu_waves_per_eu(KT_ADJ_WAVES_PER_EU)))
-adjoint_segment_kernel(const AdjParams P) {
-    const Image& im = P.im;
-    const uint32_t used = P.counters[2];
-    const uint32_t total = used < P.item_cap ? used : P.item_cap;
-    const uint32_t stride = gridDim.x * blockDim.x;
-    for (uint32_t w = blockIdx.x * blockDim.x + threadIdx.x; w < total; w += stride) {
-        const uint32_t k = P.owner[w];
-        if (k >= static_cast<uint32_t>(P.max_long)) continue;
-        const AdjLong& rec = P.longs[k];
-        if (rec.status != ADJ_LONG_SPLIT) continue;
-        const uint32_t local = w - rec.item_base;
-        if (local >= 4u * static_cast<uint32_t>(rec.n_seg)) continue;
-        const int s = static_cast<int>(local >> 2), b = static_cast<int>(local & 3u);
-        const int first = s * ADJ_SEG, last = min(rec.n, first + ADJ_SEG);
-        double yb[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-        yb[b < 2 ? b : b + 1] = 1.0;
-        adj::ParBar pb{0.0, 0.0, 0.0};
-        const double* base = P.long_store + static_cast<size_t>(rec.base) * 6u;
-        for (int j = last - 1; j >= first; --j) {
-            double yj[5], hj;
-            get6(base + static_cast<size_t>(j) * 6u, 1u, yj, &hj);
-            adj::dp_step_vjp(im.M, im.a, rec.E, rec.L, yj, hj, yb, &pb);
+    // steps and segment items of the stored bins, and the bins to split
+    unsigned long long steps = 0, items = 0;
+    for (int i = 0; i < PER; ++i) {
+        const int k = t * PER + i, v = SORT_BINS - 1 - k;
+        if (k >= stop_store) cnt[i] = 0u;
+        steps += static_cast<unsigned long long>(cnt[i]) * static_cast<unsigned long long>(4 * v + 2);
+        items += static_cast<unsigned long long>(cnt[i]) * static_cast<unsigned long long>(4 * ((4 * v + 4) / ADJ_SEG + 1));
+    }
+    unsigned long long run_steps = block_scan(steps, part);
+    if (t == SORT_BLOCK - 1) all_steps = run_steps;
+    run_steps -= steps;
+    unsigned long long run_items = block_scan(items, part) - items;
+    for (int i = 0; i < PER; ++i) {
+        const int k = t * PER + i, v = SORT_BINS - 1 - k;
+        // run_steps: the steps of the bins before this one
+        const unsigned long long load = (all_steps + 3ull * run_steps) / static_cast<unsigned long long>(P.grid_lanes);
+        const unsigned long long longest = static_cast<unsigned long long>(4 * v + 3);
+        const bool enough = P.split_above > 0 ? 4 * v <= P.split_above
+                                              : longest <= (load > ADJ_SEG ? load : ADJ_SEG);
+        run_steps += static_cast<unsigned long long>(cnt[i]) * static_cast<unsigned long long>(4 * v + 2);
+        run_items += static_cast<unsigned long long>(cnt[i]) * static_cast<unsigned long long>(4 * ((4 * v + 4) / ADJ_SEG + 1));
+        if (k > 0 && (enough || k >= stop_store || run_items > P.item_cap)) {
+            atomicMin(&stop_split, k);
+            break;
         }
-        double* o = P.items + static_cast<size_t>(w) * 8u;
-        o[0] = yb[0];
-        o[1] = yb[1];
-        o[2] = yb[3];
-        o[3] = yb[4];
-        o[4] = pb.E;
-        o[5] = pb.L;
-        o[6] = pb.a;
-        o[7] = yb[2];
+    }
+    __syncthreads();
+    if (t == 0) {
+        P.counters[ADJ_C_FIRST] = first;
+        P.counters[ADJ_C_END] = P.hist[stop_store - 1];
+        P.counters[ADJ_C_SPLIT] = P.hist[stop_split - 1] - first;
     }
 }
 
-// Each split ray: its seeded cotangent through the segments' maps, last
-// segment first (cotangent' = sum_b cotangent_b * column_b, parameter
-// cotangents += sum_b cotangent_b * their column_b), then the camera.
+// The seeds of the stored rays, from the crossing that the forward pass left
+// in each record, and the items of the split ones.
+__global__ void __launch_bounds__(ADJ_BLOCK) adjoint_seed_kernel(const AdjParams P) {
+    const uint32_t n = P.counters[ADJ_C_END] - P.counters[ADJ_C_FIRST], n_split = P.counters[ADJ_C_SPLIT];
+    for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x) {
+        AdjLong& rec = P.longs[k];
+        if (rec.status != ADJ_OK) continue;
+        double zb[5], gr;
+        adj::ParBar pb;
+        seed(P, rec.zb[0], rec.zb[1], rec.zb[2], rec.E, rec.L, P.cot[rec.ray], zb, &pb, &gr);
+        rec.zb[0] = zb[0];
+        rec.zb[1] = zb[1];
+        rec.zb[2] = rec.zb[3] = 0.0;
+        rec.pb[0] = pb.E;
+        rec.pb[1] = pb.L;
+        rec.pb[2] = pb.a;
+        rec.gr = gr;
+        if (k >= n_split) continue;
+        const uint32_t n_seg = static_cast<uint32_t>(rec.n) / ADJ_SEG + 1u;  // of n + 1 entries
+        const uint32_t ib = atomicAdd(P.counters + ADJ_C_ITEMS, 4u * n_seg);
+        rec.n_seg = static_cast<int32_t>(n_seg);
+        rec.item_base = ib;
+        // the split kernel left room for every split ray's items
+        if (ib + 4u * n_seg > P.item_cap) rec.status = ADJ_OVERFLOW;
+        for (uint32_t i = 0; i < 4u * n_seg && ib + i < P.item_cap; ++i) P.owner[ib + i] = k;
+    }
+}
+
+// The sweeps: the unsplit stored rays, longest first, then the split rays'
+// segment items.  Each lane works through one of them, a step VJP per
+// iteration from the step's entry in the store (the next one's is fetched
+// meanwhile), and takes another from the wave's ticket when it is done; lanes
+// of a wave need not run rays of one length.
+//
+// Bound by the FP64 vector issue rate: ~1300 vector instructions per step of
+// a wave, 40 bytes read per lane and step.  Two waves per SIMD fit (see
+// stage_fence) and hide each other's loads.
+__global__ void __launch_bounds__(ADJ_BLOCK) __attribute__((amdgpu_waves_per_eu(2)))
+adjoint_sweep_kernel(const AdjParams P) {
+    const double M = P.im.M, a = P.im.a;
+    const uint32_t n_split = P.counters[ADJ_C_SPLIT];
+    const uint32_t n_whole = P.counters[ADJ_C_END] - P.counters[ADJ_C_FIRST] - n_split;
+    const uint32_t total = n_whole + min(P.counters[ADJ_C_ITEMS], P.item_cap);
+    bool more = true;
+    int left = -1;  // steps of this lane's item still to do, after the current one; -1: idle
+    uint32_t item = 0;
+    const double* e = nullptr;  // the current step's entry
+    double y0 = 0.0, y1 = 0.0, y3 = 0.0, y4 = 0.0, h = 0.0, E = 0.0, L = 0.0;
+    double b0 = 0.0, b1 = 0.0, b3 = 0.0, b4 = 0.0;
+    adj::ParBar pb{0.0, 0.0, 0.0};
+    for (;;) {
+        unsigned long long idle = __ballot(left < 0);
+        while (idle != 0ull && more) {
+            const uint32_t want = static_cast<uint32_t>(__popcll(idle));
+            const int leader = __ffsll(idle) - 1;
+            uint32_t base = 0;
+            if (static_cast<int>(__lane_id()) == leader) base = atomicAdd(P.counters + ADJ_C_SWEEP, want);
+            base = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(base), leader));
+            more = base < total;
+            const uint32_t rank = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(idle >> 32),
+                                                            __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(idle), 0u));
+            item = left < 0 ? base + rank : item;
+            if (left < 0 && item < total) {
+                const uint32_t w = item - n_whole;
+                const AdjLong& rec = P.longs[item < n_whole ? n_split + item : P.owner[w]];
+                if (rec.status == ADJ_OK) {
+                    int last = rec.n, first = 0;
+                    if (item < n_whole) {
+                        b0 = rec.zb[0];
+                        b1 = rec.zb[1];
+                        b3 = b4 = 0.0;
+                        pb = adj::ParBar{rec.pb[0], rec.pb[1], rec.pb[2]};
+                    } else {
+                        const uint32_t local = w - rec.item_base, b = local & 3u;
+                        first = static_cast<int>(local >> 2) * ADJ_SEG;
+                        last = min(last, first + ADJ_SEG - 1);
+                        b0 = b == 0u ? 1.0 : 0.0;
+                        b1 = b == 1u ? 1.0 : 0.0;
+                        b3 = b == 2u ? 1.0 : 0.0;
+                        b4 = b == 3u ? 1.0 : 0.0;
+                        pb = adj::ParBar{0.0, 0.0, 0.0};
+                    }
+                    E = rec.E;
+                    L = rec.L;
+                    left = last - first;
+                    e = P.long_store + (static_cast<size_t>(rec.base) + static_cast<size_t>(last)) * ADJ_ENTRY;
+                    y0 = e[0];
+                    y1 = e[1];
+                    y3 = e[2];
+                    y4 = e[3];
+                    h = e[4];
+                }
+            }
+            idle = __ballot(left < 0);
+        }
+        if (__ballot(left >= 0) == 0ull) break;
+        if (left < 0) continue;
+        const double y[5] = {y0, y1, 0.0, y3, y4}, hs = h;
+        double yb[5] = {b0, b1, 0.0, b3, b4};
+        if (left > 0) {
+            e -= ADJ_ENTRY;
+            y0 = e[0];
+            y1 = e[1];
+            y3 = e[2];
+            y4 = e[3];
+            h = e[4];
+        }
+        adj::dp_step_vjp<false>(M, a, E, L, y, hs, yb, &pb);
+        b0 = yb[0];
+        b1 = yb[1];
+        b3 = yb[3];
+        b4 = yb[4];
+        if (--left < 0) {
+            double *z, *q;
+            if (item < n_whole) {
+                AdjLong& rec = P.longs[n_split + item];
+                z = rec.zb;
+                q = rec.pb;
+            } else {
+                z = P.items + static_cast<size_t>(item - n_whole) * 8u;
+                q = z + 4;
+            }
+            z[0] = b0;
+            z[1] = b1;
+            z[2] = b3;
+            z[3] = b4;
+            q[0] = pb.E;
+            q[1] = pb.L;
+            q[2] = pb.a;
+        }
+    }
+}
+
+// The stored rays' ends: a split ray's seeded cotangent through the segments'
+// maps, last segment first (cotangent' = sum_b cotangent_b * column_b,
+// parameter cotangents += sum_b cotangent_b * their column_b), then the camera.
 __global__ void __launch_bounds__(ADJ_BLOCK) adjoint_combine_kernel(const AdjParams P) {
-    const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= P.counters[0]) return;
-    const AdjLong& rec = P.longs[k];
-    if (rec.status != ADJ_LONG_SPLIT) return;
-    double v[4] = {rec.zb[0], rec.zb[1], rec.zb[2], rec.zb[3]};
-    adj::ParBar pb{rec.pb[0], rec.pb[1], rec.pb[2]};
-    for (int s = rec.n_seg - 1; s >= 0; --s) {
-        const double* o = P.items + (static_cast<size_t>(rec.item_base) + 4u * static_cast<size_t>(s)) * 8u;
-        double nv[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const double* c = o + 8 * b;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) nv[i] = fma(v[b], c[i], nv[i]);
-            pb.E = fma(v[b], c[4], pb.E);
-            pb.L = fma(v[b], c[5], pb.L);
-            pb.a = fma(v[b], c[6], pb.a);
+    const uint32_t n = P.counters[ADJ_C_END] - P.counters[ADJ_C_FIRST], n_split = P.counters[ADJ_C_SPLIT];
+    for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x) {
+        const AdjLong& rec = P.longs[k];
+        if (rec.status != ADJ_OK) {
+            put_grads(P, rec.ray, rec.status, 0.0, 0.0, 0.0);
+            continue;
         }
+        double v[4] = {rec.zb[0], rec.zb[1], rec.zb[2], rec.zb[3]};
+        adj::ParBar pb{rec.pb[0], rec.pb[1], rec.pb[2]};
+        for (int s = k < n_split ? rec.n_seg - 1 : -1; s >= 0; --s) {
+            const double* o = P.items + (static_cast<size_t>(rec.item_base) + 4u * static_cast<size_t>(s)) * 8u;
+            double nv[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = nv[i];
+            for (int b = 0; b < 4; ++b) {
+                const double* c = o + 8 * b;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) nv[i] = fma(v[b], c[i], nv[i]);
+                pb.E = fma(v[b], c[4], pb.E);
+                pb.L = fma(v[b], c[5], pb.L);
+                pb.a = fma(v[b], c[6], pb.a);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = nv[i];
+        }
+        const double zb[5] = {v[0], v[1], 0.0, v[2], v[3]};
+        double ga, gi;
+        camera_chain(P, rec.ray, zb, pb, &ga, &gi);
+        put_grads(P, rec.ray, ADJ_OK, ga, gi, rec.gr);
     }
-    const double zb[5] = {v[0], v[1], 0.0, v[2], v[3]};
-    double ga, gi;
-    camera_chain(P, rec.ray, zb, pb, &ga, &gi);
-    put_grads(P, rec.ray, ADJ_OK, ga, gi, rec.gr);
 }
 
-// Clears the ticket, the statistics, the split counters and the sort's
-// histogram (block 0), and marks every segment item unused.
-__global__ void adjoint_init_kernel(const AdjParams P) {
+// Clears the ticket, the statistics, the counters and the sort's histogram,
+// and leaves the forward pass its parameters.
+__global__ void adjoint_init_kernel(const AdjParams P, const Params fwd) {
     const int t = threadIdx.x;
-    if (blockIdx.x == 0) {
-        if (t == 0) *P.ticket = 0u;
-        if (t < 4) P.stats[t] = 0ull;
-        if (t < 3 && P.max_long > 0) P.counters[t] = 0u;
-        for (int b = t; b <= SORT_BINS; b += blockDim.x) P.hist[b] = 0u;
+    if (t == 0) *P.ticket = 0u;
+    if (t < 4) P.stats[t] = 0ull;
+    if (P.max_long > 0) {
+        if (t < ADJ_C_COUNT) P.counters[t] = 0u;
+        if (t == 0) *P.params = fwd;
     }
-    if (P.max_long > 0)
-        for (uint32_t w = blockIdx.x * blockDim.x + t; w < P.item_cap; w += gridDim.x * blockDim.x)
-            P.owner[w] = 0xffffffffu;
+    for (int b = t; b <= SORT_BINS; b += blockDim.x) P.hist[b] = 0u;
 }
 
 // ---- work list ------------------------------------------------------------
@@ -628,28 +680,58 @@ __global__ void __launch_bounds__(RED_THREADS) grad_final_sum_kernel(const doubl
     if (t < 3) out[t] = v[t][0];
 }
 
+// The parameters of the stored forward pass.
+static Params forward_params(const AdjParams& p) {
+    Params f;
+    std::memset(&f, 0, sizeof f);
+    f.method = KT_DP45;
+    f.precision = KT_FP64;
+    f.rtol = p.rtol;
+    f.atol = p.atol;
+    f.h_init = p.h_init;
+    f.max_steps = p.max_attempts / 16;
+    f.max_evals = p.max_attempts;
+    f.n_rays = p.n_rays;
+    f.n_images = 1;
+    f.img0 = p.im;
+    f.ticket = p.counters + ADJ_C_TRACE;
+    f.ws_params = p.params;
+    f.persistent = 1;
+    f.batch = 4;
+    f.adj.list = p.list;
+    f.adj.range = p.counters + ADJ_C_FIRST;
+    f.adj.n_steps = p.n_steps;
+    f.adj.r_hit = p.r_hit;
+    f.adj.recs = p.longs;
+    f.adj.store = p.long_store;
+    f.adj.next = p.counters + ADJ_C_STORE;
+    f.adj.entries = static_cast<uint32_t>(static_cast<uint64_t>(p.long_cap) * 6u / ADJ_ENTRY);
+    return f;
+}
+
 int launch_adjoint(const AdjParams& p, void* stream) {
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const bool split = p.max_long > 0;
-    const uint32_t fill_blocks = split ? (p.item_cap + 255u) / 256u : 1u;
-    hipLaunchKernelGGL(adjoint_init_kernel, dim3(fill_blocks < 1u ? 1u : fill_blocks), dim3(256), 0, s, p);
+    const bool stored = p.max_long > 0;
+    const Params fwd = forward_params(p);
+    hipLaunchKernelGGL(adjoint_init_kernel, dim3(1), dim3(256), 0, s, p, fwd);
     if (hipGetLastError() != hipSuccess) return -1;
     const SortBufs b{p.n_rays, p.hist, p.keys, p.list};
     if (launch_sort(b, StepKey{p.fate, p.cot, p.n_steps, p.grad_a, p.grad_incl, p.grad_rin}, s)) return -1;
-    if (split) {
+    if (stored) {
         hipLaunchKernelGGL(adjoint_split_kernel, dim3(1), dim3(SORT_BLOCK), 0, s, p);
+        if (hipGetLastError() != hipSuccess) return -1;
+        const int64_t need = (p.n_rays + ADJ_BLOCK - 1) / ADJ_BLOCK;
+        if (launch_trace_store(fwd, static_cast<int>(need < p.trace_blocks ? need : p.trace_blocks), s)) return -1;
+        hipLaunchKernelGGL(adjoint_seed_kernel, dim3(static_cast<int>(need < 1024 ? need : 1024)), dim3(ADJ_BLOCK), 0, s, p);
+        if (hipGetLastError() != hipSuccess) return -1;
+        hipLaunchKernelGGL(adjoint_sweep_kernel, dim3(p.grid_lanes / ADJ_BLOCK), dim3(ADJ_BLOCK), 0, s, p);
+        if (hipGetLastError() != hipSuccess) return -1;
+        hipLaunchKernelGGL(adjoint_combine_kernel, dim3(static_cast<int>(need < 1024 ? need : 1024)), dim3(ADJ_BLOCK), 0, s, p);
         if (hipGetLastError() != hipSuccess) return -1;
     }
     const int grid = (p.n_lanes + ADJ_BLOCK - 1) / ADJ_BLOCK;
     hipLaunchKernelGGL(adjoint_kernel, dim3(grid), dim3(ADJ_BLOCK), 0, s, p);
     if (hipGetLastError() != hipSuccess) return -1;
-    if (split) {
-        hipLaunchKernelGGL(adjoint_segment_kernel, dim3(grid), dim3(ADJ_BLOCK), 0, s, p);
-        if (hipGetLastError() != hipSuccess) return -1;
-        hipLaunchKernelGGL(adjoint_combine_kernel, dim3((p.max_long + ADJ_BLOCK - 1) / ADJ_BLOCK), dim3(ADJ_BLOCK),
-                           0, s, p);
-        if (hipGetLastError() != hipSuccess) return -1;
-    }
     if (p.grad_sum) {
         hipLaunchKernelGGL(grad_block_sum_kernel, dim3(ADJ_RED_BLOCKS), dim3(RED_THREADS), 0, s, p.grad_a,
                            p.grad_incl, p.grad_rin, static_cast<int64_t>(p.n_rays), p.partials);

@@ -1,5 +1,5 @@
 // kt_adjoint_math.h -- the pieces of the discrete adjoint that are pure
-// arithmetic: the gradient of the Hamiltonian in all its arguments, the
+// arithmetic: Hamilton's equations, the
 // vector-Jacobian product of the RHS as a Hessian-vector product, one
 // Dormand-Prince step as a map y -> y' with frozen step size and its
 // vector-Jacobian product, and the disk observables with their derivatives.
@@ -12,74 +12,52 @@
 namespace kt {
 namespace adj {
 
-// sin and cos of theta from their values (sv, cv): for a dual theta the
-// tangents follow from d sin = cos d theta, d cos = -sin d theta.
-__host__ __device__ inline void sincos_from(const double&, double sv, double cv, double* s, double* c) {
-    *s = sv;
-    *c = cv;
-}
-template <int N>
-__host__ __device__ inline void sincos_from(const Dual<N>& th, double sv, double cv, Dual<N>* s, Dual<N>* c) {
-    *s = Dual<N>(sv);
-    *c = Dual<N>(cv);
-    for (int i = 0; i < N; ++i) {
-        s->d[i] = cv * th.d[i];
-        c->d[i] = -sv * th.d[i];
-    }
+// What the field and its derivatives share at one state, from Carter's
+// separated form: H = K / (2 Sigma), K = Delta p_r^2 + p_th^2 + T^2 - W^2/Delta,
+// T = L/sin - aE sin, W = (r^2 + a^2)E - aL.  (s, c) are sin and cos of theta;
+// 1/sin, 1/Sigma and 1/Delta come from one reciprocal of their product.
+struct Parts {
+    double Del, rho2, iS, iD, is, T, W, Wd, G, H2, hdK, Q, X;  // Wd = W/Delta, H2 = 2H
+};
+
+__host__ __device__ inline __attribute__((always_inline)) Parts parts_at(double M, double a, double E, double L,
+                                                                         const double z[5], double s, double c) {
+    const double r = z[0], pr = z[3], pth = z[4];
+    Parts p;
+    const double a2 = a * a, r2 = r * r;
+    const double Sig = r2 + a2 * c * c;
+    p.Del = r * (r - 2.0 * M) + a2;
+    p.rho2 = r2 + a2;
+    const double SD = Sig * p.Del;
+    const double R = rcp(SD * s);
+    const double iSD = s * R;
+    p.is = SD * R;
+    p.iS = p.Del * iSD;
+    p.iD = Sig * iSD;
+    p.T = L * p.is - a * E * s;
+    p.W = p.rho2 * E - a * L;
+    p.Wd = p.W * p.iD;
+    p.G = pr * pr + p.Wd * p.Wd;
+    p.H2 = (p.Del * pr * pr + pth * pth + p.T * p.T - p.W * p.Wd) * p.iS;
+    p.hdK = (r - M) * p.G - 2.0 * r * E * p.Wd;      // (1/2) dK/dr
+    p.Q = L * p.is * p.is + a * E;                   // dT/dtheta = -cos Q
+    p.X = p.T * p.Q - a2 * s * p.H2;                 // dH/dtheta = -cos X / Sigma
+    return p;
 }
 
-// Gradient of H = K / (2 Sigma), K = Delta p_r^2 + p_th^2 + T^2 - W^2/Delta
-// (Carter's separated form, T = L/sin - aE sin, W = (r^2 + a^2)E - aL), with
-// respect to X = (r, theta, p_r, p_theta, L, E, a); M is a constant.  (sv, cv)
-// are sin and cos of theta's value.  1/sin, 1/Sigma and 1/Delta come from one
-// reciprocal of their product.  E and a are plain numbers: the dual form is
-// only ever taken along directions in (r, theta, p_r, p_theta, L).
-template <class T>
-__host__ __device__ inline void grad_H(double M, const T& r, const T& th, const T& pr, const T& pth,
-                                       const T& L, double E, double a, double sv, double cv, T g[7]) {
-    T s, c;
-    sincos_from(th, sv, cv, &s, &c);
-    const T r2 = r * r;
-    const double a2 = a * a;
-    const T Sig = r2 + a2 * c * c;
-    const T Del = r2 - 2.0 * M * r + a2;
-    const T rho2 = r2 + a2;
-    const T SD = Sig * Del;
-    const T R = recip(SD * s);
-    const T iS = Del * s * R, iD = Sig * s * R, is = SD * R;
-    const T Lis = L * is;
-    const T Tt = Lis - a * E * s;
-    const T W = rho2 * E - a * L;
-    const T pr2 = pr * pr;
-    const T WiD = W * iD;
-    const T K = Del * pr2 + pth * pth + Tt * Tt - W * WiD;
-    const T H2 = K * iS;  // 2H
-    const T rM2 = 2.0 * (r - M);
-    const T Kr = rM2 * pr2 - 4.0 * r * E * WiD + WiD * WiD * rM2;
-    const T Kth = -2.0 * Tt * c * (Lis * is + a * E);
-    const T Ka = 2.0 * a * pr2 - 2.0 * Tt * E * s - 2.0 * WiD * (2.0 * a * E - L) + WiD * WiD * (2.0 * a);
-    g[0] = 0.5 * (Kr - 2.0 * r * H2) * iS;
-    g[1] = 0.5 * (Kth + 2.0 * a2 * s * c * H2) * iS;
-    g[2] = Del * pr * iS;
-    g[3] = pth * iS;
-    g[4] = (Tt * is + a * WiD) * iS;
-    g[5] = (-(a * s * Tt) - rho2 * WiD) * iS;
-    g[6] = 0.5 * (Ka - 2.0 * a * c * c * H2) * iS;
-}
-
-// Hamilton's equations from the gradient: d/dlambda (r, th, phi, p_r, p_th).
-// Returns sin and cos of theta (the trace kernel's own sincos_theta), which
-// the step VJP reuses.
-__host__ __device__ inline void field(double M, double a, double E, double L, const double z[5], double f[5],
-                                      double* sv, double* cv) {
+// Hamilton's equations: d/dlambda (r, th, phi, p_r, p_th).  Returns sin and
+// cos of theta (the trace kernel's own sincos_theta), which the step VJP
+// reuses.
+__host__ __device__ inline __attribute__((always_inline)) void field(double M, double a, double E, double L,
+                                                                     const double z[5], double f[5], double* sv,
+                                                                     double* cv) {
     sincos_theta(z[1], sv, cv);
-    double g[7];
-    grad_H<double>(M, z[0], z[1], z[3], z[4], L, E, a, *sv, *cv, g);
-    f[0] = g[2];
-    f[1] = g[3];
-    f[2] = g[4];
-    f[3] = -g[0];
-    f[4] = -g[1];
+    const Parts p = parts_at(M, a, E, L, z, *sv, *cv);
+    f[0] = p.Del * z[3] * p.iS;
+    f[1] = z[4] * p.iS;
+    f[2] = (p.T * p.is + a * p.Wd) * p.iS;
+    f[3] = (z[0] * p.H2 - p.hdK) * p.iS;
+    f[4] = *cv * p.X * p.iS;
 }
 
 // Parameter cotangents accumulated along a ray.
@@ -90,26 +68,57 @@ struct ParBar {
 // Vector-Jacobian product of the field at z: zbar += (df/dz)^T v and the
 // parameter cotangents += (df/d(E, L, a))^T v.  The field is S grad H, so
 // this is the Hessian-vector product of H along u = (-v_pr, -v_th, v_r, v_th,
-// v_phi, 0, 0) in (r, th, p_r, p_th, L, E, a), taken by forward-mode duals
-// on grad_H.
-__host__ __device__ inline void field_vjp(double M, double a, double E, double L, const double z[5], double sv,
-                                          double cv, const double v[5], double zbar[5], ParBar* pb) {
-    using D = Dual<1>;
-    D rr(z[0]), tt(z[1]), pp(z[3]), qq(z[4]), LL(L);
-    rr.d[0] = -v[3];
-    tt.d[0] = -v[4];
-    pp.d[0] = v[0];
-    qq.d[0] = v[1];
-    LL.d[0] = v[2];
-    D g[7];
-    grad_H<D>(M, rr, tt, pp, qq, LL, E, a, sv, cv, g);
-    zbar[0] += g[0].d[0];
-    zbar[1] += g[1].d[0];
-    zbar[3] += g[2].d[0];
-    zbar[4] += g[3].d[0];
-    pb->L += g[4].d[0];
-    pb->E += g[5].d[0];
-    pb->a += g[6].d[0];
+// v_phi) in (r, th, p_r, p_th, L): the derivative along u of each component
+// g = N / Sigma of grad H, (dN - N dSigma/Sigma) / Sigma.  (sv, cv) are sin
+// and cos of theta.  PHI false: v_phi is zero (phi enters no component of the
+// field, so a cotangent without it stays without it), and its terms drop out.
+//
+// Written out: the same product by dual numbers through grad H took ~140
+// vector instructions per stage, this ~115, and holds fewer values at once.
+template <bool PHI = true>
+__host__ __device__ inline __attribute__((always_inline)) void field_vjp(double M, double a, double E, double L,
+                                                                         const double z[5], double sv, double cv,
+                                                                         const double v[5], double zbar[5],
+                                                                         ParBar* pb) {
+    const double r = z[0], pr = z[3], pth = z[4], s = sv, c = cv, a2 = a * a;
+    const double dr = -v[3], dth = -v[4], dpr = v[0], dpth = v[1];
+    const Parts p = parts_at(M, a, E, L, z, s, c);
+    const double rM = r - M, ds = c * dth, dc = -s * dth;
+    const double dS = 2.0 * (r * dr + a2 * c * dc) * p.iS;  // dSigma / Sigma
+    const double dDel = 2.0 * rM * dr;
+    double dT = -p.Q * ds;
+    double dW = 2.0 * r * E * dr;
+    if (PHI) {
+        dT += p.is * v[2];
+        dW -= a * v[2];
+    }
+    const double dWd = (dW - p.Wd * dDel) * p.iD;
+    const double dG = 2.0 * (pr * dpr + p.Wd * dWd);
+    double hdK = p.hdK * dr + p.Del * pr * dpr + pth * dpth + p.T * dT;  // (1/2) dK
+    if (PHI) hdK += a * p.Wd * v[2];
+    const double dH2 = 2.0 * hdK * p.iS - p.H2 * dS;
+    const double dhdK = dr * p.G + rM * dG - 2.0 * E * (dr * p.Wd + r * dWd);
+    // numerators N of grad H and their derivatives
+    const double Nr = p.hdK - r * p.H2;
+    zbar[0] += (dhdK - dr * p.H2 - r * dH2 - Nr * dS) * p.iS;
+    const double Lis2 = L * p.is * p.is;
+    double dQ = -2.0 * Lis2 * p.is * ds;
+    if (PHI) dQ += p.is * p.is * v[2];
+    const double dX = dT * p.Q + p.T * dQ - a2 * (ds * p.H2 + s * dH2);
+    zbar[1] += (c * p.X * dS - dc * p.X - c * dX) * p.iS;
+    const double Npr = p.Del * pr;
+    zbar[3] += (dDel * pr + p.Del * dpr - Npr * dS) * p.iS;
+    zbar[4] += (dpth - pth * dS) * p.iS;
+    const double NL = p.T * p.is + a * p.Wd;
+    pb->L += (dT * p.is - p.T * p.is * p.is * ds + a * dWd - NL * dS) * p.iS;
+    const double sT = s * p.T, dsT = ds * p.T + s * dT;
+    const double NE = a * sT + p.rho2 * p.Wd;
+    pb->E += (NE * dS - a * dsT - 2.0 * r * dr * p.Wd - p.rho2 * dWd) * p.iS;
+    const double Wa = 2.0 * a * E - L;  // dW/da
+    const double Na = a * p.G - E * sT - p.Wd * Wa - a * c * c * p.H2;
+    double dNa = a * dG - E * dsT - dWd * Wa - a * c * (2.0 * dc * p.H2 + c * dH2);
+    if (PHI) dNa += p.Wd * v[2];
+    pb->a += (dNa - Na * dS) * p.iS;
 }
 
 // Dormand & Prince (1980) RK5(4)7M: the rows and 5th-order weights of the
@@ -128,19 +137,41 @@ __host__ __device__ constexpr double dp_b(int j) {
     return t[j];
 }
 
+// Keeps a stage of the reverse pass to itself on the device: what parts_at
+// gave in the forward pass is recomputed from the stage state instead of kept
+// (13 values per stage), and the scheduler does not mix stages.  The step VJP
+// then fits 208 VGPRs, two waves per SIMD, without a spill; left to itself it
+// took 358 with 194 moves to and from the other half of the register file, or
+// 77 scratch accesses per step at two waves.
+template <bool PHI>
+__host__ __device__ inline __attribute__((always_inline)) void stage_fence(double Y[5]) {
+#ifdef __HIP_DEVICE_COMPILE__
+#pragma unroll
+    for (int i = 0; i < 5; ++i)
+        if (PHI || i != 2) asm volatile("" : "+v"(Y[i]));
+    __builtin_amdgcn_sched_barrier(0);
+#else
+    (void)Y;
+#endif
+}
+
 // Vector-Jacobian product of one step with frozen h: given ybar at the
 // step's end, returns ybar at its start (in place) and accumulates the
 // parameter cotangents.  The stage states are rebuilt from y (the step's
 // end value itself is not needed, so the last stage's field is skipped).
 // Every loop is unrolled so that the stage arrays stay in registers: with
 // run-time indices they would live in scratch memory, at half the speed.
-__host__ __device__ inline void dp_step_vjp(double M, double a, double E, double L, const double y[5], double h,
-                                            double ybar[5], ParBar* pb) {
+// PHI false: ybar[2] is zero and stays so (see field_vjp), y[2] is not read.
+template <bool PHI = true>
+__host__ __device__ inline __attribute__((always_inline)) void dp_step_vjp(double M, double a, double E, double L,
+                                                                           const double y[5], double h,
+                                                                           double ybar[5], ParBar* pb) {
     double Y[6][5], K[5][5], S[6], C[6];
 #pragma unroll
     for (int j = 0; j < 6; ++j) {
 #pragma unroll
         for (int i = 0; i < 5; ++i) {
+            if (!PHI && i == 2) continue;
             double acc = 0.0;
 #pragma unroll
             for (int l = 0; l < j; ++l) acc += dp_a(j, l) * K[l][i];
@@ -155,17 +186,22 @@ __host__ __device__ inline void dp_step_vjp(double M, double a, double E, double
 #pragma unroll
     for (int j = 0; j < 6; ++j)
 #pragma unroll
-        for (int i = 0; i < 5; ++i) kb[j][i] = h * dp_b(j) * ybar[i];
+        for (int i = 0; i < 5; ++i) {
+            if (!PHI && i == 2) continue;
+            kb[j][i] = h * dp_b(j) * ybar[i];
+        }
 #pragma unroll
     for (int j = 5; j >= 0; --j) {
+        stage_fence<PHI>(Y[j]);
         double Yb[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-        field_vjp(M, a, E, L, Y[j], S[j], C[j], kb[j], Yb, pb);
+        field_vjp<PHI>(M, a, E, L, Y[j], S[j], C[j], kb[j], Yb, pb);
 #pragma unroll
-        for (int i = 0; i < 5; ++i) ybar[i] += Yb[i];
+        for (int i = 0; i < 5; ++i) {
+            if (!PHI && i == 2) continue;
+            ybar[i] += Yb[i];
 #pragma unroll
-        for (int l = 0; l < j; ++l)
-#pragma unroll
-            for (int i = 0; i < 5; ++i) kb[l][i] += h * dp_a(j, l) * Yb[i];
+            for (int l = 0; l < j; ++l) kb[l][i] += h * dp_a(j, l) * Yb[i];
+        }
     }
 }
 

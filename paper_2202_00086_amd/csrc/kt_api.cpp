@@ -103,6 +103,12 @@ int waves_per_simd(int32_t method, int64_t n_rays) {
 
 constexpr int32_t DEFAULT_BATCH = 4;  // ids per ticket fetch after a wave's first
 
+// Waves per SIMD of the adjoint's stored passes.
+int adjoint_waves(int64_t n_rays) {
+    const int64_t lanes = static_cast<int64_t>(device_cus()) * 4 * 64;
+    return n_rays <= 8 * lanes ? 1 : 2;
+}
+
 double horizon(const kt_spacetime* st) {
     if (st->metric == KT_METRIC_Q) return 2.0 * st->M;
     return st->M + std::sqrt(st->M * st->M - st->a * st->a);
@@ -657,7 +663,7 @@ int kt_adjoint(const kt_camera* camera, const kt_spacetime* spacetime, const kt_
     p.list = reinterpret_cast<uint32_t*>(ws + w.list);
     p.n_lanes = w.n_lanes;
     p.max_ckpt = w.max_ckpt;
-    // split sweeps need the forward step counts (the work list's order)
+    // stored forward passes need the forward step counts
     p.split_above = integ->split_above;
     p.max_long = n_steps && integ->split_above >= 0 ? w.max_long : 0;
     p.long_cap = w.long_cap;
@@ -667,6 +673,11 @@ int kt_adjoint(const kt_camera* camera, const kt_spacetime* spacetime, const kt_
     p.longs = reinterpret_cast<kt::AdjLong*>(ws + w.longs);
     p.owner = reinterpret_cast<uint32_t*>(ws + w.owner);
     p.items = reinterpret_cast<double*>(ws + w.items);
+    p.params = reinterpret_cast<kt::Params*>(ws + w.params);
+    // waves per SIMD of the forward pass and of the sweep: see adjoint_waves
+    const int waves = adjoint_waves(static_cast<int64_t>(n));
+    p.trace_blocks = device_cus() * waves;
+    p.grid_lanes = device_cus() * waves * 256;
     if (kt::launch_adjoint(p, hip_stream))
         return fail(KT_EDEVICE, "adjoint launch failed: %s", hipGetErrorString(hipGetLastError()));
     return KT_OK;

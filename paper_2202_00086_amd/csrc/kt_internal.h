@@ -53,6 +53,21 @@ struct Image {
     double rho_ring, order_scale;
 };
 
+// Where the adjoint's forward pass leaves the accepted steps of the rays it
+// stores: entries of ADJ_ENTRY doubles (r, theta, p_r, p_theta at a step's
+// start and its size), a ray's in order from its record's base.
+struct AdjLong;
+struct AdjStore {
+    const uint32_t* list;     // the work list; the stored rays are [range[0], range[1])
+    const uint32_t* range;
+    const int32_t* n_steps;   // the forward render's step counts
+    const double* r_hit;      // its hit radii, or NULL
+    AdjLong* recs;            // record of list entry t at t - range[0]
+    double* store;
+    uint32_t* next;           // entries taken so far
+    uint32_t entries;
+};
+
 // Everything a render needs, copied into the workspace by ws_init.
 struct Params {
     // integrator (shared by all images)
@@ -81,6 +96,7 @@ struct Params {
     int32_t persistent, batch;
     int32_t from_list;  // take ray ids from fb_list[0 .. *fb_count)
     double wall_khz;    // the device's wall clock rate, kHz (0: unknown)
+    AdjStore adj;       // the adjoint's forward pass only
 };
 
 // Bins of the device counting sorts (dispatch order, adjoint work list), and
@@ -139,22 +155,24 @@ struct Hot {
     int32_t max_steps, max_evals;
     uint32_t first;             // ray ids of a persistent wave's first fetch, 1..64
     unsigned long long* acc;    // the evaluation counters
+    double* store;              // the adjoint's step store
     const Params* cold;         // the workspace copy of Params
 };
 
-// A ray whose backward sweep is split into segments (the first n_long
-// entries of the work list).  The forward pass stores every accepted step
-// in the split-ray store from `base`, then the cotangents of the state at
-// the start of the located partial step.  Segment s covers the steps
-// [ADJ_SEG s, ADJ_SEG (s + 1)); its four basis runs are segment items
-// item_base + 4 s + b.
-enum : int32_t { ADJ_LONG_DONE = 0, ADJ_LONG_SPLIT = 1 };
+// A ray whose forward pass is stored (kt_adjoint with step counts).  Its
+// entries start at `base`: entry j < n the j-th accepted step before the
+// crossing, entry n the located partial step.  The seed kernel turns the
+// crossing into the cotangents at it; the sweep leaves those at the camera
+// (status ADJ_OK), or for a split ray, the first n_split of the stored ones,
+// the maps of its segments as items item_base + 4 s + b (segment s covers the
+// entries [ADJ_SEG s, ADJ_SEG (s + 1)), b runs over the basis cotangents).
+enum : int { ADJ_OK = 0, ADJ_FAIL = 1, ADJ_OVERFLOW = 2, ADJ_MISMATCH = 3 };
 struct AdjLong {
-    int32_t ray, status, n, n_seg;  // n accepted steps before the crossing
+    int32_t ray, status, n, n_seg;
     uint32_t base, item_base, pad0, pad1;
-    double zb[4];                   // cotangents of (r, theta, p_r, p_theta); that of phi is 0
-    double pb[3];                   // of (E, L, a)
-    double gr, E, L;                // the r_in gradient (from the seed alone) and the ray constants
+    double zb[4];     // cotangents of (r, theta, p_r, p_theta); first (r, r', theta') at the crossing
+    double pb[3];     // of (E, L, a)
+    double gr, E, L;  // the r_in gradient (from the seed alone) and the ray constants
 };
 
 // Everything the adjoint kernel needs (passed by value).
@@ -182,15 +200,29 @@ struct AdjParams {
     uint32_t* hist;             // [SORT_BINS + 1] bin counts, then offsets; [SORT_BINS] = list length
     uint16_t* keys;             // [n_rays] bin of each ray, SORT_SKIP if not differentiated
     uint32_t* list;             // [n_rays] ray ids
-    // split backward sweeps (only with n_steps; max_long 0 switches them off)
+    // stored forward passes (only with n_steps; max_long 0 switches them off)
     int32_t split_above;        // 0: threshold from the work list; > 0: this many steps
     int32_t max_long;           // records in `longs`
-    uint32_t long_cap, item_cap;
-    uint32_t* counters;         // [0] n_long, [1] store allocation, [2] item allocation
-    double* long_store;         // [long_cap][6] every accepted step (state, size) of the split rays
+    uint32_t long_cap, item_cap;  // long_cap: the store's size in 6 doubles
+    uint32_t* counters;         // ADJ_C_*
+    double* long_store;         // the stored entries (shares the checkpoints' memory)
     AdjLong* longs;             // [max_long]
-    uint32_t* owner;            // [item_cap] record of each segment item (0xffffffff: none)
+    uint32_t* owner;            // [item_cap] record of each segment item
     double* items;              // [item_cap][8] one segment's sweep of one basis cotangent
+    Params* params;             // the forward pass's parameters (device copy)
+    int32_t trace_blocks, grid_lanes;  // grid of the forward pass, lanes of the sweep's
+};
+
+// AdjParams.counters
+enum : int {
+    ADJ_C_SPLIT = 0,     // split rays
+    ADJ_C_STORE = 1,     // entries taken
+    ADJ_C_ITEMS = 2,     // segment items taken
+    ADJ_C_FIRST = 3,     // the stored rays' range of the work list
+    ADJ_C_END = 4,
+    ADJ_C_TRACE = 5,     // ticket of the forward pass
+    ADJ_C_SWEEP = 6,     // ticket of the sweep
+    ADJ_C_COUNT = 7
 };
 
 #ifndef KT_ADJ_MAX_LANES
@@ -204,13 +236,14 @@ constexpr int ADJ_CK_SHIFT_DEFAULT = 6;      // checkpoints every 64 accepted st
 // sweep then reads each step instead of recomputing it
 constexpr int ADJ_CK_SHIFT_MIN = 0, ADJ_CK_SHIFT_MAX = 10;
 constexpr int ADJ_RED_BLOCKS = 256;      // fixed grid of the gradient reduction (deterministic)
-// Split backward sweeps: segments of ADJ_SEG steps, at most ADJ_SEG_MAX of
-// them per ray, at most ADJ_MAX_LONG split rays, and a store of
-// ADJ_LONG_STEPS_PER_LANE accepted steps per lane of the grid.
-constexpr int ADJ_SEG = 64, ADJ_SEG_MAX = 32;
-constexpr int ADJ_MAX_LONG = 8192;
-constexpr int ADJ_LONG_STEPS_PER_LANE = 32;
-constexpr int ADJ_SPLIT_MIN = 128;        // the automatic threshold is at least this many steps
+// Stored forward passes: ADJ_ENTRY doubles per accepted step, room for
+// ADJ_STEPS_PER_PIXEL of them per pixel of the image up to ADJ_STORE_MAX_BYTES
+// (a 512x512 disk image of 117k hits takes 135 per pixel; 2.7 GB), at most
+// ADJ_MAX_RECORDS rays, sweeps split into segments of ADJ_SEG entries.
+constexpr int ADJ_SEG = 64, ADJ_ENTRY = 5;
+constexpr int ADJ_STEPS_PER_PIXEL = 256;
+constexpr size_t ADJ_STORE_MAX_BYTES = size_t{8} << 30;
+constexpr size_t ADJ_MAX_RECORDS = 524288;
 
 // log2 of kt_integrator.checkpoint_every (0 selects 64); -1 unless a power
 // of two in [1, 1024].
@@ -222,7 +255,7 @@ inline int adj_ck_shift(int32_t every) {
 }
 
 struct AdjLayout {
-    size_t stats, hist, partials, ckpt, seg, keys, list, grad, longs, owner, items, long_store, total;
+    size_t stats, hist, partials, params, ckpt, seg, keys, list, grad, longs, owner, items, long_store, total;
     int32_t n_lanes, max_ckpt, max_long;
     uint32_t long_cap, item_cap;
 };
@@ -245,21 +278,30 @@ inline AdjLayout adj_layout(size_t n_rays, int64_t max_steps, int ck_shift, bool
     w.stats = 64;
     w.hist = 256;
     w.partials = align256(w.hist + 4u * (SORT_BINS + 1));
-    w.ckpt = align256(w.partials + 3u * ADJ_RED_BLOCKS * sizeof(double));
+    w.params = align256(w.partials + 3u * ADJ_RED_BLOCKS * sizeof(double));
+    // the checkpoints and segment slots of the one-lane path; the stored
+    // forward passes, done with before that path starts, share their memory
+    w.ckpt = align256(w.params + WS_PARAMS_MAX);
     w.seg = align256(w.ckpt + static_cast<size_t>(ck) * 6u * lanes * sizeof(double));
-    w.keys = align256(w.seg + (size_t{1} << ck_shift) * 6u * lanes * sizeof(double));
+    size_t end = w.seg + (size_t{1} << ck_shift) * 6u * lanes * sizeof(double);
+    size_t store = n_rays * ADJ_STEPS_PER_PIXEL * ADJ_ENTRY * sizeof(double);
+    if (store > ADJ_STORE_MAX_BYTES) store = ADJ_STORE_MAX_BYTES;
+    if (end < w.ckpt + store) end = w.ckpt + store;
+    w.keys = align256(end);
     w.list = align256(w.keys + 2u * n_rays);
     w.grad = align256(w.list + 4u * n_rays);
-    w.max_long = split ? static_cast<int32_t>(n_rays < size_t{ADJ_MAX_LONG} ? n_rays : size_t{ADJ_MAX_LONG}) : 0;
-    w.long_cap = split ? static_cast<uint32_t>(lanes * ADJ_LONG_STEPS_PER_LANE) : 0u;
-    // every split ray's segments fit: sum over rays of 4 ceil(n / ADJ_SEG)
-    // <= 4 (long_cap / ADJ_SEG + max_long), since the rays' stores do not overlap
-    w.item_cap = split ? 4u * (w.long_cap / ADJ_SEG + static_cast<uint32_t>(w.max_long)) : 0u;
+    w.long_store = w.ckpt;
+    w.long_cap = split ? static_cast<uint32_t>((end - w.ckpt) / (6u * sizeof(double))) : 0u;
+    w.max_long = split ? static_cast<int32_t>(n_rays < ADJ_MAX_RECORDS ? n_rays : ADJ_MAX_RECORDS) : 0;
+    // records, and in the rest of this room (68 bytes each) segment items
+    const size_t few = n_rays < size_t{8192} ? n_rays : size_t{8192};
+    const size_t room = split ? lanes * 1672u + few * 384u : 0u;
     w.longs = align256(w.grad + 3u * sizeof(double) * n_rays);
-    w.owner = align256(w.longs + static_cast<size_t>(w.max_long) * sizeof(AdjLong));
+    const size_t recs = static_cast<size_t>(w.max_long) * sizeof(AdjLong);
+    w.item_cap = split ? static_cast<uint32_t>((room - recs + 271u) / 272u * 4u) : 0u;
+    w.owner = align256(w.longs + recs);
     w.items = align256(w.owner + 4u * static_cast<size_t>(w.item_cap));
-    w.long_store = align256(w.items + 8u * sizeof(double) * w.item_cap);
-    w.total = align256(w.long_store + 6u * sizeof(double) * w.long_cap);
+    w.total = align256(w.items + 8u * sizeof(double) * w.item_cap);
     return w;
 }
 
@@ -273,6 +315,7 @@ int validate_single(const kt_camera* camera, const kt_spacetime* spacetime, cons
 
 // Host-side launchers (kt_trace.hip, kt_adjoint.hip).
 int launch_adjoint(const AdjParams& p, void* stream);
+int launch_trace_store(const Params& p, int grid, void* stream);  // the adjoint's forward pass
 int launch_ws_init(const Params& p, void* stream);  // also copies p into the workspace
 int launch_upload_images(const Image* host, int32_t n, Image* dev, void* stream);
 int launch_order(const Params& p, void* stream);  // fills p.perm (ring-first dispatch)

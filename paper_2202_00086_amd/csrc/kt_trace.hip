@@ -239,6 +239,9 @@ struct Vec5 {
     }
 };
 
+// STORE: the end of a ray that took more steps than its forward render.
+constexpr int FATE_NO_ROOM = 8;
+
 // The running maxima of |2H| and of |H|_rel = Kabs / D, the latter as its
 // two parts (ratios compared by cross products): no quotient per step.
 __device__ __forceinline__ void keep_max(const Diag& dg, double* max_h2, double* rel_k, double* rel_d) {
@@ -270,7 +273,11 @@ constexpr int FEAT_DYN = -1;
 // with each test in a branch of its own, and the per-ray scalars in LDS, an
 // attempt took ~830 vector and ~215 scalar instructions, and a wave alone on
 // its SIMD, as in small images, needed 2.5 us for it.
-template <int METHOD, int PREC, bool BATCH, bool QMET = false, int FEAT = FEAT_DYN>
+//
+// STORE: the adjoint's forward pass.  The rays come from its work list, every
+// accepted step and the located partial step go to the ray's range of the
+// step store, and its end to its record instead of the outputs.
+template <int METHOD, int PREC, bool BATCH, bool QMET = false, int FEAT = FEAT_DYN, bool STORE = false>
 __global__ void __launch_bounds__(BLOCK_MAX) __attribute__((amdgpu_waves_per_eu(KT_WAVES_PER_EU)))
 trace_kernel(const Hot hp) {
     static_assert(!(QMET && (BATCH || METHOD == KT_RK4_S || PREC != KT_FP64)),
@@ -304,7 +311,10 @@ trace_kernel(const Hot hp) {
     bool first_fetch;
     {
         const Params& P = cold_params(hp.cold);
-        n_total = P.from_list ? *P.fb_count : static_cast<uint32_t>(P.n_rays);
+        if constexpr (STORE)
+            n_total = P.adj.range[1] - P.adj.range[0];
+        else
+            n_total = P.from_list ? *P.fb_count : static_cast<uint32_t>(P.n_rays);
         first_fetch = P.persistent != 0;
     }
     if (first_fetch) {
@@ -338,6 +348,7 @@ trace_kernel(const Hot hp) {
     double r_lo = 0.0, r_hi = 0.0;  // MAY_SRC: the window of r without an event
     float fac_max = 5.0f;           // growth limit: 1 after a rejection
     int misses = 0;                 // attempts that were not accepted steps
+    uint32_t rec = 0, entry = 0, entry_end = 0;  // STORE: the ray's record, its next entry and their end
     unsigned long long evals_acc = 0, evals32_acc = 0;
     // Attempts are counted for the wave: a lane's are it - it0, its accepted
     // steps those less its misses.  From it_limit on, some lane may have
@@ -372,6 +383,36 @@ trace_kernel(const Hot hp) {
                     r_lo = fmax(r_lo, rd.r_src);
             }
         }
+    };
+    // STORE: a step of size h from ys goes to the ray's next entry
+    const auto put_entry = [&]() {
+        double* e = hp.store + static_cast<size_t>(entry) * ADJ_ENTRY;
+        e[0] = ys.r;
+        e[1] = ys.th;
+        e[2] = ys.pr;
+        e[3] = ys.pth;
+        e[4] = h;
+    };
+    const auto write_record = [&](int fate, double r_c, double dr_c, double dth_c) {
+        const Params& P = cold_params(hp.cold);
+        AdjLong& o = P.adj.recs[rec];
+        int status = ADJ_FAIL;
+        if (fate == KT_FATE_DISK) {
+            status = P.adj.r_hit && !(r_c == P.adj.r_hit[ray]) ? ADJ_MISMATCH : ADJ_OK;
+            put_entry();
+            o.n = static_cast<int32_t>(entry - o.base);
+            o.zb[0] = r_c;
+            o.zb[1] = dr_c;
+            o.zb[2] = dth_c;
+            o.E = rc.E;
+            o.L = rc.L;
+        } else if (fate == KT_FATE_CAPTURED || fate == KT_FATE_ESCAPED) {
+            status = ADJ_MISMATCH;
+        } else if (fate == FATE_NO_ROOM) {
+            status = ADJ_OVERFLOW;
+        }
+        o.status = status;
+        ray = -1;
     };
     const auto write_outputs = [&](int fate, double r_c, double psi, double defl, double thf, double phf, int nsteps,
                                    int nevals) {
@@ -420,7 +461,11 @@ trace_kernel(const Hot hp) {
             if (ray < 0 && rank < avail) {
                 const Params& P = cold_params(hp.cold);
                 const uint32_t slot = q_next + rank;
-                ray = P.from_list ? static_cast<int32_t>(P.fb_list[slot])
+                if constexpr (STORE) {
+                    rec = slot;
+                    ray = static_cast<int32_t>(P.adj.list[P.adj.range[0] + slot]);
+                } else
+                    ray = P.from_list ? static_cast<int32_t>(P.fb_list[slot])
                       : P.perm    ? static_cast<int32_t>(P.perm[slot])
                                   : static_cast<int32_t>(slot);
                 double y[5], E, L;
@@ -434,10 +479,26 @@ trace_kernel(const Hot hp) {
                     valid = camera_state(P.img0, ray, y, &E, &L);
                 }
                 fl = 0;
+                if constexpr (STORE) {
+                    // room for the forward render's steps and the partial one
+                    const uint32_t room = static_cast<uint32_t>(max(P.adj.n_steps[ray], 0)) + 2u;
+                    entry = atomicAdd(P.adj.next, room);
+                    entry_end = entry + room;
+                    AdjLong& o = P.adj.recs[rec];
+                    o.ray = ray;
+                    o.base = entry;
+                    const bool fits_store = entry_end >= entry && entry_end <= P.adj.entries;
+                    if (!valid || !fits_store) {
+                        write_record(fits_store ? static_cast<int>(KT_FATE_INVALID) : FATE_NO_ROOM, 0.0, 0.0, 0.0);
+                        valid = false;
+                    }
+                }
                 if (!valid) {
-                    const double NaN = __builtin_nan("");
-                    max_h2 = rel_k = NaN;
-                    write_outputs(KT_FATE_INVALID, NaN, NaN, NaN, y[1], y[2], 0, 0);
+                    if constexpr (!STORE) {
+                        const double NaN = __builtin_nan("");
+                        max_h2 = rel_k = NaN;
+                        write_outputs(KT_FATE_INVALID, NaN, NaN, NaN, y[1], y[2], 0, 0);
+                    }
                 } else {
                     // k1 = f(y0) (FSAL seed) and H at lambda = 0
                     const auto st = spacetime();
@@ -542,6 +603,7 @@ trace_kernel(const Hot hp) {
                 // it the error NaN or infinite, an infinite scale makes
                 // the norm NaN; phi enters no evaluation and is tested.
                 odd = !(msq < 1e20) | !isfinite(yn[2]);
+                if constexpr (STORE) odd = odd | (entry + 1u >= entry_end);
             } else {
 #pragma unroll
                 for (int i = 0; i < 5; ++i) odd = odd | !isfinite(yn[i]);
@@ -568,7 +630,12 @@ trace_kernel(const Hot hp) {
             if (!odd & mine) {
                 if (accept) {
                     // commit
-                    keep_max(dg, &max_h2, &rel_k, &rel_d);
+                    if constexpr (STORE) {
+                        put_entry();
+                        ++entry;
+                    } else {
+                        keep_max(dg, &max_h2, &rel_k, &rel_d);
+                    }
                     unsafeAtomicAdd(&COLD(C_LAM), h);  // one LDS add, no result
                     if constexpr (MAY_SRC) swept += arc;
                     ys = ye;
@@ -641,9 +708,11 @@ trace_kernel(const Hot hp) {
                         COLD(C_DEFL) = sw;  // parked until the ray ends
                         fl |= F_SRCDONE;
                     }
-                    // continue from the end of the accepted step: retake it (bit-identical)
-                    fl = (fl & ~F_LOCATE) | F_RETAKE;
-                    h = COLD(C_H);
+                    if (fate < 0) {
+                        // continue from the end of the accepted step: retake it (bit-identical)
+                        fl = (fl & ~F_LOCATE) | F_RETAKE;
+                        h = COLD(C_H);
+                    }
                 } else {
                     double a = COLD(C_EVA), fa = COLD(C_EVFA), b = COLD(C_EVB), fb = COLD(C_EVFB);
                     if (fc * fb < 0.0) {
@@ -731,6 +800,14 @@ trace_kernel(const Hot hp) {
                                     phf = ye.ph;
                                 } else {
                                     // commit the step
+                                    if constexpr (STORE) {
+                                        if (entry + 1u < entry_end) {
+                                            put_entry();
+                                            ++entry;
+                                        } else {
+                                            fate = FATE_NO_ROOM;
+                                        }
+                                    }
                                     ys = ye;
                                     ks = ke;
                                     unsafeAtomicAdd(&COLD(C_LAM), h);  // one LDS add, no result
@@ -768,7 +845,10 @@ trace_kernel(const Hot hp) {
                     psi = COLD(C_SRCPSI);
                 }
                 fl &= ~(F_LOCATE | F_RETAKE);
-                write_outputs(fate, r_c, psi, defl, thf, phf, nsteps, nevals);
+                if constexpr (STORE)
+                    write_record(fate, r_c, ke.r, ke.th);
+                else
+                    write_outputs(fate, r_c, psi, defl, thf, phf, nsteps, nevals);
             }
             set_window(rd, ys.r);
         }
@@ -787,6 +867,7 @@ trace_kernel(const Hot hp) {
     }
 #undef COLD
 
+    if constexpr (STORE) return;
     // one atomic per wave for each evaluation counter
     const unsigned long long evals = wave_sum(evals_acc);
     if (lane == 0 && evals != 0ull) atomicAdd(hp.acc + ACC_EVALS, evals);
@@ -1127,6 +1208,7 @@ static Hot make_hot(const Params& p) {
     hp.max_evals = static_cast<int32_t>(p.max_evals);
     hp.first = 64;
     hp.acc = p.acc;
+    hp.store = p.adj.store;
     hp.cold = p.ws_params;
     return hp;
 }
@@ -1232,6 +1314,12 @@ int trace_max_blocks_per_cu(const Params& p, int block) {
 }
 
 #if !KT_TRACE_ONLY
+int launch_trace_store(const Params& p, int grid, void* stream) {
+    hipLaunchKernelGGL((trace_kernel<KT_DP45, KT_FP64, false, false, FEAT_DISK, true>), dim3(grid), dim3(BLOCK_MAX), 0,
+                       static_cast<hipStream_t>(stream), make_hot(p));
+    return check_launch();
+}
+
 int launch_disk_obs(const Params& p, void* stream) {
     hipLaunchKernelGGL(disk_obs_kernel, dim3(small_grid(p.n_rays, 256)), dim3(256), 0,
                        static_cast<hipStream_t>(stream), p.ws_params);
