@@ -698,6 +698,7 @@ static Params forward_params(const AdjParams& p) {
     f.ws_params = p.params;
     f.persistent = 1;
     f.batch = 4;
+    f.min_idle = 8;
     f.adj.list = p.list;
     f.adj.range = p.counters + ADJ_C_FIRST;
     f.adj.n_steps = p.n_steps;

@@ -101,7 +101,7 @@ int waves_per_simd(int32_t method, int64_t n_rays) {
     return n_rays >= THREE_WAVE_MIN_RAYS_PER_LANE * lanes ? 3 : 2;
 }
 
-constexpr int32_t DEFAULT_BATCH = 4;  // ids per ticket fetch after a wave's first
+constexpr int32_t DEFAULT_BATCH = 4;  // ids per ticket fetch after a wave's first, at least one per idle lane
 
 // Waves per SIMD of the adjoint's stored passes.
 int adjoint_waves(int64_t n_rays) {
@@ -427,6 +427,7 @@ int render_images(const kt::Image* table, int32_t n_images, int64_t n_rays, cons
     }
     if (grid < 1) grid = 1;
     p.batch = ln.batch;
+    p.min_idle = waves <= 1 ? 8 : 4;
 
     if (batch && kt::launch_upload_images(table, n_images, reinterpret_cast<kt::Image*>(ws + w.images),
                                           hip_stream))

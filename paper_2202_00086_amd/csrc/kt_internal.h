@@ -93,7 +93,7 @@ struct Params {
     uint32_t* order_hist;  // uint32[SORT_BINS + 1] counts, then offsets and the total
     uint16_t* order_bins;  // uint16[n_rays] bin of each ray
     // launch
-    int32_t persistent, batch;
+    int32_t persistent, batch, min_idle;
     int32_t from_list;  // take ray ids from fb_list[0 .. *fb_count)
     double wall_khz;    // the device's wall clock rate, kHz (0: unknown)
     AdjStore adj;       // the adjoint's forward pass only
@@ -154,6 +154,7 @@ struct Hot {
     int32_t feat;               // FEAT_* bits of the image's disk, source and sky
     int32_t max_steps, max_evals;
     uint32_t first;             // ray ids of a persistent wave's first fetch, 1..64
+    int32_t min_idle;           // idle lanes a refill waits for
     unsigned long long* acc;    // the evaluation counters
     double* store;              // the adjoint's step store
     const Params* cold;         // the workspace copy of Params

@@ -301,8 +301,8 @@ trace_kernel(const Hot hp) {
     uint32_t n_total;
 
     // this wave's queue of ray ids [q_next, q_end).  A persistent wave's
-    // first fetch takes hp.first ids, up to one per lane, in one atomic;
-    // later fetches take P.batch.  Taken in batch-sized pieces, the start of
+    // first fetch takes hp.first ids, one per lane, in one atomic; later
+    // fetches take P.batch, or one per idle lane if those are more.  Taken in batch-sized pieces, the start of
     // the launch was a burst of 64 / batch serial round trips per wave on one
     // address, and the wave's first rays came from interleaved places in the
     // dispatch order instead of one run of similar cost.
@@ -438,14 +438,23 @@ trace_kernel(const Hot hp) {
 
     for (;;) {
         // ---- refill idle lanes from the wave queue -------------------------
+        // A refill is a chain of memory round trips (ticket, dispatch order),
+        // a few microseconds in which the wave's other rays stand still, so
+        // it waits until hp.min_idle lanes are idle.  That costs a part of
+        // min_idle / 128 of the lanes: 8 for a wave that has its SIMD to
+        // itself (512x512 ring 5.98 -> 5.46 ms, disk 3.98 -> 3.62 against a
+        // refill per idle lane; 16: 5.52 and 3.75), 4 where other waves fill
+        // in (1024x1024 ring 16.35 -> 15.84; 8: 16.09).
         unsigned long long idle = __ballot(ray < 0);
+        if (__popcll(idle) < hp.min_idle) idle = 0ull;
         while (idle != 0ull) {
             if (q_next >= q_end) {
                 if (exhausted) break;
                 const Params& P = cold_params(hp.cold);
                 const int leader = __ffsll(idle) - 1;
                 uint32_t base = 0;
-                const uint32_t take = first_fetch ? hp.first : static_cast<uint32_t>(P.batch);
+                const uint32_t take = first_fetch ? hp.first
+                                                  : max(static_cast<uint32_t>(P.batch), static_cast<uint32_t>(__popcll(idle)));
                 first_fetch = false;
                 if (static_cast<int>(lane) == leader) base = atomicAdd(P.ticket, take);
                 base = static_cast<uint32_t>(__shfl(static_cast<int>(base), leader));
@@ -1207,6 +1216,7 @@ static Hot make_hot(const Params& p) {
     hp.max_steps = static_cast<int32_t>(p.max_steps);
     hp.max_evals = static_cast<int32_t>(p.max_evals);
     hp.first = 64;
+    hp.min_idle = p.min_idle;
     hp.acc = p.acc;
     hp.store = p.adj.store;
     hp.cold = p.ws_params;
