@@ -381,16 +381,6 @@ __device__ __forceinline__ void field_at(const QSpacetime& st, const RayConst& r
     rhs_q<WANT_DIAG>(st, rc, z, s, c, dz, dg);
 }
 
-template <bool WANT_DIAG, bool S_TIME, class ST>
-__device__ __forceinline__ void rhs(const ST& st, const RayConst& rc, const double z[5], double dz[5], Diag* dg) {
-    double s, c;
-    sincos_theta(z[1], &s, &c);
-    if constexpr (S_TIME)
-        rhs_sc<WANT_DIAG, true>(st, rc, z, s, c, dz, dg);
-    else
-        field_at<WANT_DIAG>(st, rc, z, s, c, dz, dg);
-}
-
 // sin and cos of theta0 + d from those of theta0 by angle addition, with
 // sin d = d - d x S(x) and cos d - 1 = -x C(x), x = d^2, where S and C are
 // minimax polynomials for |d| <= 1/2 (degrees 4 and 5, coefficients from
@@ -402,14 +392,16 @@ __device__ __forceinline__ void rhs(const ST& st, const RayConst& rc, const doub
 // most 0.045 rad on the 1024^2 image and 0.10 rad over random images at rtol
 // down to 1e-10.  Beyond it the error grows like d^13 (2e-14 relative at
 // |d| = 0.6, 8e-11 at 1) for the wild stages of steps that get rejected.
-__device__ __forceinline__ void sincos_shift(double s0, double c0, double d, double* s_out, double* c_out) {
+template <class FMA = HornerFma<true>>
+__device__ __forceinline__ void sincos_shift(double s0, double c0, double d, double* s_out, double* c_out,
+                                             FMA fma = FMA{}) {
     const double d2 = d * d;
     double ps = 2.49340193295306e-08;
     ps = fma(ps, d2, -2.7556995708658808e-06);
     ps = fma(ps, d2, 0.00019841269438799643);
     ps = fma(ps, d2, -0.008333333333114794);
     ps = fma(ps, d2, 0.1666666666666628);
-    const double sd = fma(-ps * d2, d, d);  // sin d
+    const double sd = __builtin_fma(-ps * d2, d, d);  // sin d
     double pc = -2.0777882749707575e-09;
     pc = fma(pc, d2, 2.755698550128358e-07);
     pc = fma(pc, d2, -2.480158674730891e-05);
@@ -417,8 +409,52 @@ __device__ __forceinline__ void sincos_shift(double s0, double c0, double d, dou
     pc = fma(pc, d2, -0.04166666666666487);
     pc = fma(pc, d2, 0.5);
     const double cdm1 = -pc * d2;  // cos d - 1
-    *s_out = fma(s0, cdm1, fma(c0, sd, s0));
-    *c_out = fma(c0, cdm1, fma(-s0, sd, c0));
+    *s_out = __builtin_fma(s0, cdm1, __builtin_fma(c0, sd, s0));
+    *c_out = __builtin_fma(c0, cdm1, __builtin_fma(-s0, sd, c0));
+}
+
+// The two functions as the steppers call them: with the constants of the one
+// that a stepper leans on pinned in registers (SHIFT for the Runge-Kutta
+// pairs, THETA for Bulirsch-Stoer), the other's left to the compiler; and for
+// RK4, short enough for the compiler to keep them all, both.
+template <bool SHIFT = false, bool THETA = false>
+struct Elem {
+    HornerK<9, 4> ks;
+    HornerK<15, 8> kt;
+    __device__ __forceinline__ Elem() {
+        double s, c;
+        if constexpr (SHIFT) {
+            sincos_shift(0.0, 0.0, 0.0, &s, &c, HornerRecord<9, 4>{&ks});
+            pin(&ks);
+        }
+        if constexpr (THETA) {
+            sincos_theta(0.0, &s, &c, HornerRecord<15, 8>{&kt});
+            pin(&kt);
+        }
+    }
+    __device__ __forceinline__ void shift(double s0, double c0, double d, double* s, double* c) const {
+        if constexpr (SHIFT)
+            sincos_shift(s0, c0, d, s, c, HornerUse<true, 9, 4>{&ks});
+        else
+            sincos_shift(s0, c0, d, s, c);
+    }
+    __device__ __forceinline__ void theta(double th, double* s, double* c) const {
+        if constexpr (THETA)
+            sincos_theta(th, s, c, HornerUse<false, 15, 8>{&kt});
+        else
+            sincos_theta(th, s, c, HornerFma<SHIFT>{});  // SHIFT: once per step, amid other work
+    }
+};
+
+template <bool WANT_DIAG, bool S_TIME, class ST, class EL = Elem<>>
+__device__ __forceinline__ void rhs(const ST& st, const RayConst& rc, const double z[5], double dz[5], Diag* dg,
+                                    const EL& el = EL{}) {
+    double s, c;
+    el.theta(z[1], &s, &c);
+    if constexpr (S_TIME)
+        rhs_sc<WANT_DIAG, true>(st, rc, z, s, c, dz, dg);
+    else
+        field_at<WANT_DIAG>(st, rc, z, s, c, dz, dg);
 }
 
 // ---------------------------------------------------------------------------
@@ -502,15 +538,15 @@ __device__ __forceinline__ void rhs_split(const Spacetime& st, const Spacetime32
 // at the step's start angle th0; the last stage (D: the step's end, whose
 // sin/cos seed the next step) computes them from theta itself, so the
 // shifts never accumulate.
-template <bool SPLIT, bool D, class ST>
+template <bool SPLIT, bool D, class ST, class EL>
 __device__ __forceinline__ void eval_rhs(const ST& st, const Spacetime32* sf, const RayConst& rc,
                                          const double* z, double th0, double s0, double c0, double* out,
-                                         Diag* dg) {
+                                         Diag* dg, const EL& el) {
     double s, c;
     if constexpr (D)
-        sincos_theta(z[1], &s, &c);
+        el.theta(z[1], &s, &c);
     else
-        sincos_shift(s0, c0, z[1] - th0, &s, &c);
+        el.shift(s0, c0, z[1] - th0, &s, &c);
     if constexpr (SPLIT)
         rhs_split<D>(st, *sf, rc, z, s, c, out, dg);
     else
@@ -540,31 +576,31 @@ constexpr double E1 = 71.0 / 57600, E3 = -71.0 / 16695, E4 = 71.0 / 1920,
 // solution yn, kn = f(yn) with its diagnostics, and the error vector err.
 // Six RHS evaluations.
 // (s0, c0) are sin and cos of y[1].
-template <bool SPLIT = false, class ST = Spacetime>
+template <bool SPLIT = false, class ST = Spacetime, class EL = Elem<>>
 __device__ __forceinline__ void dp45_step(const ST& st, const RayConst& rc, const double y[5],
                                           const double k1[5], double s0, double c0, double h, double yn[5],
                                           double kn[5], double err[5], Diag* dg,
-                                          const Spacetime32* sf = nullptr) {
+                                          const Spacetime32* sf = nullptr, const EL& el = EL{}) {
     using namespace dp;
     double k2[5], k3[5], k4[5], k5[5], k6[5], ys[5];
 #pragma unroll
     for (int i = 0; i < 5; ++i) ys[i] = fma(h, A21 * k1[i], y[i]);
-    eval_rhs<SPLIT, false>(st, sf, rc, ys, y[1], s0, c0, k2, dg);
+    eval_rhs<SPLIT, false>(st, sf, rc, ys, y[1], s0, c0, k2, dg, el);
 #pragma unroll
     for (int i = 0; i < 5; ++i) ys[i] = fma(h, fma(A31, k1[i], A32 * k2[i]), y[i]);
-    eval_rhs<SPLIT, false>(st, sf, rc, ys, y[1], s0, c0, k3, dg);
+    eval_rhs<SPLIT, false>(st, sf, rc, ys, y[1], s0, c0, k3, dg, el);
 #pragma unroll
     for (int i = 0; i < 5; ++i) ys[i] = fma(h, fma(A41, k1[i], fma(A42, k2[i], A43 * k3[i])), y[i]);
-    eval_rhs<SPLIT, false>(st, sf, rc, ys, y[1], s0, c0, k4, dg);
+    eval_rhs<SPLIT, false>(st, sf, rc, ys, y[1], s0, c0, k4, dg, el);
 #pragma unroll
     for (int i = 0; i < 5; ++i)
         ys[i] = fma(h, fma(A51, k1[i], fma(A52, k2[i], fma(A53, k3[i], A54 * k4[i]))), y[i]);
-    eval_rhs<SPLIT, false>(st, sf, rc, ys, y[1], s0, c0, k5, dg);
+    eval_rhs<SPLIT, false>(st, sf, rc, ys, y[1], s0, c0, k5, dg, el);
 #pragma unroll
     for (int i = 0; i < 5; ++i)
         ys[i] = fma(h, fma(A61, k1[i], fma(A62, k2[i], fma(A63, k3[i], fma(A64, k4[i], A65 * k5[i])))),
                     y[i]);
-    eval_rhs<SPLIT, false>(st, sf, rc, ys, y[1], s0, c0, k6, dg);
+    eval_rhs<SPLIT, false>(st, sf, rc, ys, y[1], s0, c0, k6, dg, el);
     // error partial sums before stage 7 so that k3..k6 are dead across it
     double ep[5];
 #pragma unroll
@@ -572,7 +608,7 @@ __device__ __forceinline__ void dp45_step(const ST& st, const RayConst& rc, cons
         yn[i] = fma(h, fma(B1, k1[i], fma(B3, k3[i], fma(B4, k4[i], fma(B5, k5[i], B6 * k6[i])))), y[i]);
         ep[i] = fma(E1, k1[i], fma(E3, k3[i], fma(E4, k4[i], fma(E5, k5[i], E6 * k6[i]))));
     }
-    eval_rhs<SPLIT, true>(st, sf, rc, yn, y[1], s0, c0, kn, dg);
+    eval_rhs<SPLIT, true>(st, sf, rc, yn, y[1], s0, c0, kn, dg, el);
 #pragma unroll
     for (int i = 0; i < 5; ++i) err[i] = h * fma(E7, kn[i], ep[i]);
 }
@@ -631,10 +667,10 @@ struct CashKarp45 {
 // propagated solution yn, kn = f(yn) with its diagnostics, and err = h sum
 // e_j k_j.  Inner stages take sin/cos of theta by angle addition from
 // (s0, c0); f(yn) computes them from theta.  Six RHS evaluations.
-template <class TAB, class ST>
+template <class TAB, class ST, class EL>
 __device__ __forceinline__ void erk6_step(const ST& st, const RayConst& rc, const double y[5],
                                           const double k1[5], double s0, double c0, double h, double yn[5],
-                                          double kn[5], double err[5], Diag* dg) {
+                                          double kn[5], double err[5], Diag* dg, const EL& el) {
     double k[6][5];
 #pragma unroll
     for (int i = 0; i < 5; ++i) k[0][i] = k1[i];
@@ -649,7 +685,7 @@ __device__ __forceinline__ void erk6_step(const ST& st, const RayConst& rc, cons
                 if (TAB::a(stg, j) != 0.0) acc = fma(TAB::a(stg, j), k[j][i], acc);
             ys[i] = fma(h, acc, y[i]);
         }
-        eval_rhs<false, false>(st, nullptr, rc, ys, y[1], s0, c0, k[stg], dg);
+        eval_rhs<false, false>(st, nullptr, rc, ys, y[1], s0, c0, k[stg], dg, el);
     }
 #pragma unroll
     for (int i = 0; i < 5; ++i) {
@@ -662,7 +698,7 @@ __device__ __forceinline__ void erk6_step(const ST& st, const RayConst& rc, cons
         yn[i] = fma(h, acc, y[i]);
         err[i] = h * ea;
     }
-    eval_rhs<false, true>(st, nullptr, rc, yn, y[1], s0, c0, kn, dg);
+    eval_rhs<false, true>(st, nullptr, rc, yn, y[1], s0, c0, kn, dg, el);
 }
 
 // ---------------------------------------------------------------------------
@@ -688,10 +724,10 @@ constexpr double bs_ratio2(int k, int j) {
 }
 constexpr double bs_weight(int k, int j) { return 1.0 / (bs_ratio2(k, j) - 1.0); }
 
-template <bool RATIONAL = false, class ST>
+template <bool RATIONAL = false, class ST, class EL>
 __device__ __forceinline__ void bs_step(const ST& st, const RayConst& rc, const double y[5],
                                         const double k1[5], double h, double yn[5], double kn[5],
-                                        double err[5], Diag* dg) {
+                                        double err[5], Diag* dg, const EL& el) {
     double T[BS_COLUMNS][5];  // row k of the tableau after chain k
 #pragma unroll
     for (int k = 0; k < BS_COLUMNS; ++k) {
@@ -707,7 +743,7 @@ __device__ __forceinline__ void bs_step(const ST& st, const RayConst& rc, const 
 #pragma unroll 1
         for (int m = 1; m < ns; ++m) {
             double fz[5];
-            rhs<false, false>(st, rc, zc, fz, nullptr);
+            rhs<false, false>(st, rc, zc, fz, nullptr, el);
 #pragma unroll
             for (int i = 0; i < 5; ++i) {
                 const double zn = fma(h2, fz[i], zp[i]);
@@ -744,30 +780,31 @@ __device__ __forceinline__ void bs_step(const ST& st, const RayConst& rc, const 
         yn[i] = T[BS_COLUMNS - 1][i];
         err[i] = T[BS_COLUMNS - 1][i] - T[BS_COLUMNS - 2][i];
     }
-    rhs<true, false>(st, rc, yn, kn, dg);
+    rhs<true, false>(st, rc, yn, kn, dg, el);
 }
 
 // One classic RK4 step of size h (in s) from y with k1 = F(y), F the field
 // scaled by Delta/r.  Writes yn and kn = F(yn) with diagnostics.  Four RHS
 // evaluations.
+template <class EL>
 __device__ __forceinline__ void rk4s_step(const Spacetime& st, const RayConst& rc, const double y[5],
                                           const double k1[5], double h, double yn[5], double kn[5],
-                                          Diag* dg) {
+                                          Diag* dg, const EL& el) {
     double k2[5], k3[5], k4[5], ys[5];
     const double hh = 0.5 * h;
 #pragma unroll
     for (int i = 0; i < 5; ++i) ys[i] = fma(hh, k1[i], y[i]);
-    rhs<false, true>(st, rc, ys, k2, nullptr);
+    rhs<false, true>(st, rc, ys, k2, nullptr, el);
 #pragma unroll
     for (int i = 0; i < 5; ++i) ys[i] = fma(hh, k2[i], y[i]);
-    rhs<false, true>(st, rc, ys, k3, nullptr);
+    rhs<false, true>(st, rc, ys, k3, nullptr, el);
 #pragma unroll
     for (int i = 0; i < 5; ++i) ys[i] = fma(h, k3[i], y[i]);
-    rhs<false, true>(st, rc, ys, k4, nullptr);
+    rhs<false, true>(st, rc, ys, k4, nullptr, el);
     const double h6 = h * (1.0 / 6.0);
 #pragma unroll
     for (int i = 0; i < 5; ++i) yn[i] = fma(h6, k1[i] + 2.0 * (k2[i] + k3[i]) + k4[i], y[i]);
-    rhs<true, true>(st, rc, yn, kn, dg);
+    rhs<true, true>(st, rc, yn, kn, dg, el);
 }
 
 }  // namespace kt

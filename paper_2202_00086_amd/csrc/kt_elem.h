@@ -21,21 +21,89 @@ __device__ __forceinline__ double rcp(double x) {
 }
 __host__ inline double rcp(double x) { return 1.0 / x; }
 
-// a b + k for a constant k.  In the 3-wave build of the trace kernels k goes
-// into the FMA as its scalar operand (set up by the scalar unit): left to
-// itself the compiler takes the two-operand form, whose addend is overwritten,
-// and moves k into a vector register pair before each use, two vector
-// instructions that the kernel's bottleneck has to issue.
+// a b + k for a constant k, as the three-operand FMA.  Left to itself the
+// compiler takes the two-operand form, whose addend is overwritten, and copies
+// k into a vector register pair before each use.  In the 3-wave build k is a
+// scalar operand (set up by the scalar unit, which has slots to spare there);
+// elsewhere a vector register pair.
+__host__ __device__ constexpr bool inline_constant(double k) {
+    return k == 0.5 || k == -0.5 || k == 1.0 || k == -1.0 || k == 2.0 || k == -2.0 || k == 4.0 || k == -4.0;
+}
 __device__ __forceinline__ double fma_k(double a, double b, double k) {
-#if defined(KT_WAVES_PER_EU) && KT_WAVES_PER_EU == 3
+    if (__builtin_constant_p(k) && inline_constant(k)) return fma(a, b, k);
     double r;
+#if defined(KT_WAVES_PER_EU) && KT_WAVES_PER_EU == 3
     asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(k));
-    return r;
 #else
-    return fma(a, b, k);
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(k));
 #endif
+    return r;
 }
 __host__ inline double fma_k(double a, double b, double k) { return fma(a, b, k); }
+
+// How the polynomials below take a Horner step a b + k: HornerFma as written;
+// or with their constants in registers that a loop around them keeps.  For
+// that, HornerK holds the constants of a function with two chains (the
+// constant addends in call order, and each chain's leading coefficient; the
+// second chain starts at call SECOND), HornerRecord fills it by running the
+// function once, and HornerUse runs the function on it.  The compiler's own
+// loop-invariant code motion gives up on these constants once registers look
+// short and sets them up again for every step: three instructions each, 4-6%
+// of the time of a wave alone on its SIMD (512x512 lensing 3.40 -> 3.22 ms).
+// FORCED: with the three-operand FMA above; not in the long chains of
+// sincos_theta outside the 3-wave build, which the scheduler then no longer
+// interleaves with other work.
+template <bool FORCED>
+struct HornerFma {
+    __host__ __device__ double operator()(double a, double b, double k) const {
+#if defined(KT_WAVES_PER_EU) && KT_WAVES_PER_EU == 3
+        return fma_k(a, b, k);
+#else
+        if constexpr (FORCED) return fma_k(a, b, k);
+        return __builtin_fma(a, b, k);
+#endif
+    }
+};
+template <int CALLS, int SECOND>
+struct HornerK {
+    double k[CALLS], lead[2];
+};
+template <int CALLS, int SECOND>
+struct HornerRecord {
+    HornerK<CALLS, SECOND>* to;
+    int n = 0;
+    __device__ __forceinline__ double operator()(double a, double, double k) {
+        if (n == 0) to->lead[0] = a;
+        if (n == SECOND) to->lead[1] = a;
+        to->k[n++] = k;
+        return k;
+    }
+};
+template <bool FORCED, int CALLS, int SECOND>
+struct HornerUse {
+    const HornerK<CALLS, SECOND>* from;
+    int n = 0;
+    __device__ __forceinline__ double operator()(double a, double b, double k) {
+        const double x = n == 0 ? from->lead[0] : n == SECOND ? from->lead[1] : a;
+        const double kept = from->k[n++];
+        return HornerFma<FORCED>{}(x, b, inline_constant(k) ? k : kept);
+    }
+};
+// Puts the constants into registers for good: the asm makes them opaque.
+template <int CALLS, int SECOND>
+__device__ __forceinline__ void pin(HornerK<CALLS, SECOND>* h) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) asm volatile("" : "+v"(h->lead[i]));
+#pragma unroll
+    for (int i = 0; i < CALLS; ++i) {
+        if (inline_constant(h->k[i])) continue;
+#if defined(KT_WAVES_PER_EU) && KT_WAVES_PER_EU == 3
+        asm volatile("" : "+s"(h->k[i]));
+#else
+        asm volatile("" : "+v"(h->k[i]));
+#endif
+    }
+}
 
 // sin and cos of the polar angle theta.  theta is folded to t in [-pi, pi]
 // by t = theta - 2 pi rint(theta / 2 pi) (t = theta exactly on [0, pi), the
@@ -47,19 +115,19 @@ __host__ inline double fma_k(double a, double b, double k) { return fma(a, b, k)
 // coefficients rounded to double the absolute error stays below 1.4e-17 for
 // cos u and 4.1e-17 for sin u, under a third of an ulp of 1; Taylor's series
 // needs two more terms each for the same.  No quadrant selects.
-__host__ __device__ inline __attribute__((always_inline)) void sincos_theta(double th, double* s_out,
-                                                                           double* c_out) {
+template <class FMA = HornerFma<false>>
+__host__ __device__ inline __attribute__((always_inline)) void sincos_theta(double th, double* s_out, double* c_out,
+                                                                           FMA fma = FMA{}) {
     constexpr double INV_TWO_PI = 0.15915494309189533577;
     constexpr double TWO_PI_HI = 6.2831853071795862320e+00;  // 2 pi rounded to double
     constexpr double TWO_PI_LO = 2.4492935982947064e-16;     // 2 pi - TWO_PI_HI
     constexpr double PIO2_HI = 1.5707963267948965580e+00;
     constexpr double PIO2_LO = 6.1232339957367658e-17;
     const double n = __builtin_rint(th * INV_TWO_PI);
-    double t = fma(-n, TWO_PI_HI, th);
-    t = fma(-n, TWO_PI_LO, t);
+    double t = __builtin_fma(-n, TWO_PI_HI, th);
+    t = __builtin_fma(-n, TWO_PI_LO, t);
     const double u = (fabs(t) - PIO2_HI) - PIO2_LO;
     const double u2 = u * u;
-    const auto fma = [](double a, double b, double k) { return fma_k(a, b, k); };
     double pc = 4.616135051438568e-14;
     pc = fma(pc, u2, -1.1463635437491283e-11);
     pc = fma(pc, u2, 2.0876592592498227e-09);

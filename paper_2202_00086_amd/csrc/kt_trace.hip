@@ -175,22 +175,22 @@ constexpr int EVIT_SHIFT = 16;    // 8 bits: trial steps of the current event
 enum : int { C_H = 0, C_EVA, C_EVFA, C_EVB, C_EVFB, C_DEFL, C_SRCPSI, C_LAM, C_SWEPT, C_MAXH2, C_RELK, C_RELD, N_COLD };
 constexpr int BLOCK_MAX = 256;
 
-template <int METHOD, class ST>
+template <int METHOD, class ST, class EL>
 __device__ __forceinline__ void take_step(const ST& st, const RayConst& rc, const double y[5],
                                           const double k1[5], double s0, double c0, double h, double yn[5],
-                                          double kn[5], double er[5], Diag* dg) {
+                                          double kn[5], double er[5], Diag* dg, const EL& el) {
     if constexpr (METHOD == KT_DP45) {
-        dp45_step(st, rc, y, k1, s0, c0, h, yn, kn, er, dg);
+        dp45_step(st, rc, y, k1, s0, c0, h, yn, kn, er, dg, nullptr, el);
     } else if constexpr (METHOD == KT_RKF45) {
-        erk6_step<Fehlberg45>(st, rc, y, k1, s0, c0, h, yn, kn, er, dg);
+        erk6_step<Fehlberg45>(st, rc, y, k1, s0, c0, h, yn, kn, er, dg, el);
     } else if constexpr (METHOD == KT_CK45) {
-        erk6_step<CashKarp45>(st, rc, y, k1, s0, c0, h, yn, kn, er, dg);
+        erk6_step<CashKarp45>(st, rc, y, k1, s0, c0, h, yn, kn, er, dg, el);
     } else if constexpr (METHOD == KT_BS) {
-        bs_step<false>(st, rc, y, k1, h, yn, kn, er, dg);
+        bs_step<false>(st, rc, y, k1, h, yn, kn, er, dg, el);
     } else if constexpr (METHOD == KT_BS_RAT) {
-        bs_step<true>(st, rc, y, k1, h, yn, kn, er, dg);
+        bs_step<true>(st, rc, y, k1, h, yn, kn, er, dg, el);
     } else {
-        rk4s_step(st, rc, y, k1, h, yn, kn, dg);
+        rk4s_step(st, rc, y, k1, h, yn, kn, dg, el);
 #pragma unroll
         for (int i = 0; i < 5; ++i) er[i] = 0.0;
     }
@@ -287,6 +287,8 @@ trace_kernel(const Hot hp) {
     constexpr bool ADAPTIVE = (METHOD != KT_RK4_S);
     constexpr bool S_TIME = (METHOD == KT_RK4_S);
     constexpr bool MIXED = (PREC == KT_MIXED) && (METHOD == KT_DP45) && !QMET;
+    constexpr bool LONG_STEPS = METHOD == KT_BS || METHOD == KT_BS_RAT;
+    constexpr bool PIN_SHIFT = !LONG_STEPS && METHOD != KT_RK4_S, PIN_THETA = LONG_STEPS && !QMET;
     constexpr bool MAY_DISK = FEAT < 0 ? !QMET : (FEAT & FEAT_DISK) != 0;
     constexpr bool MAY_SRC = FEAT < 0 || (FEAT & FEAT_SRC) != 0;
     __shared__ double cold[N_COLD][BLOCK_MAX];
@@ -327,6 +329,7 @@ trace_kernel(const Hot hp) {
         exhausted = true;
     }
 
+    const Elem<PIN_SHIFT, PIN_THETA> el;
     int32_t ray = -1;
     int fl = 0;
     Vec5 ys{}, ks{};  // the state and the field there
@@ -594,7 +597,7 @@ trace_kernel(const Hot hp) {
                 }
                 if (!fits) ++it0;
             } else {
-                take_step<METHOD>(st, rc, y, k1, s0, c0, h, yn, kn, er, &dg);
+                take_step<METHOD>(st, rc, y, k1, s0, c0, h, yn, kn, er, &dg, el);
             }
             ye = Vec5::of(yn);
             ke = Vec5::of(kn);
