@@ -325,10 +325,17 @@ adjoint_kernel(const AdjParams P) {
     const bool stored = P.max_long > 0;
     const uint32_t first = stored ? P.counters[ADJ_C_FIRST] : 0u, end = stored ? P.counters[ADJ_C_END] : 0u;
     const uint32_t n = P.hist[SORT_BINS] - (end - first);
+    // then the stored rays that took more steps than the caller's count said
+    const uint32_t total = n + (stored && P.counters[ADJ_C_REDO] != 0u ? end - first : 0u);
     for (;;) {
         uint32_t t = atomicAdd(P.ticket, 1u);
-        if (t >= n) break;
-        if (t >= first) t += end - first;
+        if (t >= total) break;
+        if (t >= n) {
+            t = t - n + first;
+            if (P.longs[t - first].status != ADJ_OVERFLOW) continue;
+        } else if (t >= first) {
+            t += end - first;
+        }
         adjoint_entry(P, st, lane, t);
     }
 }
@@ -353,9 +360,11 @@ __device__ __forceinline__ unsigned long long block_scan(unsigned long long v, u
 // k holds the rays of 4 v to 4 v + 3 forward steps, v = SORT_BINS - 1 - k, bin
 // 0 also every longer ray).  Both are whole bins, longest first, so that the
 // sets, and with them the gradients, do not depend on which lanes take the
-// rays: stored are bins 1, 2, ... as long as the store and the records hold
-// them for certain (a ray of bin v takes at most 4 v + 5 entries); bin 0 has
-// no such bound and is left to the one-lane path.
+// rays: stored are the bins from `skip` + 1 on as long as the store and the
+// records hold them for certain (a ray of bin v takes at most 4 v + 5
+// entries).  Bin 0, which has no such bound, and bins of more steps than the
+// one-lane path's checkpoints cover are left to that path, which counts such
+// rays as it does without step counts.
 // A split sweep takes four step VJPs per step instead of one, in pieces of
 // ADJ_SEG steps instead of the ray's length.  The longest bins are split until
 // the longest sweep left is no longer than the sweep kernel's work per lane,
@@ -369,13 +378,15 @@ __global__ void __launch_bounds__(SORT_BLOCK) adjoint_split_kernel(const AdjPara
     __shared__ unsigned long long all_steps;
     __shared__ int stop_store, stop_split;
     const int t = threadIdx.x;
-    const uint32_t first = P.hist[0];
+    const int covered = (P.max_ckpt << P.ck_shift) / 4 - 2;  // v of the longest bin within the checkpoints
+    const int skip = SORT_BINS - 2 < covered ? 0 : SORT_BINS - 2 - covered;
+    const uint32_t first = P.hist[skip];
     if (t == 0) stop_store = stop_split = SORT_BINS;
     uint32_t cnt[PER];
     unsigned long long need = 0;
     for (int i = 0; i < PER; ++i) {
         const int k = t * PER + i;
-        cnt[i] = k > 0 ? P.hist[k] - P.hist[k - 1] : 0u;
+        cnt[i] = k > skip ? P.hist[k] - P.hist[k - 1] : 0u;
         need += static_cast<unsigned long long>(cnt[i]) * static_cast<unsigned long long>(4 * (SORT_BINS - 1 - k) + 5);
     }
     unsigned long long run = block_scan(need, part) - need;
@@ -410,7 +421,7 @@ __global__ void __launch_bounds__(SORT_BLOCK) adjoint_split_kernel(const AdjPara
                                               : longest <= (load > ADJ_SEG ? load : ADJ_SEG);
         run_steps += static_cast<unsigned long long>(cnt[i]) * static_cast<unsigned long long>(4 * v + 2);
         run_items += static_cast<unsigned long long>(cnt[i]) * static_cast<unsigned long long>(4 * ((4 * v + 4) / ADJ_SEG + 1));
-        if (k > 0 && (enough || k >= stop_store || run_items > P.item_cap)) {
+        if (k > skip && (enough || k >= stop_store || run_items > P.item_cap)) {
             atomicMin(&stop_split, k);
             break;
         }
@@ -563,6 +574,10 @@ __global__ void __launch_bounds__(ADJ_BLOCK) adjoint_combine_kernel(const AdjPar
     const uint32_t n = P.counters[ADJ_C_END] - P.counters[ADJ_C_FIRST], n_split = P.counters[ADJ_C_SPLIT];
     for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x) {
         const AdjLong& rec = P.longs[k];
+        if (rec.status == ADJ_OVERFLOW) {
+            atomicAdd(P.counters + ADJ_C_REDO, 1u);  // left to the one-lane path
+            continue;
+        }
         if (rec.status != ADJ_OK) {
             put_grads(P, rec.ray, rec.status, 0.0, 0.0, 0.0);
             continue;

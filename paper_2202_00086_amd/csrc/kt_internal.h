@@ -223,7 +223,8 @@ enum : int {
     ADJ_C_END = 4,
     ADJ_C_TRACE = 5,     // ticket of the forward pass
     ADJ_C_SWEEP = 6,     // ticket of the sweep
-    ADJ_C_COUNT = 7
+    ADJ_C_REDO = 7,      // stored rays left to the one-lane path
+    ADJ_C_COUNT = 8
 };
 
 #ifndef KT_ADJ_MAX_LANES
