@@ -103,6 +103,41 @@ int waves_per_simd(int32_t method, int64_t n_rays) {
 
 constexpr int32_t DEFAULT_BATCH = 4;  // ids per ticket fetch after a wave's first, at least one per idle lane
 
+// The grid of a trace launch of about n_rays / share rays in a render of
+// n_rays, the build it runs (a shape of 3 or more waves per SIMD is the 3-wave
+// form) and the idle lanes that a refill waits for.
+struct Shape {
+    bool w3;
+    int grid, min_idle;
+};
+
+// One ray in six or fewer is re-run by KT_MIXED at budgets of use (13-18% of
+// the 1024x1024 ring at 1e-10, 3% of a 2048x2048 disk): its re-run pass is a
+// launch of that many rays, not of the image's.  At the image's shape, two
+// waves per SIMD, the 640x640 disk's pass took 2.7 ms, at one wave 1.7.
+constexpr int MIXED_RERUN_SHARE = 6;
+
+Shape launch_shape(const kt::Params& p, const kt_launch& ln, int64_t n_rays, int share = 1) {
+    const int64_t lane_grid = (n_rays + ln.block - 1) / ln.block;
+    const int waves =
+        ln.blocks_per_cu > 0 ? ln.blocks_per_cu * ln.block / 256 : waves_per_simd(p.method, n_rays / share);
+    Shape s;
+    s.w3 = ln.persistent && waves >= 3;
+    s.min_idle = waves <= 1 ? 8 : 4;
+    int64_t grid = lane_grid;
+    if (ln.persistent) {
+        int per_cu = ln.blocks_per_cu;
+        if (per_cu == 0) {
+            const int fit =
+                s.w3 ? kt_w3::trace_max_blocks_per_cu(p, ln.block) : kt::trace_max_blocks_per_cu(p, ln.block);
+            per_cu = std::min(fit, waves * 256 / ln.block);
+        }
+        grid = std::min<int64_t>(lane_grid, static_cast<int64_t>(device_cus()) * per_cu);
+    }
+    s.grid = static_cast<int>(std::max<int64_t>(grid, 1));
+    return s;
+}
+
 // Waves per SIMD of the adjoint's stored passes.
 int adjoint_waves(int64_t n_rays) {
     const int64_t lanes = static_cast<int64_t>(device_cus()) * 4 * 64;
@@ -409,25 +444,9 @@ int render_images(const kt::Image* table, int32_t n_images, int64_t n_rays, cons
     p.persistent = ln.persistent ? 1 : 0;
     p.from_list = 0;
     p.wall_khz = out->stats ? device_wall_khz() : 0.0;
-    const int64_t lane_grid = (n_rays + ln.block - 1) / ln.block;
-    // a shape that asks for 3 or more waves per SIMD runs the 3-wave form
-    const int waves = ln.blocks_per_cu > 0 ? (ln.blocks_per_cu * ln.block) / 256 : waves_per_simd(p.method, n_rays);
-    const bool w3 = p.persistent && waves >= 3;
-    int grid;
-    if (p.persistent) {
-        int per_cu = ln.blocks_per_cu;
-        if (per_cu == 0) {
-            const int fit = w3 ? kt_w3::trace_max_blocks_per_cu(p, ln.block) : kt::trace_max_blocks_per_cu(p, ln.block);
-            per_cu = std::min(fit, waves * 256 / ln.block);
-        }
-        grid = device_cus() * per_cu;
-        if (grid > lane_grid) grid = static_cast<int>(lane_grid);
-    } else {
-        grid = static_cast<int>(lane_grid);
-    }
-    if (grid < 1) grid = 1;
     p.batch = ln.batch;
-    p.min_idle = waves <= 1 ? 8 : 4;
+    const Shape shape = launch_shape(p, ln, n_rays);
+    p.min_idle = shape.min_idle;
 
     if (batch && kt::launch_upload_images(table, n_images, reinterpret_cast<kt::Image*>(ws + w.images),
                                           hip_stream))
@@ -438,16 +457,16 @@ int render_images(const kt::Image* table, int32_t n_images, int64_t n_rays, cons
         return fail(KT_EDEVICE, "dispatch order launch failed: %s", hipGetErrorString(hipGetLastError()));
     if (out->stats && kt::launch_stamp(p, kt::ACC_T0, hip_stream))
         return fail(KT_EDEVICE, "clock stamp launch failed: %s", hipGetErrorString(hipGetLastError()));
-    if ((w3 ? kt_w3::launch_trace : kt::launch_trace)(p, grid, ln.block, hip_stream))
+    if ((shape.w3 ? kt_w3::launch_trace : kt::launch_trace)(p, shape.grid, ln.block, hip_stream))
         return fail(KT_EDEVICE, "trace kernel launch failed: %s", hipGetErrorString(hipGetLastError()));
     if (p.precision == KT_MIXED) {
         // re-run every ray over the |H|_rel budget in FP64, from a compacted
         // list whose length stays on the device
         if (kt::launch_fallback_list(p, hip_stream))
             return fail(KT_EDEVICE, "fallback list launch failed: %s", hipGetErrorString(hipGetLastError()));
-        int grid2 = ln.persistent ? grid : static_cast<int>(lane_grid);
-        if (grid2 < 1) grid2 = 1;
-        if ((w3 ? kt_w3::launch_trace_fallback : kt::launch_trace_fallback)(p, grid2, ln.block, hip_stream))
+        const Shape again = launch_shape(p, ln, n_rays, MIXED_RERUN_SHARE);
+        p.min_idle = again.min_idle;
+        if ((again.w3 ? kt_w3::launch_trace_fallback : kt::launch_trace_fallback)(p, again.grid, ln.block, hip_stream))
             return fail(KT_EDEVICE, "fallback trace launch failed: %s", hipGetErrorString(hipGetLastError()));
     }
     if (out->stats && kt::launch_stamp(p, kt::ACC_T1, hip_stream))
