@@ -9,6 +9,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "kt_elem.h"
 
 namespace kt {
@@ -130,6 +132,12 @@ __device__ __forceinline__ double asin_small(double x) {
 struct Spacetime {
     double M, a, a2, two_a2;
 };
+// a = 0: the right-hand side without its terms in a.  They are zeros there, so
+// the results are the same bits; six of some seventy FP64 instructions per
+// evaluation go.
+struct Schwarzschild {
+    double M;
+};
 
 struct RayConst {
     double E, L;    // -p_t, p_phi
@@ -147,6 +155,10 @@ __device__ __forceinline__ RayConst make_ray_const(const Spacetime& st, double E
     rc.twoE = 2.0 * E;
     rc.Wc = fma(st.a2, E, -rc.aL);
     return rc;
+}
+
+__device__ __forceinline__ RayConst make_ray_const(const Schwarzschild&, double E, double L) {
+    return RayConst{E, L, 0.0, 0.0, 2.0 * E, 0.0};
 }
 
 // By-products of an RHS evaluation used at accepted states.
@@ -167,13 +179,19 @@ struct Diag {
 // is the Hamiltonian flow of H itself (H is then conserved to truncation).
 // S_TIME scales the field by d(lambda)/ds = Delta/r.
 // ---------------------------------------------------------------------------
-template <bool WANT_DIAG, bool S_TIME>
-__device__ __forceinline__ void rhs_sc(const Spacetime& st, const RayConst& rc, const double z[5], double s,
+template <bool WANT_DIAG, bool S_TIME, class ST>
+__device__ __forceinline__ void rhs_sc(const ST& st, const RayConst& rc, const double z[5], double s,
                                        double c, double dz[5], Diag* dg) {
     const double r = z[0], pr = z[3], pth = z[4];
     const double r2 = r * r;
-    const double Sig = fma(st.a2 * c, c, r2);
-    const double Del = fma(r, r - 2.0 * st.M, st.a2);
+    constexpr bool SPIN = !std::is_same_v<ST, Schwarzschild>;
+    double Sig = r2, Del, W, T, Q;
+    if constexpr (SPIN) {
+        Sig = fma(st.a2 * c, c, r2);
+        Del = fma(r, r - 2.0 * st.M, st.a2);
+    } else {
+        Del = r * (r - 2.0 * st.M);
+    }
     // 1/sin, 1/Sigma, 1/Delta (and 1/r for the s-time scaling) from one
     // reciprocal of their product
     const double SD = Sig * Del;
@@ -183,8 +201,13 @@ __device__ __forceinline__ void rhs_sc(const Spacetime& st, const RayConst& rc, 
     const double inv_SD = S_TIME ? s * r * q : s * q;
     const double inv_Sig = Del * inv_SD;
     const double inv_Del = Sig * inv_SD;
-    const double W = fma(r2, rc.E, rc.Wc);
-    const double T = fma(rc.L, inv_s, -rc.aE * s);
+    if constexpr (SPIN) {
+        W = fma(r2, rc.E, rc.Wc);
+        T = fma(rc.L, inv_s, -rc.aE * s);
+    } else {
+        W = r2 * rc.E;
+        T = rc.L * inv_s;
+    }
     const double Wd = W * inv_Del;
     const double pr2 = pr * pr;
     const double WWd = W * Wd;
@@ -193,13 +216,24 @@ __device__ __forceinline__ void rhs_sc(const Spacetime& st, const RayConst& rc, 
     // (1/2) d K / d r = (r - M) (p_r^2 + Wd^2) - 2 r E Wd
     const double hdK = fma(r - st.M, fma(Wd, Wd, pr2), -(rc.twoE * r) * Wd);
     // d T / d theta = -cos Q, Q = L / sin^2 + a E
-    const double Q = fma(rc.L, inv_s * inv_s, rc.aE);
+    if constexpr (SPIN)
+        Q = fma(rc.L, inv_s * inv_s, rc.aE);
+    else
+        Q = rc.L * (inv_s * inv_s);
     double d0 = Del * pr * inv_Sig;
     double d1 = pth * inv_Sig;
-    double d2 = fma(T, inv_s, st.a * Wd) * inv_Sig;
+    double d2;
+    if constexpr (SPIN)
+        d2 = fma(T, inv_s, st.a * Wd) * inv_Sig;
+    else
+        d2 = T * inv_s * inv_Sig;
     // -dH/dr = (2 r H - (1/2) dK/dr) / Sigma;  -dH/dtheta = cos (T Q - a^2 sin 2H) / Sigma
     double d3 = fma(r, H2, -hdK) * inv_Sig;
-    double d4 = (c * inv_Sig) * fma(T, Q, -(st.a2 * H2) * s);
+    double d4;
+    if constexpr (SPIN)
+        d4 = (c * inv_Sig) * fma(T, Q, -(st.a2 * H2) * s);
+    else
+        d4 = (c * inv_Sig) * (T * Q);
     if (S_TIME) {
         const double w = Del * (s * SD * q);  // Delta / r
         d0 *= w;
@@ -370,6 +404,11 @@ __device__ __forceinline__ void rhs_q(const QSpacetime& st, const RayConst& rc, 
 }
 
 // The RHS of either spacetime at z, given sin/cos of theta.
+template <bool WANT_DIAG>
+__device__ __forceinline__ void field_at(const Schwarzschild& st, const RayConst& rc, const double z[5], double s,
+                                         double c, double dz[5], Diag* dg) {
+    rhs_sc<WANT_DIAG, false>(st, rc, z, s, c, dz, dg);
+}
 template <bool WANT_DIAG>
 __device__ __forceinline__ void field_at(const Spacetime& st, const RayConst& rc, const double z[5], double s,
                                          double c, double dz[5], Diag* dg) {
@@ -808,8 +847,8 @@ __device__ __forceinline__ void bs_step(const ST& st, const RayConst& rc, const 
 // One classic RK4 step of size h (in s) from y with k1 = F(y), F the field
 // scaled by Delta/r.  Writes yn and kn = F(yn) with diagnostics.  Four RHS
 // evaluations.
-template <class EL>
-__device__ __forceinline__ void rk4s_step(const Spacetime& st, const RayConst& rc, const double y[5],
+template <class ST, class EL>
+__device__ __forceinline__ void rk4s_step(const ST& st, const RayConst& rc, const double y[5],
                                           const double k1[5], double h, double yn[5], double kn[5],
                                           Diag* dg, const EL& el) {
     double k2[5], k3[5], k4[5], ys[5];

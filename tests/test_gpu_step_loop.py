@@ -153,3 +153,25 @@ def test_stored_passes_equal_the_one_lane_path(K, nx, ny):
                 if what not in ("none", "negative", "beyond the list's bins"):
                     continue
                 np.testing.assert_array_equal(a.view(np.uint8), b.view(np.uint8), err_msg=f"{every} {what}")
+
+
+SPHERE = dict(src_on=1, r_src=700.0)
+THIN = dict(disk_on=1, r_in=6.0, r_out=30.0)
+SKY = dict(sky_on=1, grid_deg=6.0, line_deg=0.25)
+
+
+@pytest.mark.parametrize("method,options", [(1, {}), (1, SPHERE), (1, THIN), (1, SKY), (1, dict(SPHERE, **THIN)),
+                                            (1, dict(SPHERE, **SKY)), (1, dict(THIN, **SKY)),
+                                            (1, dict(SPHERE, **THIN, **SKY)), (0, {}), (0, dict(SPHERE, **THIN))],
+                         ids=str)
+@pytest.mark.parametrize("waves", [1, 3])
+def test_spin_zero_equals_the_general_right_hand_side(K, method, options, waves):
+    """A spin of 1e-200 takes the general right-hand side, and its terms vanish
+    against the others in every sum: the same bits as a spin of 0, which takes
+    the right-hand side without them."""
+    params = dict(W.schwarzschild_disk(n=8), disk_on=0, nx=38, ny=27, method=method, h_fixed=1.0 / 64, r_obs=900.0,
+                  r_escape=990.0)
+    params.update(options)
+    _announce("spin 0", method, options, waves)
+    launch = K.kt_launch(1, 256, waves, 4)
+    _same(_render(K, dict(params, a=0.0), launch), _render(K, dict(params, a=1e-200), launch), "a = 0")
