@@ -12,10 +12,10 @@
 //      with the accepted step sizes frozen, the located partial step first;
 //   4. chain the cotangents of the initial state and of (E, L) through the
 //      camera's dependence on (a, inclination).
-// With the forward step counts these are kernels of their own.  Step 1 is the
-// trace kernel itself (its STORE form) with every accepted step written to a
-// store; step 3 reads the steps back, one item per lane at two waves per
-// SIMD.  A long ray's sweep is split: each 64-step segment is swept backward
+// With the forward step counts step 1 is the trace kernel itself (its STORE
+// form) with every accepted step written to a store, and step 3 reads the steps
+// back, one item per lane, partly by waves of the forward pass that have no ray
+// left (see sweep in kt_trace.hip).  A long ray's sweep is split: each 64-step segment is swept backward
 // from four basis cotangents (its transposed Jacobian, a linear map since the
 // steps are frozen), one lane each, and the last kernel applies the segments'
 // maps to the ray's seeded cotangent in order.  A sweep is otherwise one
@@ -189,21 +189,6 @@ __device__ __forceinline__ int forward_to_hit(const AdjParams& P, const Spacetim
     return ADJ_OK;
 }
 
-// 2. Seeds from the intensity at crossing radius r_c with the crossing-time
-// correction; (dr_c, dth_c) are r' and theta' there.
-__device__ __forceinline__ void seed(const AdjParams& P, double r_c, double dr_c, double dth_c, double E, double L,
-                                     double w, double zb[5], adj::ParBar* pb, double* gr) {
-    const Image& im = P.im;
-    const Dual<5> I = adj::disk_intensity(P.dm, r_c, E, L, im.a, im.r_in);
-    *pb = adj::ParBar{w * I.d[1], w * I.d[2], w * I.d[3]};
-    *gr = w * I.d[4];
-    const double rbar = w * I.d[0];
-    // r_c = r(lambda*) with theta(lambda*) = pi/2: dr_c = dr - (r' / theta') dtheta
-    zb[0] = rbar;
-    zb[1] = -rbar * dr_c / dth_c;
-    zb[2] = zb[3] = zb[4] = 0.0;
-}
-
 // 3. The rest of the reverse sweep with frozen steps, from the lane's own
 // checkpoints: stored steps are read back; otherwise each segment between
 // checkpoints is recomputed forward from its checkpoint into the lane's
@@ -306,7 +291,7 @@ __device__ __forceinline__ void adjoint_entry(const AdjParams& P, const Spacetim
     adj::ParBar pb;
     int status = forward_to_hit(P, st, ray, sto, &f);
     if (status == ADJ_OK) {
-        seed(P, f.zs[0], f.ks[0], f.ks[1], f.E, f.L, P.cot[ray], zb, &pb, &gr);
+        adj::seed(P.dm, im.a, im.r_in, f.zs[0], f.ks[0], f.ks[1], f.E, f.L, P.cot[ray], zb, &pb, &gr);
         adj::dp_step_vjp<false>(im.M, im.a, f.E, f.L, f.y, f.hstar, zb, &pb);
         status = sweep_lane(P, st, lane, f, zb, &pb);
     }
@@ -371,17 +356,23 @@ __device__ __forceinline__ unsigned long long block_scan(unsigned long long v, u
 // (all steps + 3 times the split ones) / lanes: splitting fewer would leave
 // that sweep running alone at the end, splitting more only adds work.  With a
 // threshold of the caller's, the rays above it are split.
+// The forward pass's waves sweep their own rays where that pass is bound by its
+// longest ray, that is where a lane's share of all steps is at most half of that
+// ray's: ms of a fit's step without and with it, by that share, 512x512 at 45
+// degrees (0.32) 8.4 and 7.0, 560x560 at 60 degrees 9.3 and 8.2; where lanes
+// have more to do the sweeps are better dealt out once, in order of length:
+// 480x480 at 30 degrees 6.3 and 7.6, 640x640 at 30 degrees 11.7 and 12.9.
 __global__ void __launch_bounds__(SORT_BLOCK) adjoint_split_kernel(const AdjParams P) {
     constexpr int PER = SORT_BINS / SORT_BLOCK;  // consecutive bins per thread
     static_assert(SORT_BINS % SORT_BLOCK == 0, "bins must split evenly over the block");
     __shared__ unsigned long long part[SORT_BLOCK];
     __shared__ unsigned long long all_steps;
-    __shared__ int stop_store, stop_split;
+    __shared__ int stop_store, stop_split, longest_bin;
     const int t = threadIdx.x;
     const int covered = (P.max_ckpt << P.ck_shift) / 4 - 2;  // v of the longest bin within the checkpoints
     const int skip = SORT_BINS - 2 < covered ? 0 : SORT_BINS - 2 - covered;
     const uint32_t first = P.hist[skip];
-    if (t == 0) stop_store = stop_split = SORT_BINS;
+    if (t == 0) stop_store = stop_split = longest_bin = SORT_BINS;
     uint32_t cnt[PER];
     unsigned long long need = 0;
     for (int i = 0; i < PER; ++i) {
@@ -407,6 +398,7 @@ __global__ void __launch_bounds__(SORT_BLOCK) adjoint_split_kernel(const AdjPara
         if (k >= stop_store) cnt[i] = 0u;
         steps += static_cast<unsigned long long>(cnt[i]) * static_cast<unsigned long long>(4 * v + 2);
         items += static_cast<unsigned long long>(cnt[i]) * static_cast<unsigned long long>(4 * ((4 * v + 4) / ADJ_SEG + 1));
+        if (cnt[i] != 0u) atomicMin(&longest_bin, k);
     }
     unsigned long long run_steps = block_scan(steps, part);
     if (t == SORT_BLOCK - 1) all_steps = run_steps;
@@ -431,19 +423,21 @@ __global__ void __launch_bounds__(SORT_BLOCK) adjoint_split_kernel(const AdjPara
         P.counters[ADJ_C_FIRST] = first;
         P.counters[ADJ_C_END] = P.hist[stop_store - 1];
         P.counters[ADJ_C_SPLIT] = P.hist[stop_split - 1] - first;
+        P.counters[ADJ_C_OVERLAP] = 2ull * all_steps <= static_cast<unsigned long long>(4 * (SORT_BINS - longest_bin)) * P.grid_lanes ? 1u : 0u;
     }
 }
 
-// The seeds of the stored rays, from the crossing that the forward pass left
-// in each record, and the items of the split ones.
+// The seeds of the rays that no wave of the forward pass has swept, from the
+// crossing left in each record, and the items of the split ones.
 __global__ void __launch_bounds__(ADJ_BLOCK) adjoint_seed_kernel(const AdjParams P) {
-    const uint32_t n = P.counters[ADJ_C_END] - P.counters[ADJ_C_FIRST], n_split = P.counters[ADJ_C_SPLIT];
+    const uint32_t n_split = P.counters[ADJ_C_SPLIT];
+    const uint32_t n = P.counters[ADJ_C_OVERLAP] != 0u ? n_split : P.counters[ADJ_C_END] - P.counters[ADJ_C_FIRST];
     for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x) {
         AdjLong& rec = P.longs[k];
         if (rec.status != ADJ_OK) continue;
         double zb[5], gr;
         adj::ParBar pb;
-        seed(P, rec.zb[0], rec.zb[1], rec.zb[2], rec.E, rec.L, P.cot[rec.ray], zb, &pb, &gr);
+        adj::seed(P.dm, P.im.a, P.im.r_in, rec.zb[0], rec.zb[1], rec.zb[2], rec.E, rec.L, P.cot[rec.ray], zb, &pb, &gr);
         rec.zb[0] = zb[0];
         rec.zb[1] = zb[1];
         rec.zb[2] = rec.zb[3] = 0.0;
@@ -459,111 +453,6 @@ __global__ void __launch_bounds__(ADJ_BLOCK) adjoint_seed_kernel(const AdjParams
         // the split kernel left room for every split ray's items
         if (ib + 4u * n_seg > P.item_cap) rec.status = ADJ_OVERFLOW;
         for (uint32_t i = 0; i < 4u * n_seg && ib + i < P.item_cap; ++i) P.owner[ib + i] = k;
-    }
-}
-
-// The sweeps: the unsplit stored rays, longest first, then the split rays'
-// segment items.  Each lane works through one of them, a step VJP per
-// iteration from the step's entry in the store (the next one's is fetched
-// meanwhile), and takes another from the wave's ticket when it is done; lanes
-// of a wave need not run rays of one length.
-//
-// Bound by the FP64 vector issue rate: ~1300 vector instructions per step of
-// a wave, 40 bytes read per lane and step.  Two waves per SIMD fit (see
-// stage_fence) and hide each other's loads.
-__global__ void __launch_bounds__(ADJ_BLOCK) __attribute__((amdgpu_waves_per_eu(2)))
-adjoint_sweep_kernel(const AdjParams P) {
-    const double M = P.im.M, a = P.im.a;
-    const uint32_t n_split = P.counters[ADJ_C_SPLIT];
-    const uint32_t n_whole = P.counters[ADJ_C_END] - P.counters[ADJ_C_FIRST] - n_split;
-    const uint32_t total = n_whole + min(P.counters[ADJ_C_ITEMS], P.item_cap);
-    bool more = true;
-    int left = -1;  // steps of this lane's item still to do, after the current one; -1: idle
-    uint32_t item = 0;
-    const double* e = nullptr;  // the current step's entry
-    double y0 = 0.0, y1 = 0.0, y3 = 0.0, y4 = 0.0, h = 0.0, E = 0.0, L = 0.0;
-    double b0 = 0.0, b1 = 0.0, b3 = 0.0, b4 = 0.0;
-    adj::ParBar pb{0.0, 0.0, 0.0};
-    for (;;) {
-        unsigned long long idle = __ballot(left < 0);
-        while (idle != 0ull && more) {
-            const uint32_t want = static_cast<uint32_t>(__popcll(idle));
-            const int leader = __ffsll(idle) - 1;
-            uint32_t base = 0;
-            if (static_cast<int>(__lane_id()) == leader) base = atomicAdd(P.counters + ADJ_C_SWEEP, want);
-            base = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(base), leader));
-            more = base < total;
-            const uint32_t rank = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(idle >> 32),
-                                                            __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(idle), 0u));
-            item = left < 0 ? base + rank : item;
-            if (left < 0 && item < total) {
-                const uint32_t w = item - n_whole;
-                const AdjLong& rec = P.longs[item < n_whole ? n_split + item : P.owner[w]];
-                if (rec.status == ADJ_OK) {
-                    int last = rec.n, first = 0;
-                    if (item < n_whole) {
-                        b0 = rec.zb[0];
-                        b1 = rec.zb[1];
-                        b3 = b4 = 0.0;
-                        pb = adj::ParBar{rec.pb[0], rec.pb[1], rec.pb[2]};
-                    } else {
-                        const uint32_t local = w - rec.item_base, b = local & 3u;
-                        first = static_cast<int>(local >> 2) * ADJ_SEG;
-                        last = min(last, first + ADJ_SEG - 1);
-                        b0 = b == 0u ? 1.0 : 0.0;
-                        b1 = b == 1u ? 1.0 : 0.0;
-                        b3 = b == 2u ? 1.0 : 0.0;
-                        b4 = b == 3u ? 1.0 : 0.0;
-                        pb = adj::ParBar{0.0, 0.0, 0.0};
-                    }
-                    E = rec.E;
-                    L = rec.L;
-                    left = last - first;
-                    e = P.long_store + (static_cast<size_t>(rec.base) + static_cast<size_t>(last)) * ADJ_ENTRY;
-                    y0 = e[0];
-                    y1 = e[1];
-                    y3 = e[2];
-                    y4 = e[3];
-                    h = e[4];
-                }
-            }
-            idle = __ballot(left < 0);
-        }
-        if (__ballot(left >= 0) == 0ull) break;
-        if (left < 0) continue;
-        const double y[5] = {y0, y1, 0.0, y3, y4}, hs = h;
-        double yb[5] = {b0, b1, 0.0, b3, b4};
-        if (left > 0) {
-            e -= ADJ_ENTRY;
-            y0 = e[0];
-            y1 = e[1];
-            y3 = e[2];
-            y4 = e[3];
-            h = e[4];
-        }
-        adj::dp_step_vjp<false>(M, a, E, L, y, hs, yb, &pb);
-        b0 = yb[0];
-        b1 = yb[1];
-        b3 = yb[3];
-        b4 = yb[4];
-        if (--left < 0) {
-            double *z, *q;
-            if (item < n_whole) {
-                AdjLong& rec = P.longs[n_split + item];
-                z = rec.zb;
-                q = rec.pb;
-            } else {
-                z = P.items + static_cast<size_t>(item - n_whole) * 8u;
-                q = z + 4;
-            }
-            z[0] = b0;
-            z[1] = b1;
-            z[2] = b3;
-            z[3] = b4;
-            q[0] = pb.E;
-            q[1] = pb.L;
-            q[2] = pb.a;
-        }
     }
 }
 
@@ -715,13 +604,17 @@ static Params forward_params(const AdjParams& p) {
     f.batch = 4;
     f.min_idle = 8;
     f.adj.list = p.list;
-    f.adj.range = p.counters + ADJ_C_FIRST;
     f.adj.n_steps = p.n_steps;
     f.adj.r_hit = p.r_hit;
+    f.adj.cot = p.cot;
+    f.adj.counters = p.counters;
     f.adj.recs = p.longs;
     f.adj.store = p.long_store;
-    f.adj.next = p.counters + ADJ_C_STORE;
+    f.adj.owner = p.owner;
+    f.adj.items = p.items;
     f.adj.entries = static_cast<uint32_t>(static_cast<uint64_t>(p.long_cap) * 6u / ADJ_ENTRY);
+    f.adj.item_cap = p.item_cap;
+    f.adj.dm = p.dm;
     return f;
 }
 
@@ -737,11 +630,10 @@ int launch_adjoint(const AdjParams& p, void* stream) {
         hipLaunchKernelGGL(adjoint_split_kernel, dim3(1), dim3(SORT_BLOCK), 0, s, p);
         if (hipGetLastError() != hipSuccess) return -1;
         const int64_t need = (p.n_rays + ADJ_BLOCK - 1) / ADJ_BLOCK;
-        if (launch_trace_store(fwd, static_cast<int>(need < p.trace_blocks ? need : p.trace_blocks), s)) return -1;
+        if (launch_trace_store(fwd, static_cast<int>(need < p.trace_blocks ? need : p.trace_blocks), 0, s)) return -1;
         hipLaunchKernelGGL(adjoint_seed_kernel, dim3(static_cast<int>(need < 1024 ? need : 1024)), dim3(ADJ_BLOCK), 0, s, p);
         if (hipGetLastError() != hipSuccess) return -1;
-        hipLaunchKernelGGL(adjoint_sweep_kernel, dim3(p.grid_lanes / ADJ_BLOCK), dim3(ADJ_BLOCK), 0, s, p);
-        if (hipGetLastError() != hipSuccess) return -1;
+        if (launch_trace_store(fwd, p.trace_blocks, 1, s)) return -1;
         hipLaunchKernelGGL(adjoint_combine_kernel, dim3(static_cast<int>(need < 1024 ? need : 1024)), dim3(ADJ_BLOCK), 0, s, p);
         if (hipGetLastError() != hipSuccess) return -1;
     }

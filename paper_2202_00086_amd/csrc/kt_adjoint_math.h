@@ -245,5 +245,20 @@ __host__ __device__ inline Dual<5> disk_intensity(const DiskModel& dm, double r_
     return g * g * g * em;
 }
 
+// The seeds: cotangents from the intensity at crossing radius r_c with the crossing-time
+// correction; (dr_c, dth_c) are r' and theta' there.
+__host__ __device__ inline void seed(const DiskModel& dm, double a, double r_in, double r_c, double dr_c,
+                                     double dth_c, double E, double L, double w, double zb[5], ParBar* pb,
+                                     double* gr) {
+    const Dual<5> I = disk_intensity(dm, r_c, E, L, a, r_in);
+    *pb = ParBar{w * I.d[1], w * I.d[2], w * I.d[3]};
+    *gr = w * I.d[4];
+    const double rbar = w * I.d[0];
+    // r_c = r(lambda*) with theta(lambda*) = pi/2: dr_c = dr - (r' / theta') dtheta
+    zb[0] = rbar;
+    zb[1] = -rbar * dr_c / dth_c;
+    zb[2] = zb[3] = zb[4] = 0.0;
+}
+
 }  // namespace adj
 }  // namespace kt

@@ -58,14 +58,17 @@ struct Image {
 // start and its size), a ray's in order from its record's base.
 struct AdjLong;
 struct AdjStore {
-    const uint32_t* list;     // the work list; the stored rays are [range[0], range[1])
-    const uint32_t* range;
+    const uint32_t* list;     // the work list; the stored rays are [FIRST, END) of it
     const int32_t* n_steps;   // the forward render's step counts
     const double* r_hit;      // its hit radii, or NULL
-    AdjLong* recs;            // record of list entry t at t - range[0]
+    const double* cot;        // cotangents of the intensity
+    uint32_t* counters;       // ADJ_C_*
+    AdjLong* recs;            // record of list entry t at t - FIRST
     double* store;
-    uint32_t* next;           // entries taken so far
-    uint32_t entries;
+    const uint32_t* owner;    // record of each segment item
+    double* items;            // [item_cap][8]
+    uint32_t entries, item_cap;
+    adj::DiskModel dm;
 };
 
 // Everything a render needs, copied into the workspace by ws_init.
@@ -157,6 +160,7 @@ struct Hot {
     int32_t min_idle;           // idle lanes a refill waits for
     unsigned long long* acc;    // the evaluation counters
     double* store;              // the adjoint's step store
+    int32_t sweep_only;         // STORE: the second launch, which has only sweeps to do
     const Params* cold;         // the workspace copy of Params
 };
 
@@ -170,7 +174,9 @@ struct Hot {
 enum : int { ADJ_OK = 0, ADJ_FAIL = 1, ADJ_OVERFLOW = 2, ADJ_MISMATCH = 3 };
 struct AdjLong {
     int32_t ray, status, n, n_seg;
-    uint32_t base, item_base, pad0, pad1;
+    uint32_t base, item_base;
+    uint32_t next;  // the record that the same lane finished after this one
+    uint32_t left;  // slot of the list of the records whose sweep is left to the second launch
     double zb[4];     // cotangents of (r, theta, p_r, p_theta); first (r, r', theta') at the crossing
     double pb[3];     // of (E, L, a)
     double gr, E, L;  // the r_in gradient (from the seed alone) and the ray constants
@@ -224,7 +230,10 @@ enum : int {
     ADJ_C_TRACE = 5,     // ticket of the forward pass
     ADJ_C_SWEEP = 6,     // ticket of the sweep
     ADJ_C_REDO = 7,      // stored rays left to the one-lane path
-    ADJ_C_COUNT = 8
+    ADJ_C_DONE = 8,      // waves of the forward pass that have no forward ray left
+    ADJ_C_LEFT = 9,      // sweeps left to the second launch
+    ADJ_C_OVERLAP = 10,  // 1: the forward pass's waves sweep their own rays
+    ADJ_C_COUNT = 11
 };
 
 #ifndef KT_ADJ_MAX_LANES
@@ -317,7 +326,8 @@ int validate_single(const kt_camera* camera, const kt_spacetime* spacetime, cons
 
 // Host-side launchers (kt_trace.hip, kt_adjoint.hip).
 int launch_adjoint(const AdjParams& p, void* stream);
-int launch_trace_store(const Params& p, int grid, void* stream);  // the adjoint's forward pass
+// The adjoint's forward pass and sweeps, then (sweep_only) what is left of the sweeps.
+int launch_trace_store(const Params& p, int grid, int sweep_only, void* stream);
 int launch_ws_init(const Params& p, void* stream);  // also copies p into the workspace
 int launch_upload_images(const Image* host, int32_t n, Image* dev, void* stream);
 int launch_order(const Params& p, void* stream);  // fills p.perm (ring-first dispatch)

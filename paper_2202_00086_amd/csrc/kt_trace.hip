@@ -199,6 +199,10 @@ __device__ __forceinline__ void take_step(const ST& st, const RayConst& rc, cons
 }
 
 // The number of lanes below this one in a mask of the wave.
+__device__ __forceinline__ uint32_t uniform(uint32_t v) {
+    return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(v)));
+}
+
 __device__ __forceinline__ uint32_t lanes_below(unsigned long long m) {
     return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
                                      __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u));
@@ -243,6 +247,7 @@ struct Vec5 {
 
 // STORE: the end of a ray that took more steps than its forward render.
 constexpr int FATE_NO_ROOM = 8;
+constexpr uint32_t NO_RECORD = 0xffffffffu;
 
 // The running maxima of |2H| and of |H|_rel = Kabs / D, the latter as its
 // two parts (ratios compared by cross products): no quotient per step.
@@ -251,6 +256,170 @@ __device__ __forceinline__ void keep_max(const Diag& dg, double* max_h2, double*
     if (dg.Kabs * *rel_d > *rel_k * dg.D) {
         *rel_k = dg.Kabs;
         *rel_d = dg.D;
+    }
+}
+
+// STORE: the backward sweeps, a step VJP per iteration from the step's entry in
+// the store (the next one's is fetched meanwhile).  First launch: a wave with no
+// forward ray left sweeps the rays that its own lanes stored, longest first, while
+// other waves still run the longest rays' forward passes, chains of up to 1700
+// steps that keep few lanes busy (512x512 fit: 2.9 ms for 0.8 ms of work, and 2.0
+// ms of sweeps after it).  A lane reads only what it has written itself, so
+// nothing has to be waited for.  Once no wave has a forward ray, the rest of the
+// work is dealt out anew: what a lane has left it puts on a list, also the middle
+// of a sweep, and the second launch's lanes take that list's sweeps and the split
+// rays' segment items from a ticket.  Both launches run this one loop, so the
+// gradients do not depend on where a sweep was cut.
+//
+// Bound by the FP64 vector issue rate: ~1300 vector instructions per step of
+// a wave, 40 bytes read per lane and step.
+__device__ __forceinline__ void sweep(const Hot& hp, uint32_t own) {
+    const AdjStore& A = cold_params(hp.cold).adj;
+    const double M = hp.M, a = hp.a;
+    const bool second = hp.sweep_only != 0;
+    const bool overlap = uniform(A.counters[ADJ_C_OVERLAP]) != 0u;
+    if (!second && !overlap) return;
+    const uint32_t n_split = uniform(A.counters[ADJ_C_SPLIT]);
+    const uint32_t waves = (gridDim.x * blockDim.x) >> 6;
+    uint32_t n_left = 0, total = 0, done = 0, seen = 0;
+    if (second) {
+        n_left = uniform(overlap ? A.counters[ADJ_C_LEFT] : A.counters[ADJ_C_END] - A.counters[ADJ_C_FIRST] - n_split);
+        total = n_left + min(A.counters[ADJ_C_ITEMS], A.item_cap);
+    } else {
+        if (__lane_id() == 0u) atomicAdd(A.counters + ADJ_C_DONE, 1u);
+        const double r_in = cold_params(hp.cold).img0.r_in;
+        for (uint32_t k = own; k != NO_RECORD; k = A.recs[k].next) {
+            AdjLong& o = A.recs[k];
+            double zb[5], gr;
+            adj::ParBar q;
+            adj::seed(A.dm, a, r_in, o.zb[0], o.zb[1], o.zb[2], o.E, o.L, A.cot[o.ray], zb, &q, &gr);
+            o.zb[0] = zb[0];
+            o.zb[1] = zb[1];
+            o.zb[2] = o.zb[3] = 0.0;
+            o.pb[0] = q.E;
+            o.pb[1] = q.L;
+            o.pb[2] = q.a;
+            o.gr = gr;
+        }
+    }
+    bool more = second;
+    uint32_t rec = 0, item = 0;
+    int left = -1;  // steps still to do, after the current one; -1: idle
+    const double* e = nullptr;  // the current step's entry
+    double y0 = 0.0, y1 = 0.0, y3 = 0.0, y4 = 0.0, h = 0.0, E = 0.0, L = 0.0;
+    double b0 = 0.0, b1 = 0.0, b3 = 0.0, b4 = 0.0;
+    adj::ParBar pb{0.0, 0.0, 0.0};
+    const auto begin = [&](int first, int last) {
+        const AdjLong& o = A.recs[rec];
+        E = o.E;
+        L = o.L;
+        left = last - first;
+        e = A.store + (static_cast<size_t>(o.base) + static_cast<size_t>(last)) * ADJ_ENTRY;
+        y0 = e[0];
+        y1 = e[1];
+        y3 = e[2];
+        y4 = e[3];
+        h = e[4];
+    };
+    const auto begin_ray = [&]() {
+        const AdjLong& o = A.recs[rec];
+        b0 = o.zb[0];
+        b1 = o.zb[1];
+        b3 = o.zb[2];
+        b4 = o.zb[3];
+        pb = adj::ParBar{o.pb[0], o.pb[1], o.pb[2]};
+        begin(0, o.n);
+    };
+    const auto put_ray = [&]() {
+        AdjLong& o = A.recs[rec];
+        o.zb[0] = b0;
+        o.zb[1] = b1;
+        o.zb[2] = b3;
+        o.zb[3] = b4;
+        o.pb[0] = pb.E;
+        o.pb[1] = pb.L;
+        o.pb[2] = pb.a;
+    };
+    for (;;) {
+        unsigned long long idle = __ballot(left < 0);
+        while (idle != 0ull && more) {
+            const uint32_t want = static_cast<uint32_t>(__popcll(idle));
+            const int leader = __ffsll(idle) - 1;
+            uint32_t base = 0;
+            if (static_cast<int>(__lane_id()) == leader) base = atomicAdd(A.counters + ADJ_C_SWEEP, want);
+            base = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(base), leader));
+            more = base < total;
+            item = left < 0 ? base + lanes_below(idle) : item;
+            if (left < 0 && item < n_left) {
+                rec = overlap ? A.recs[item].left : n_split + item;
+                if (A.recs[rec].status == ADJ_OK) begin_ray();
+            } else if (left < 0 && item < total) {
+                rec = A.owner[item - n_left];
+                const AdjLong& o = A.recs[rec];
+                if (o.status == ADJ_OK) {
+                    const uint32_t local = item - n_left - o.item_base, b = local & 3u;
+                    const int first = static_cast<int>(local >> 2) * ADJ_SEG;
+                    b0 = b == 0u ? 1.0 : 0.0;
+                    b1 = b == 1u ? 1.0 : 0.0;
+                    b3 = b == 2u ? 1.0 : 0.0;
+                    b4 = b == 3u ? 1.0 : 0.0;
+                    pb = adj::ParBar{0.0, 0.0, 0.0};
+                    begin(first, min(o.n, first + ADJ_SEG - 1));
+                }
+            }
+            idle = __ballot(left < 0);
+        }
+        if (!second && done != waves) {
+            // the count as it was one iteration ago, so that its load is not waited for
+            done = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(seen)));
+            seen = __hip_atomic_load(A.counters + ADJ_C_DONE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (left < 0 && own != NO_RECORD) {
+                rec = own;
+                own = A.recs[rec].next;
+                begin_ray();
+            }
+        } else if (!second) {
+            // no wave has a forward ray left
+            if (left >= 0) {
+                put_ray();
+                A.recs[rec].n = left;
+                A.recs[atomicAdd(A.counters + ADJ_C_LEFT, 1u)].left = rec;
+            }
+            for (; own != NO_RECORD; own = A.recs[own].next)
+                A.recs[atomicAdd(A.counters + ADJ_C_LEFT, 1u)].left = own;
+            break;
+        }
+        if (__ballot(left >= 0) == 0ull) break;
+        if (left < 0) continue;
+        const double y[5] = {y0, y1, 0.0, y3, y4}, hs = h;
+        double yb[5] = {b0, b1, 0.0, b3, b4};
+        if (left > 0) {
+            e -= ADJ_ENTRY;
+            y0 = e[0];
+            y1 = e[1];
+            y3 = e[2];
+            y4 = e[3];
+            h = e[4];
+        }
+        adj::dp_step_vjp<false>(M, a, E, L, y, hs, yb, &pb);
+        b0 = yb[0];
+        b1 = yb[1];
+        b3 = yb[3];
+        b4 = yb[4];
+        if (--left < 0) {
+            if (!second || item < n_left) {
+                put_ray();
+            } else {
+                double* o = A.items + static_cast<size_t>(item - n_left) * 8u;
+                o[0] = b0;
+                o[1] = b1;
+                o[2] = b3;
+                o[3] = b4;
+                o[4] = pb.E;
+                o[5] = pb.L;
+                o[6] = pb.a;
+            }
+        }
     }
 }
 
@@ -304,6 +473,7 @@ trace_kernel(const Hot hp) {
     li.k = 0;
     const uint32_t lane = __lane_id();
     uint32_t n_total;
+    uint32_t adj_first = 0, own_from = NO_RECORD;  // STORE: the first stored ray in the list, the first that its lane sweeps
 
     // this wave's queue of ray ids [q_next, q_end).  A persistent wave's
     // first fetch takes hp.first ids, one per lane, in one atomic; later
@@ -317,7 +487,12 @@ trace_kernel(const Hot hp) {
     {
         const Params& P = cold_params(hp.cold);
         if constexpr (STORE)
-            n_total = P.adj.range[1] - P.adj.range[0];
+            {
+                const uint32_t* c = P.adj.counters;
+                adj_first = uniform(c[ADJ_C_FIRST]);
+                own_from = uniform(c[ADJ_C_OVERLAP] != 0u ? c[ADJ_C_SPLIT] : NO_RECORD);
+                n_total = hp.sweep_only ? 0u : uniform(c[ADJ_C_END]) - adj_first;
+            }
         else
             n_total = P.from_list ? *P.fb_count : static_cast<uint32_t>(P.n_rays);
         first_fetch = P.persistent != 0;
@@ -360,6 +535,7 @@ trace_kernel(const Hot hp) {
     float fac_max = 5.0f;           // growth limit: 1 after a rejection
     int misses = 0;                 // attempts that were not accepted steps
     uint32_t rec = 0, entry = 0, entry_end = 0;  // STORE: the ray's record, its next entry and their end
+    uint32_t own = NO_RECORD, own_last = 0;      // the first and last of the lane's rays that it will sweep itself
     unsigned long long evals_acc = 0, evals32_acc = 0;
     // Attempts are counted for the wave: a lane's are it - it0, its accepted
     // steps those less its misses.  From it_limit on, some lane may have
@@ -425,6 +601,14 @@ trace_kernel(const Hot hp) {
             status = ADJ_OVERFLOW;
         }
         o.status = status;
+        if (status == ADJ_OK && rec >= own_from) {
+            o.next = NO_RECORD;
+            if (own == NO_RECORD)
+                own = rec;
+            else
+                P.adj.recs[own_last].next = rec;
+            own_last = rec;
+        }
         ray = -1;
     };
     const auto write_outputs = [&](int fate, double r_c, double psi, double defl, double thf, double phf, int nsteps,
@@ -485,7 +669,7 @@ trace_kernel(const Hot hp) {
                 const uint32_t slot = q_next + rank;
                 if constexpr (STORE) {
                     rec = slot;
-                    ray = static_cast<int32_t>(P.adj.list[P.adj.range[0] + slot]);
+                    ray = static_cast<int32_t>(P.adj.list[adj_first + slot]);
                 } else
                     ray = P.from_list ? static_cast<int32_t>(P.fb_list[slot])
                       : P.perm    ? static_cast<int32_t>(P.perm[slot])
@@ -504,7 +688,7 @@ trace_kernel(const Hot hp) {
                 if constexpr (STORE) {
                     // room for the forward render's steps and the partial one
                     const uint32_t room = static_cast<uint32_t>(max(P.adj.n_steps[ray], 0)) + 2u;
-                    entry = atomicAdd(P.adj.next, room);
+                    entry = atomicAdd(P.adj.counters + ADJ_C_STORE, room);
                     entry_end = entry + room;
                     AdjLong& o = P.adj.recs[rec];
                     o.ray = ray;
@@ -889,7 +1073,10 @@ trace_kernel(const Hot hp) {
     }
 #undef COLD
 
-    if constexpr (STORE) return;
+    if constexpr (STORE) {
+        sweep(hp, own);
+        return;
+    }
     // one atomic per wave for each evaluation counter
     const unsigned long long evals = wave_sum(evals_acc);
     if (lane == 0 && evals != 0ull) atomicAdd(hp.acc + ACC_EVALS, evals);
@@ -1232,6 +1419,7 @@ static Hot make_hot(const Params& p) {
     hp.min_idle = p.min_idle;
     hp.acc = p.acc;
     hp.store = p.adj.store;
+    hp.sweep_only = 0;
     hp.cold = p.ws_params;
     return hp;
 }
@@ -1344,9 +1532,11 @@ int trace_max_blocks_per_cu(const Params& p, int block) {
 }
 
 #if !KT_TRACE_ONLY
-int launch_trace_store(const Params& p, int grid, void* stream) {
+int launch_trace_store(const Params& p, int grid, int sweep_only, void* stream) {
+    Hot hp = make_hot(p);
+    hp.sweep_only = sweep_only;
     hipLaunchKernelGGL((trace_kernel<KT_DP45, KT_FP64, false, METRIC_KERR, FEAT_DISK, true>), dim3(grid), dim3(BLOCK_MAX), 0,
-                       static_cast<hipStream_t>(stream), make_hot(p));
+                       static_cast<hipStream_t>(stream), hp);
     return check_launch();
 }
 

@@ -155,6 +155,31 @@ def test_stored_passes_equal_the_one_lane_path(K, nx, ny):
                 np.testing.assert_array_equal(a.view(np.uint8), b.view(np.uint8), err_msg=f"{every} {what}")
 
 
+@pytest.mark.parametrize("n,incl_deg,a", [(96, 60.0, 0.5), (420, 25.0, 0.9), (360, 45.0, 0.7)])
+def test_sweeps_do_not_depend_on_who_runs_them(K, n, incl_deg, a):
+    """The waves of the forward pass sweep rays of their own (360x360, 96x96) or
+    none (420x420, nearly face on: every lane has enough to do).  Where a sweep
+    is cut and who goes on with it changes from run to run, the gradients do
+    not, and they equal the one-lane path's to the bound of the split sweeps."""
+    import torch
+    params = W.differentiable_disk(n=n, incl_deg=incl_deg, a=a)
+    _announce("sweeps", n, incl_deg, a)
+    r = K.Renderer(device="cuda:0", want=("fate", "r_hit", "n_cross", "n_steps"), stats=False, **params)
+    out = r.render()
+    torch.cuda.synchronize()
+    cot = torch.linspace(-1.0, 2.0, r.n, dtype=torch.float64, device="cuda:0")
+    first, first_st = _adjoint(K, torch, r, out, cot, r.integ, out["n_steps"])
+    for _ in range(3):
+        maps, st = _adjoint(K, torch, r, out, cot, r.integ, out["n_steps"])
+        assert st.tolist() == first_st.tolist()
+        for x, y in zip(maps, first):
+            np.testing.assert_array_equal(x.view(np.uint8), y.view(np.uint8))
+    lane, lane_st = _adjoint(K, torch, r, out, cot, K.make_structs(**dict(params, split_above=-1))[4], out["n_steps"])
+    assert lane_st.tolist() == first_st.tolist() and lane_st[1:].tolist() == [0, 0, 0]
+    for x, y in zip(first, lane):
+        _assert_split_close(x, y)
+
+
 SPHERE = dict(src_on=1, r_src=700.0)
 THIN = dict(disk_on=1, r_in=6.0, r_out=30.0)
 SKY = dict(sky_on=1, grid_deg=6.0, line_deg=0.25)
