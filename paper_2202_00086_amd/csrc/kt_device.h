@@ -452,14 +452,37 @@ __device__ __forceinline__ void sincos_shift(double s0, double c0, double d, dou
     *c_out = __builtin_fma(c0, cdm1, __builtin_fma(-s0, sd, c0));
 }
 
+// ---------------------------------------------------------------------------
+// Dormand & Prince (1980) RK5(4)7M, first-same-as-last.
+// ---------------------------------------------------------------------------
+namespace dp {
+constexpr double A21 = 1.0 / 5;
+constexpr double A31 = 3.0 / 40, A32 = 9.0 / 40;
+constexpr double A41 = 44.0 / 45, A42 = -56.0 / 15, A43 = 32.0 / 9;
+constexpr double A51 = 19372.0 / 6561, A52 = -25360.0 / 2187, A53 = 64448.0 / 6561,
+                 A54 = -212.0 / 729;
+constexpr double A61 = 9017.0 / 3168, A62 = -355.0 / 33, A63 = 46732.0 / 5247, A64 = 49.0 / 176,
+                 A65 = -5103.0 / 18656;
+// 5th-order weights; the 7th stage is evaluated at the 5th-order solution.
+constexpr double B1 = 35.0 / 384, B3 = 500.0 / 1113, B4 = 125.0 / 192, B5 = -2187.0 / 6784,
+                 B6 = 11.0 / 84;
+// error weights: 5th-order minus embedded 4th-order weights
+constexpr double E1 = 71.0 / 57600, E3 = -71.0 / 16695, E4 = 71.0 / 1920,
+                 E5 = -17253.0 / 339200, E6 = 22.0 / 525, E7 = -1.0 / 40;
+constexpr int N_COEF = 26;
+constexpr double COEF[N_COEF] = {A21, A31, A32, A41, A42, A43, A51, A52, A53, A54, A61, A62, A63,
+                                 A64, A65, B1,  B3,  B4,  B5,  B6,  E1,  E3,  E4,  E5,  E6,  E7};
+}  // namespace dp
+
 // The two functions as the steppers call them: with the constants of the one
 // that a stepper leans on pinned in registers (SHIFT for the Runge-Kutta
 // pairs, THETA for Bulirsch-Stoer), the other's left to the compiler; and for
 // RK4, short enough for the compiler to keep them all, both.
-template <bool SHIFT = false, bool THETA = false>
+template <bool SHIFT = false, bool THETA = false, int COEFS = 0>
 struct Elem {
     HornerK<9, 4> ks;
     HornerK<15, 8> kt;
+    double tab[COEFS > 0 ? COEFS : 1];
     __device__ __forceinline__ Elem() {
         double s, c;
         if constexpr (SHIFT) {
@@ -470,7 +493,13 @@ struct Elem {
             sincos_theta(0.0, &s, &c, HornerRecord<15, 8>{&kt});
             pin(&kt);
         }
+#pragma unroll
+        for (int i = 0; i < COEFS; ++i) {
+            tab[i] = dp::COEF[i];
+            asm volatile("" : "+v"(tab[i]));
+        }
     }
+    __device__ __forceinline__ double coef(int i) const { return i < COEFS ? tab[i] : dp::COEF[i]; }
     __device__ __forceinline__ void shift(double s0, double c0, double d, double* s, double* c) const {
         if constexpr (SHIFT)
             sincos_shift(s0, c0, d, s, c, HornerUse<true, 9, 4>{&ks});
@@ -592,25 +621,6 @@ __device__ __forceinline__ void eval_rhs(const ST& st, const Spacetime32* sf, co
         field_at<D>(st, rc, z, s, c, out, dg);
 }
 
-// ---------------------------------------------------------------------------
-// Dormand & Prince (1980) RK5(4)7M, first-same-as-last.
-// ---------------------------------------------------------------------------
-namespace dp {
-constexpr double A21 = 1.0 / 5;
-constexpr double A31 = 3.0 / 40, A32 = 9.0 / 40;
-constexpr double A41 = 44.0 / 45, A42 = -56.0 / 15, A43 = 32.0 / 9;
-constexpr double A51 = 19372.0 / 6561, A52 = -25360.0 / 2187, A53 = 64448.0 / 6561,
-                 A54 = -212.0 / 729;
-constexpr double A61 = 9017.0 / 3168, A62 = -355.0 / 33, A63 = 46732.0 / 5247, A64 = 49.0 / 176,
-                 A65 = -5103.0 / 18656;
-// 5th-order weights; the 7th stage is evaluated at the 5th-order solution.
-constexpr double B1 = 35.0 / 384, B3 = 500.0 / 1113, B4 = 125.0 / 192, B5 = -2187.0 / 6784,
-                 B6 = 11.0 / 84;
-// error weights: 5th-order minus embedded 4th-order weights
-constexpr double E1 = 71.0 / 57600, E3 = -71.0 / 16695, E4 = 71.0 / 1920,
-                 E5 = -17253.0 / 339200, E6 = 22.0 / 525, E7 = -1.0 / 40;
-}  // namespace dp
-
 // One DP5(4) step of size h from y with k1 = f(y).  Writes the 5th-order
 // solution yn, kn = f(yn) with its diagnostics, and the error vector err.
 // Six RHS evaluations.
@@ -620,7 +630,12 @@ __device__ __forceinline__ void dp45_step(const ST& st, const RayConst& rc, cons
                                           const double k1[5], double s0, double c0, double h, double yn[5],
                                           double kn[5], double err[5], Diag* dg,
                                           const Spacetime32* sf = nullptr, const EL& el = EL{}) {
-    using namespace dp;
+    const double A21 = el.coef(0), A31 = el.coef(1), A32 = el.coef(2), A41 = el.coef(3), A42 = el.coef(4),
+                 A43 = el.coef(5), A51 = el.coef(6), A52 = el.coef(7), A53 = el.coef(8), A54 = el.coef(9),
+                 A61 = el.coef(10), A62 = el.coef(11), A63 = el.coef(12), A64 = el.coef(13), A65 = el.coef(14),
+                 B1 = el.coef(15), B3 = el.coef(16), B4 = el.coef(17), B5 = el.coef(18), B6 = el.coef(19),
+                 E1 = el.coef(20), E3 = el.coef(21), E4 = el.coef(22), E5 = el.coef(23), E6 = el.coef(24),
+                 E7 = el.coef(25);
     double k2[5], k3[5], k4[5], k5[5], k6[5], ys[5];
 #pragma unroll
     for (int i = 0; i < 5; ++i) ys[i] = fma(h, A21 * k1[i], y[i]);

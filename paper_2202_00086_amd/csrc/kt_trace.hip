@@ -461,6 +461,8 @@ trace_kernel(const Hot hp) {
     constexpr bool MIXED = (PREC == KT_MIXED) && (METHOD == KT_DP45) && !QMET;
     constexpr bool LONG_STEPS = METHOD == KT_BS || METHOD == KT_BS_RAT;
     constexpr bool PIN_SHIFT = !LONG_STEPS && METHOD != KT_RK4_S, PIN_THETA = LONG_STEPS && !QMET && KT_WAVES_PER_EU < 3;
+    constexpr int PIN_COEFS =
+        KT_WAVES_PER_EU < 3 && METHOD == KT_DP45 && !QMET && !MIXED && FEAT >= 0 ? ((FEAT & FEAT_SRC) ? 8 : 20) : 0;
     constexpr bool MAY_DISK = FEAT < 0 ? !QMET : (FEAT & FEAT_DISK) != 0;
     constexpr bool MAY_SRC = FEAT < 0 || (FEAT & FEAT_SRC) != 0;
     __shared__ double cold[N_COLD][BLOCK_MAX];
@@ -507,12 +509,16 @@ trace_kernel(const Hot hp) {
         exhausted = true;
     }
 
-    // The constants kept in registers: those of the shift from the base point,
+    // The constants kept in registers: as many of the Dormand-Prince tableau's 26
+    // as there are registers left in the 2-wave build (a wave alone on its SIMD
+    // waits for each scalar move that sets one up, ~40 in 626 instructions of an
+    // attempt: 96x96 ring 2.71 -> 2.64 ms, 512x512 lensing 3.24 -> 3.06; with three
+    // waves per SIMD others fill in); those of the shift from the base point,
     // which every Runge-Kutta stage needs; of sin/cos of theta itself, which
     // each Bulirsch-Stoer substep needs, only where the registers reach (2
     // waves: norm check of 625x625 rays 3.64 ms without, 3.51 with; 3 waves:
     // 1200x1000 rays 15.1 without, 15.9 with).
-    const Elem<PIN_SHIFT, PIN_THETA> el;
+    const Elem<PIN_SHIFT, PIN_THETA, PIN_COEFS> el;
     int32_t ray = -1;
     int fl = 0;
     Vec5 ys{}, ks{};  // the state and the field there
