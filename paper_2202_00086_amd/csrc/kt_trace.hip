@@ -1201,23 +1201,56 @@ __global__ void ws_init_kernel(const Params p) {
 // ---- dispatch order ------------------------------------------------------
 // Rays near the photon ring take the most steps; the persistent waves finish
 // soonest when those go out first and the cheap rays fill the tail.  The
-// slots are sorted by the bin of |rho - rho_ring| (a counting sort over
+// slots are sorted by the bin of the distance from the ring (a counting sort over
 // SORT_BINS bins).  Every ray's arithmetic is independent of the lane and
 // wave that runs it, so outputs do not change.
-#ifndef KT_ORDER_GROUP_SHIFT
-#define KT_ORDER_GROUP_SHIFT 5
-#endif
-// Rays go out in groups of consecutive ids (keyed by the group's first
+//
+// Rays go out in groups of consecutive ids (keyed by the group's middle
 // ray), so the outputs of neighbouring pixels, which share cache lines, are
 // written close together in time and merge in L2 instead of reaching HBM as
-// many partial-line writes.
-constexpr int64_t ORDER_GROUP_MASK = (int64_t{1} << KT_ORDER_GROUP_SHIFT) - 1;
+// many partial-line writes.  Where there are few rays per lane a group of 32 mixes
+// long and short ones: 32 and 16 rays give 2.65/2.57 ms on the 96x96 ring and
+// 6.35/5.87 on a 625x600 norm map; with many the writes count, 15.46/15.50 on the
+// 1024x1024 ring and 9.83/9.88 on the 1365x683 disk.  The q-metric, whose ring is
+// no exact one, keeps groups of 32 (477x361: 6.12 ms, with 16 6.25).
+constexpr int64_t ORDER_SMALL = int64_t{1} << 19;
+__device__ __forceinline__ int64_t order_group(const Params& P, int64_t ray) {
+    const int shift = P.n_rays < ORDER_SMALL && P.images[0].metric == KT_METRIC_KERR ? 4 : 5;
+    return min(((ray >> shift) << shift) + (int64_t{1} << (shift - 1)), static_cast<int64_t>(P.n_rays) - 1);
+}
+
+// How far a Kerr ray is from one that is caught on a spherical photon orbit, in
+// units of the image plane: the difference of sqrt(kappa) = (p_theta^2 + (L / sin
+// theta - a E sin theta)^2)^(1/2) / E and its critical value for the ray's L / E.
+// The spherical orbit of radius r has (r - M)(r^2 + a^2 - a L / E) = 2 r Delta, a
+// cubic in r (Bardeen 1973), and kappa = 4 r^2 Delta / (r - M)^2; outside the range of
+// L / E that has one, the equatorial photon orbit's value continues it.  Single
+// precision and the hardware's sine: it only orders the dispatch.  Against the
+// circle of a hole without spin: a 625x600 norm map at a = 0.98 8.25 -> 5.87 ms,
+// by Bulirsch-Stoer 3.52 -> 3.30, a 1000x1000 one 8.39 -> 7.58, the 640x640 mixed
+// disk 8.07 -> 7.86; rings and disks at 60 degrees within 0.5%.
+__device__ __forceinline__ float critical_distance(const Image& im, double x, double y) {
+    const float M = static_cast<float>(im.M), a = static_cast<float>(im.a), si = __sinf(static_cast<float>(im.incl));
+    const float iE = __frcp_rn(static_cast<float>(im.E0 + x * im.cE)), l = static_cast<float>(x * im.cL) * iE;
+    const float pth = static_cast<float>(y * im.cth) * iE, t = __fdividef(l, si) - a * si;
+    const float third = acosf(fminf(fabsf(a) / M, 1.0f)) * (2.0f / 3.0f);
+    const float r_pro = 2.0f * M * (1.0f + __cosf(2.0943951f - third)), r_ret = 2.0f * M * (1.0f + __cosf(third));
+    const float b = a * (a + l), c = M * a * (a - l);
+    float r = 0.5f * (3.0f * M + sqrtf(fmaxf(9.0f * M * M - 4.0f * b, 0.0f)));
+    for (int k = 0; k < 4; ++k) {
+        const float f = ((r - 3.0f * M) * r + b) * r + c, df = (3.0f * r - 6.0f * M) * r + b;
+        r = fminf(fmaxf(r - __fdividef(f, df), r_pro), r_ret);
+    }
+    const float q = __fdividef(1.0f, fmaxf(r - M, 1e-4f * M));
+    const float crit = 2.0f * r * sqrtf(fmaxf(1.0f - (M - a) * (M + a) * q * q, 0.0f));
+    return fabsf(sqrtf(pth * pth + t * t) - crit);
+}
 
 struct RingKey {
     const Params* p;  // the workspace copy
     __device__ int operator()(int64_t ray) const {
         const Params& P = *p;
-        ray &= ~ORDER_GROUP_MASK;
+        ray = order_group(P, ray);
         const Image* im = P.images;
         int64_t pix = ray;
         if (P.n_images > 1) {
@@ -1228,7 +1261,12 @@ struct RingKey {
         const int32_t i = static_cast<int32_t>(pix - static_cast<int64_t>(j) * im->nx);
         const double x = -im->fov_x + (static_cast<double>(i) + 0.5) * im->dx;
         const double y = -im->fov_y + (static_cast<double>(j) + 0.5) * im->dy;
-        const double d = fabs(sqrt(fma(x, x, y * y)) - im->rho_ring) * im->order_scale;
+        double d = fabs(sqrt(fma(x, x, y * y)) - im->rho_ring);
+        if (im->metric == KT_METRIC_KERR && im->a != 0.0 && im->rho_ring > 0.0) {
+            const double kerr = critical_distance(*im, x, y) * (im->rho_ring / (5.196152422706632 * im->M));
+            if (kerr >= 0.0) d = kerr;  // NaN for an observer on the axis
+        }
+        d *= im->order_scale;
         return d < static_cast<double>(SORT_BINS - 1) ? static_cast<int>(d) : SORT_BINS - 1;
     }
 };
