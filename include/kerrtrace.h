@@ -169,9 +169,9 @@ typedef struct kt_integrator {
    instructions per step).  A persistent launch runs the 3-wave build when its
    shape asks for 3 or more waves per SIMD (blocks_per_cu * block >= 768).
    blocks_per_cu 0 picks the waves per SIMD from the number of rays: 1 up to 4
-   rays per lane of a one-wave grid (262144 rays on 256 CUs), 3 from 12 rays
-   per lane (786432), 2 between; for the Bulirsch-Stoer schemes 1 up to 10
-   rays per lane, then 3.  Other launches run the 2-wave build. */
+   rays per lane of a one-wave grid (262144 rays on 256 CUs), 3 from 32 rays
+   per lane (2097152), 2 between; for the Bulirsch-Stoer schemes 1 up to 9 rays
+   per lane, then 2.  Other launches run the 2-wave build. */
 typedef struct kt_launch {
     int32_t persistent;     /* 1: persistent waves refill lanes from a global ticket;
                                0: one ray per lane, no refill */
@@ -185,7 +185,8 @@ typedef struct kt_launch {
 /* Dispatch order.  Outputs are identical under both; only the time differs.
    KT_ORDER_RING sends rays out by their image-plane distance from the
    photon ring (nearest first: they take the most steps), sorted on the
-   device at the start of each render; KT_ORDER_ROWS sends pixel ids in
+   device at the start of each render (with blocks_per_cu 0 only if there are
+   more rays than lanes of a one-wave grid); KT_ORDER_ROWS sends pixel ids in
    row-major order. */
 #define KT_ORDER_RING 0
 #define KT_ORDER_ROWS 1

@@ -82,21 +82,28 @@ double device_wall_khz() {
 // the VALU busier, but each ray then takes longer in wall time, and the
 // launch ends with its longest rays, so the choice goes by the rays per lane
 // of a one-wave grid (65536 lanes on 256 CUs).  Measured, ms per image at
-// 1 / 2 / 3 waves, on ring, lensing, disk and q-metric images:
-//   362x362 (2 rays per lane)    3.56/4.30/4.72  3.04/3.49/4.01  2.42/2.64/2.49  5.62/7.02/7.22
-//   512x512 (4)                  6.01/5.82/7.03  3.65/3.88/5.17  3.93/4.09/4.41  7.31/8.04/9.51
-//   600x600 (5.5)                7.65/7.05/7.76  4.76/4.62/6.19  5.15/4.89/5.35  9.68/9.67/11.2
-//   900x900 (12.4)               16.6/13.9/13.9  10.2/8.62/8.80  11.0/9.24/9.39  20.7/18.2/18.5
-//   1024x1024 (16)               21.3/17.5/16.8  13.1/10.8/10.7  14.1/11.6/11.7  26.6/22.8/23.0
-// and 3 waves are 2-4% ahead of 2 on images of 2M rays and more.  A
-// Bulirsch-Stoer step is 26 evaluations without the registers' worth of
-// staged values, and two waves never lead: 724x724 5.99/7.02/6.24, 900x900
-// 8.94/9.43/8.46, 1024x1024 11.4/11.1/10.5.
-constexpr int64_t ONE_WAVE_MAX_RAYS_PER_LANE = 4, THREE_WAVE_MIN_RAYS_PER_LANE = 12, BS_ONE_WAVE_MAX_RAYS_PER_LANE = 10;
+// 1 / 2 / 3 waves, on ring, disk (a = 0.9) and disk (a = 0) images:
+//   448x448 (3.1 rays per lane)  4.04/4.26/5.43  2.80/3.43/4.32  2.82/2.97/3.65
+//   512x512 (4)                  5.09/5.40/6.36  3.37/3.59/4.63  3.50/3.56/4.00
+//   576x576 (5.1)                6.18/5.98/6.54  4.09/4.19/4.74  4.29/4.30/4.82
+//   768x768 (9)                  10.4/9.36/9.69  6.89/6.48/6.79  7.26/6.56/6.81
+//   1024x1024 (16)               17.9/15.0/15.4  11.7/10.4/10.7  12.5/10.5/10.7
+//   1448x1448 (32)               -/28.9/29.0                     -/20.2/20.0
+//   2048x2048 (64)               -/57.0/56.8     -/38.9/38.5     -/39.6/39.0
+// The other Runge-Kutta pairs, the mixed form, the q-metric (12.4 rays per lane
+// 16.9/17.8 at 2/3 waves, 22 28.8/28.9) and batches (117: 75.2/73.7) cross over
+// there too.  The 3-wave build has no registers for the paired midpoint substeps
+// of Bulirsch-Stoer, which never takes it; 1 / 2 / 3 waves on the ring and on a
+// norm map of a = 0.98 seen edge on, whose longest rays take more of the time:
+//   625x625 (6)     4.80/4.38/5.23  3.48/4.41/5.44
+//   768x768 (9)     7.08/6.15/7.02  4.99/5.73/6.30
+//   1024x1024 (16)  12.3/10.3/11.5  8.47/8.89/10.3
+//   1200x1200 (22)  16.8/13.9/15.5  11.5/10.7/12.8
+constexpr int64_t ONE_WAVE_MAX_RAYS_PER_LANE = 4, THREE_WAVE_MIN_RAYS_PER_LANE = 32, BS_ONE_WAVE_MAX_RAYS_PER_LANE = 9;
 
 int waves_per_simd(int32_t method, int64_t n_rays) {
     const int64_t lanes = static_cast<int64_t>(device_cus()) * 4 * 64;
-    if (method == KT_BS || method == KT_BS_RAT) return n_rays <= BS_ONE_WAVE_MAX_RAYS_PER_LANE * lanes ? 1 : 3;
+    if (method == KT_BS || method == KT_BS_RAT) return n_rays <= BS_ONE_WAVE_MAX_RAYS_PER_LANE * lanes ? 1 : 2;
     if (n_rays <= ONE_WAVE_MAX_RAYS_PER_LANE * lanes) return 1;
     return n_rays >= THREE_WAVE_MIN_RAYS_PER_LANE * lanes ? 3 : 2;
 }
@@ -436,7 +443,13 @@ int render_images(const kt::Image* table, int32_t n_images, int64_t n_rays, cons
     p.rc_buf = reinterpret_cast<double*>(ws + w.rc);
     p.fb_list = reinterpret_cast<uint32_t*>(ws + w.fb_list);
     p.need_fb = reinterpret_cast<uint8_t*>(ws + w.need);
-    if (ln.order == KT_ORDER_RING) {
+    // With a ray for every lane of a one-wave grid or fewer all rays start
+    // together: an order by length has nothing to give, and its sort takes longer
+    // than it saves (72x72 disk 1.60/1.56 ms with and without, 250x250 disk
+    // 2.23/2.17, 200x200 shadow 2.83/2.79; 300x300, 1.4 rays per lane, on the
+    // q-metric 5.44/6.38).
+    const bool all_at_once = ln.persistent && n_rays <= static_cast<int64_t>(device_cus()) * 4 * 64;
+    if (ln.order == KT_ORDER_RING && !(all_at_once && ln.blocks_per_cu == 0)) {
         p.perm = reinterpret_cast<uint32_t*>(ws + w.perm);
         p.order_hist = reinterpret_cast<uint32_t*>(ws + w.hist);
         p.order_bins = reinterpret_cast<uint16_t*>(ws + w.bins);

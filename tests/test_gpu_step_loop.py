@@ -96,8 +96,8 @@ def test_budgets_end_every_ray_alike(K, method, budget):
 
 
 # rays per lane of one wave per SIMD at which the default changes, and one row more
-@pytest.mark.parametrize("nx,ny,method", [(512, 512, 1), (512, 513, 1), (1024, 767, 1), (1024, 768, 1),
-                                          (1024, 640, 4), (1024, 641, 4)])
+@pytest.mark.parametrize("nx,ny,method", [(512, 512, 1), (512, 513, 1), (2048, 1023, 1), (2048, 1024, 1),
+                                          (768, 768, 4), (768, 769, 4)])
 def test_default_launch_on_both_sides_of_its_lines(K, nx, ny, method):
     params = dict(RING, nx=nx, ny=ny, method=method)
     _announce("default launch", nx, ny, method)
