@@ -345,27 +345,27 @@ int kt_autotune_batch(int32_t n_images, const kt_image *images, const kt_integra
    Inputs: the same camera, spacetime, disk and integrator as the forward
    kt_render (method KT_DP45, KT_FP64, disk enabled), and that render's fate
    array, its r_hit array (optional, for a bit-identity check) and its
-   n_steps array (optional: the differentiated rays are run longest first
-   and neighbouring lanes get rays of similar length, and long rays can be
-   split, below).  Each ray is re-integrated with the forward's own
-   arithmetic, checkpointed every integ->checkpoint_every accepted steps (64
-   when 0), and swept backward segment by segment, each segment recomputed
-   from its checkpoint; with checkpoint_every 1 every accepted step is
+   n_steps array (optional: the differentiated rays are run longest first,
+   their forward passes are stored and long rays can be split, below).  Each ray
+   is re-integrated with the forward's own arithmetic.  With n_steps and
+   integ->split_above >= 0 every accepted step goes to a store of 256 steps per
+   pixel (at least; 8 GiB at most, 524288 rays) and the backward sweep reads it;
+   the rays that this has no room for, those that take more steps than n_steps
+   says, and all rays otherwise, are checkpointed every integ->checkpoint_every
+   accepted steps (64 when 0) and swept segment by segment, each segment
+   recomputed from its checkpoint; with checkpoint_every 1 every accepted step is
    stored and the sweep reads them instead (same gradients bit for bit).
-   Split sweeps (n_steps given, integ->split_above >= 0): a ray whose
-   forward took more than split_above accepted steps (0: 0.85 times the mean
-   number of steps per lane of the work list, at least 128; the longest rays
-   first, whole step-count bins of 4 steps at a time, as many as fit 8192
-   records and a store of 32 steps per lane of the grid; rays of more than
-   2046 steps are not split) stores every step, and the transposed Jacobian
-   of each 64-step segment is
+   Split sweeps: the transposed Jacobian of each 64-step segment of a split ray is
    swept on four lanes at once, one per basis cotangent of (r, theta, p_r,
    p_theta) (that of phi stays zero: the field does not depend on phi); the
-   segments' maps are then applied in order to the ray's cotangent.  This
-   cuts the sequential length of the longest rays, which otherwise set the
-   adjoint's run time.  Split rays' gradients equal the sequential sweep's
-   up to rounding (the same products, associated differently); they do not
-   depend on checkpoint_every.
+   segments' maps are then applied in order to the ray's cotangent.  Split are
+   stored rays of more than split_above accepted steps, whole step-count bins of 4
+   steps at a time; with split_above 0 the longest until the longest sweep left is
+   no longer than a lane's share of the work, at least 64 steps.  This cuts the
+   sequential length of the longest rays, which otherwise set the adjoint's run
+   time.  Stored and split rays' gradients equal the others' up to rounding (the
+   same products, fused or associated differently); they do not depend on
+   checkpoint_every.
    stats (device, 4 uint64, may be NULL): rays differentiated, rays that
    failed, rays beyond the checkpoint capacity (max(256, 2048 /
    checkpoint_every) checkpoints, i.e. at least 2048 accepted steps and

@@ -443,11 +443,14 @@ constexpr int FEAT_DYN = -1;
 // FP64 instructions), so everything that is not that arithmetic counts:
 // with each test in a branch of its own, and the per-ray scalars in LDS, an
 // attempt took ~830 vector and ~215 scalar instructions, and a wave alone on
-// its SIMD, as in small images, needed 2.5 us for it.
+// its SIMD, as in small images, needed 2.5 us for it.  It takes 584 and 19 now (a
+// disk, 2-wave build) and 1.45 us: 512x512 lensing 4.9 -> 3.1 ms, 1024x1024 ring
+// 18.1 -> 15.3.
 //
 // STORE: the adjoint's forward pass.  The rays come from its work list, every
 // accepted step and the located partial step go to the ray's range of the
-// step store, and its end to its record instead of the outputs.
+// step store, and its end to its record instead of the outputs; then the wave
+// sweeps (see sweep).
 template <int METHOD, int PREC, bool BATCH, int METRIC = METRIC_KERR, int FEAT = FEAT_DYN, bool STORE = false>
 __global__ void __launch_bounds__(BLOCK_MAX) __attribute__((amdgpu_waves_per_eu(KT_WAVES_PER_EU)))
 trace_kernel(const Hot hp) {
