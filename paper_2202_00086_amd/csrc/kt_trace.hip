@@ -245,7 +245,10 @@ struct Vec5 {
     }
 };
 
-// STORE: the end of a ray that took more steps than its forward render.
+// STORE: the end of a ray that took more steps than its forward render.  It
+// and the rays that end without a step or out of their budget are left to the
+// one-lane path (status ADJ_OVERFLOW), whose budget is one of attempts alone
+// and whose word on failures is the one that counts.
 constexpr int FATE_NO_ROOM = 8;
 constexpr uint32_t NO_RECORD = 0xffffffffu;
 
@@ -594,7 +597,7 @@ trace_kernel(const Hot hp) {
     const auto write_record = [&](int fate, double r_c, double dr_c, double dth_c) {
         const Params& P = cold_params(hp.cold);
         AdjLong& o = P.adj.recs[rec];
-        int status = ADJ_FAIL;
+        int status = ADJ_OVERFLOW;  // no room, no step, or out of the trace's budget
         if (fate == KT_FATE_DISK) {
             status = P.adj.r_hit && !(r_c == P.adj.r_hit[ray]) ? ADJ_MISMATCH : ADJ_OK;
             put_entry();
@@ -606,8 +609,6 @@ trace_kernel(const Hot hp) {
             o.L = rc.L;
         } else if (fate == KT_FATE_CAPTURED || fate == KT_FATE_ESCAPED) {
             status = ADJ_MISMATCH;
-        } else if (fate == FATE_NO_ROOM) {
-            status = ADJ_OVERFLOW;
         }
         o.status = status;
         if (status == ADJ_OK && rec >= own_from) {
@@ -704,7 +705,7 @@ trace_kernel(const Hot hp) {
                     o.base = entry;
                     const bool fits_store = entry_end >= entry && entry_end <= P.adj.entries;
                     if (!valid || !fits_store) {
-                        write_record(fits_store ? static_cast<int>(KT_FATE_INVALID) : FATE_NO_ROOM, 0.0, 0.0, 0.0);
+                        write_record(FATE_NO_ROOM, 0.0, 0.0, 0.0);
                         valid = false;
                     }
                 }
