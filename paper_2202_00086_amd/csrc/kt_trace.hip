@@ -1224,29 +1224,32 @@ __device__ __forceinline__ int64_t order_group(const Params& P, int64_t ray) {
 }
 
 // How far a Kerr ray is from one that is caught on a spherical photon orbit, in
-// units of the image plane: the difference of sqrt(kappa) = (p_theta^2 + (L / sin
-// theta - a E sin theta)^2)^(1/2) / E and its critical value for the ray's L / E.
-// The spherical orbit of radius r has (r - M)(r^2 + a^2 - a L / E) = 2 r Delta, a
-// cubic in r (Bardeen 1973), and kappa = 4 r^2 Delta / (r - M)^2; outside the range of
-// L / E that has one, the equatorial photon orbit's value continues it.  Single
-// precision and the hardware's sine: it only orders the dispatch.  Against the
-// circle of a hole without spin: a 625x600 norm map at a = 0.98 8.25 -> 5.87 ms,
-// by Bulirsch-Stoer 3.52 -> 3.30, a 1000x1000 one 8.39 -> 7.58, the 640x640 mixed
-// disk 8.07 -> 7.86; rings and disks at 60 degrees within 0.5%.
+// units of M: the difference of sqrt(kappa) = (p_theta^2 + (L / sin theta - a E sin
+// theta)^2)^(1/2) / E and its critical value for the ray's L / E.  The spherical
+// orbit of radius r has (r - M)(r^2 + a^2 - a L / E) = 2 r Delta, a cubic in r
+// (Bardeen 1973), and kappa = 4 r^2 Delta / (r - M)^2; outside the range of L / E
+// that has one, the equatorial photon orbit's value continues it.  Single precision
+// and the hardware's sine: it only orders the dispatch.  All lengths are divided by
+// M first: powers of r reach past the range of single precision where M is 1e13,
+// and rays then fall into bins by chance (512x512 ring 6.8 ms instead of 5.3).
+// Against the circle of a hole without spin: a 625x600 norm map at a = 0.98 8.25 ->
+// 5.87 ms, by Bulirsch-Stoer 3.52 -> 3.30, a 1000x1000 one 8.39 -> 7.58, the 640x640
+// mixed disk 8.07 -> 7.86; rings and disks at 60 degrees within 0.5%.
 __device__ __forceinline__ float critical_distance(const Image& im, double x, double y) {
-    const float M = static_cast<float>(im.M), a = static_cast<float>(im.a), si = __sinf(static_cast<float>(im.incl));
-    const float iE = __frcp_rn(static_cast<float>(im.E0 + x * im.cE)), l = static_cast<float>(x * im.cL) * iE;
-    const float pth = static_cast<float>(y * im.cth) * iE, t = __fdividef(l, si) - a * si;
-    const float third = acosf(fminf(fabsf(a) / M, 1.0f)) * (2.0f / 3.0f);
-    const float r_pro = 2.0f * M * (1.0f + __cosf(2.0943951f - third)), r_ret = 2.0f * M * (1.0f + __cosf(third));
-    const float b = a * (a + l), c = M * a * (a - l);
-    float r = 0.5f * (3.0f * M + sqrtf(fmaxf(9.0f * M * M - 4.0f * b, 0.0f)));
+    const double iM = rcp(im.M);
+    const float a = static_cast<float>(im.a * iM), si = __sinf(static_cast<float>(im.incl));
+    const float iE = __frcp_rn(static_cast<float>(im.E0 + x * im.cE)), l = static_cast<float>(x * im.cL * iM) * iE;
+    const float pth = static_cast<float>(y * im.cth * iM) * iE, t = __fdividef(l, si) - a * si;
+    const float third = acosf(fminf(fabsf(a), 1.0f)) * (2.0f / 3.0f);
+    const float r_pro = 2.0f * (1.0f + __cosf(2.0943951f - third)), r_ret = 2.0f * (1.0f + __cosf(third));
+    const float b = a * (a + l), c = a * (a - l);
+    float r = 0.5f * (3.0f + sqrtf(fmaxf(9.0f - 4.0f * b, 0.0f)));
     for (int k = 0; k < 4; ++k) {
-        const float f = ((r - 3.0f * M) * r + b) * r + c, df = (3.0f * r - 6.0f * M) * r + b;
+        const float f = ((r - 3.0f) * r + b) * r + c, df = (3.0f * r - 6.0f) * r + b;
         r = fminf(fmaxf(r - __fdividef(f, df), r_pro), r_ret);
     }
-    const float q = __fdividef(1.0f, fmaxf(r - M, 1e-4f * M));
-    const float crit = 2.0f * r * sqrtf(fmaxf(1.0f - (M - a) * (M + a) * q * q, 0.0f));
+    const float q = __fdividef(1.0f, fmaxf(r - 1.0f, 1e-4f));
+    const float crit = 2.0f * r * sqrtf(fmaxf(1.0f - (1.0f - a) * (1.0f + a) * q * q, 0.0f));
     return fabsf(sqrtf(pth * pth + t * t) - crit);
 }
 
@@ -1267,7 +1270,7 @@ struct RingKey {
         const double y = -im->fov_y + (static_cast<double>(j) + 0.5) * im->dy;
         double d = fabs(sqrt(fma(x, x, y * y)) - im->rho_ring);
         if (im->metric == KT_METRIC_KERR && im->a != 0.0 && im->rho_ring > 0.0) {
-            const double kerr = critical_distance(*im, x, y) * (im->rho_ring / (5.196152422706632 * im->M));
+            const double kerr = critical_distance(*im, x, y) * (im->rho_ring / 5.196152422706632);
             if (kerr >= 0.0) d = kerr;  // NaN for an observer on the axis
         }
         d *= im->order_scale;
