@@ -367,7 +367,7 @@ def run_adjoint_form(K, torch, W, steps, default_only=False):
     def variant(**kw):
         """A kt_adjoint call with these integrator fields, on a workspace of its own."""
         integ = K.make_structs(**dict(params, **kw))[4]
-        nb = K.kt_adjoint_workspace_bytes(r.cam, integ)
+        nb = K.adjoint_room(r.cam, integ)
         ws = torch.empty(nb, dtype=torch.uint8, device="cuda:0")
 
         def call(sorted_list=True):

@@ -348,8 +348,8 @@ int kt_autotune_batch(int32_t n_images, const kt_image *images, const kt_integra
    n_steps array (optional: the differentiated rays are run longest first,
    their forward passes are stored and long rays can be split, below).  Each ray
    is re-integrated with the forward's own arithmetic.  With n_steps and
-   integ->split_above >= 0 every accepted step goes to a store of 256 steps per
-   pixel (at least; 8 GiB at most, 524288 rays) and the backward sweep reads it;
+   integ->split_above >= 0 every accepted step goes to a store and the backward
+   sweep reads it, the longest rays first as far as the room and 524288 records go;
    the rays that this has no room for, those that take more steps than n_steps
    says, and all rays otherwise, are checkpointed every integ->checkpoint_every
    accepted steps (64 when 0) and swept segment by segment, each segment
@@ -360,19 +360,22 @@ int kt_autotune_batch(int32_t n_images, const kt_image *images, const kt_integra
    p_theta) (that of phi stays zero: the field does not depend on phi); the
    segments' maps are then applied in order to the ray's cotangent.  Split are
    stored rays of more than split_above accepted steps, whole step-count bins of 4
-   steps at a time; with split_above 0 the longest until the longest sweep left is
-   no longer than a lane's share of the work, at least 64 steps.  This cuts the
-   sequential length of the longest rays, which otherwise set the adjoint's run
-   time.  Stored and split rays' gradients equal the others' up to rounding (the
-   same products, fused or associated differently); they do not depend on
-   checkpoint_every.
+   steps at a time, the longest first as far as the room for segments goes (1.2M
+   column sweeps at 512x512, four per segment); with split_above 0 the longest until
+   the longest sweep left is no longer than a lane's share of the work, at least 64
+   steps.  This cuts the sequential length of the longest rays, which otherwise set
+   the adjoint's run time.  Stored and split rays' gradients equal the others' up to
+   rounding (the same products, fused or associated differently); they do not depend
+   on checkpoint_every.
    stats (device, 4 uint64, may be NULL): rays differentiated, rays that
    failed, rays beyond the checkpoint capacity (max(256, 2048 /
    checkpoint_every) checkpoints, i.e. at least 2048 accepted steps and
    256 * checkpoint_every from 8 on), rays whose re-integration did not
    reproduce r_hit; the last three get zero gradient and drop out of
    grad_sum, so a caller that needs the whole gradient checks them.
-   workspace: kt_adjoint_workspace_bytes() bytes, 256-byte aligned.
+   workspace: kt_adjoint_workspace_bytes() bytes or more, 256-byte aligned.  The
+   store takes what there is beyond them (KT_ADJOINT_ROOM_PER_PIXEL below); rays
+   that it does not hold take longer.
    Returns KT_OK, KT_EINVAL, KT_ENOMEM or KT_EDEVICE. */
 int kt_adjoint(const kt_camera *camera, const kt_spacetime *spacetime, const kt_disk *disk,
                const kt_integrator *integ, const uint8_t *fate, const double *r_hit,
@@ -382,6 +385,13 @@ int kt_adjoint(const kt_camera *camera, const kt_spacetime *spacetime, const kt_
 
 /* Workspace size of kt_adjoint for this camera and integrator (0 on bad input). */
 size_t kt_adjoint_workspace_bytes(const kt_camera *camera, const kt_integrator *integ);
+
+/* A workspace of this many bytes per pixel, up to the second number, holds every
+   accepted step of a disk image's differentiated rays (256 steps of 40 bytes per
+   pixel; a 512x512 image takes 136, the least workspace there holds 96).  With
+   split_above -1 no steps are stored and the least size is all that is used. */
+#define KT_ADJOINT_ROOM_PER_PIXEL 10240
+#define KT_ADJOINT_ROOM_MAX ((size_t)8 << 30)
 
 /* Initial state of every pixel (Sect. 2.3), for checking the camera alone:
    state is a device array of 7*nx*ny doubles laid out SoA as

@@ -43,7 +43,7 @@ class DiskImage(torch.autograd.Function):
             g_int.to(dtype=torch.float64).contiguous()
         grad_sum = torch.empty(3, dtype=torch.float64, device=dev)
         stats = torch.zeros(4, dtype=torch.int64, device=dev)
-        nbytes = K.kt_adjoint_workspace_bytes(r.cam, r.integ)
+        nbytes = K.adjoint_room(r.cam, r.integ)
         ws = torch.empty(nbytes, dtype=torch.uint8, device=dev)
         stream = torch.cuda.current_stream(dev)
         rc = K.kt_adjoint(r.cam, r.st, r.disk, r.integ, r.out["fate"].data_ptr(), r.out["r_hit"].data_ptr(),
@@ -84,7 +84,7 @@ def adjoint_maps(device="cuda:0", cot=None, **params):
     grads = [torch.empty(n, dtype=torch.float64, device=dev) for _ in range(3)]
     grad_sum = torch.empty(3, dtype=torch.float64, device=dev)
     stats = torch.zeros(4, dtype=torch.int64, device=dev)
-    nbytes = K.kt_adjoint_workspace_bytes(r.cam, r.integ)
+    nbytes = K.adjoint_room(r.cam, r.integ)
     ws = torch.empty(nbytes, dtype=torch.uint8, device=dev)
     stream = torch.cuda.current_stream(dev)
     rc = K.kt_adjoint(r.cam, r.st, r.disk, r.integ, out["fate"].data_ptr(), out["r_hit"].data_ptr(),

@@ -349,7 +349,14 @@ __device__ __forceinline__ unsigned long long block_scan(unsigned long long v, u
 // records hold them for certain (a ray of bin v takes at most 4 v + 5
 // entries).  Bin 0, which has no such bound, and bins of more steps than the
 // one-lane path's checkpoints cover are left to that path, which counts such
-// rays as it does without step counts.
+// rays as it does without step counts.  A store that holds less than one in
+// ADJ_STORE_SHARE of the listed steps is left empty: the one-lane path then has most
+// of the work to do after it, and with so many lanes' work gains nothing from having
+// the longest rays done.  ms of the adjoint with and without stored passes, by the
+// share that the store held: 600x600 at 45 degrees (0.51) 6.35 and 11.0, 1400x1400
+// (0.70) 26.2 and 28.0, 700x700 (0.37) 9.0 and 12.9, 2048x2048 (0.36) 57.5 and 57.9,
+// 850x850 (0.25) 14.2 and 12.1, 1024x1024 (0.17) 18.9 and 15.5, 1400x1400 (0.09) 31.6
+// and 28.0; at 20 degrees 600x600 (0.37) 8.46 and 8.21, 850x850 (0.19) 17.1 and 14.9.
 // A split sweep takes four step VJPs per step instead of one, in pieces of
 // ADJ_SEG steps instead of the ray's length.  The longest bins are split until
 // the longest sweep left is no longer than the sweep kernel's work per lane,
@@ -362,6 +369,7 @@ __device__ __forceinline__ unsigned long long block_scan(unsigned long long v, u
 // degrees (0.32) 8.4 and 7.0, 560x560 at 60 degrees 9.3 and 8.2; where lanes
 // have more to do the sweeps are better dealt out once, in order of length:
 // 480x480 at 30 degrees 6.3 and 7.6, 640x640 at 30 degrees 11.7 and 12.9.
+constexpr unsigned long long ADJ_STORE_SHARE = 3;
 __global__ void __launch_bounds__(SORT_BLOCK) adjoint_split_kernel(const AdjParams P) {
     constexpr int PER = SORT_BINS / SORT_BLOCK;  // consecutive bins per thread
     static_assert(SORT_BINS % SORT_BLOCK == 0, "bins must split evenly over the block");
@@ -391,6 +399,13 @@ __global__ void __launch_bounds__(SORT_BLOCK) adjoint_split_kernel(const AdjPara
         }
     }
     __syncthreads();
+    unsigned long long listed = 0;
+    for (int i = 0; i < PER; ++i) {
+        const int k = t * PER + i;
+        listed += static_cast<unsigned long long>(P.hist[k] - (k > 0 ? P.hist[k - 1] : 0u)) *
+                  static_cast<unsigned long long>(4 * (SORT_BINS - 1 - k) + 2);
+    }
+    listed = block_scan(listed, part);
     // steps and segment items of the stored bins, and the bins to split
     unsigned long long steps = 0, items = 0;
     for (int i = 0; i < PER; ++i) {
@@ -401,7 +416,10 @@ __global__ void __launch_bounds__(SORT_BLOCK) adjoint_split_kernel(const AdjPara
         if (cnt[i] != 0u) atomicMin(&longest_bin, k);
     }
     unsigned long long run_steps = block_scan(steps, part);
-    if (t == SORT_BLOCK - 1) all_steps = run_steps;
+    if (t == SORT_BLOCK - 1) {
+        all_steps = run_steps;
+        if (ADJ_STORE_SHARE * run_steps < listed) stop_store = skip + 1;
+    }
     run_steps -= steps;
     unsigned long long run_items = block_scan(items, part) - items;
     for (int i = 0; i < PER; ++i) {

@@ -699,10 +699,10 @@ int kt_adjoint(const kt_camera* camera, const kt_spacetime* spacetime, const kt_
     // stored forward passes need the forward step counts
     p.split_above = integ->split_above;
     p.max_long = n_steps && integ->split_above >= 0 ? w.max_long : 0;
-    p.long_cap = w.long_cap;
+    p.long_cap = integ->split_above >= 0 ? kt::adj_store_cap(w, workspace_bytes) : 0u;
     p.item_cap = w.item_cap;
     p.counters = reinterpret_cast<uint32_t*>(ws + kt::ADJ_WS_COUNTERS);
-    p.long_store = reinterpret_cast<double*>(ws + w.long_store);
+    p.long_store = reinterpret_cast<double*>(ws + w.ckpt);
     p.longs = reinterpret_cast<kt::AdjLong*>(ws + w.longs);
     p.owner = reinterpret_cast<uint32_t*>(ws + w.owner);
     p.items = reinterpret_cast<double*>(ws + w.items);

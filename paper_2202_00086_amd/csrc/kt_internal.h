@@ -247,14 +247,24 @@ constexpr int ADJ_CK_SHIFT_DEFAULT = 6;      // checkpoints every 64 accepted st
 // sweep then reads each step instead of recomputing it
 constexpr int ADJ_CK_SHIFT_MIN = 0, ADJ_CK_SHIFT_MAX = 10;
 constexpr int ADJ_RED_BLOCKS = 256;      // fixed grid of the gradient reduction (deterministic)
-// Stored forward passes: ADJ_ENTRY doubles per accepted step, room for
-// ADJ_STEPS_PER_PIXEL of them per pixel of the image up to ADJ_STORE_MAX_BYTES
-// (a 512x512 disk image of 117k hits takes 135 per pixel; 2.7 GB), at most
-// ADJ_MAX_RECORDS rays, sweeps split into segments of ADJ_SEG entries.
+// Stored forward passes: ADJ_ENTRY doubles per accepted step (a 512x512 disk image
+// of 117k hits takes 136 steps per pixel, 1.4 GB), at most ADJ_STORE_MAX_BYTES
+// unless the one-lane path's part of the workspace is larger and ADJ_MAX_RECORDS
+// rays, sweeps split into segments of ADJ_SEG entries.
 constexpr int ADJ_SEG = 64, ADJ_ENTRY = 5;
-constexpr int ADJ_STEPS_PER_PIXEL = 256;
-constexpr size_t ADJ_STORE_MAX_BYTES = size_t{8} << 30;
+constexpr size_t ADJ_STORE_MAX_BYTES = KT_ADJOINT_ROOM_MAX;
 constexpr size_t ADJ_MAX_RECORDS = 524288;
+// Room for the records and the segment items, part of the size that callers'
+// buffers have: ADJ_SPLIT_LANE_BYTES per lane and ADJ_SPLIT_RAY_BYTES per ray, of
+// ADJ_SPLIT_RAYS at most.  The records come first, 112 bytes per ray; what they
+// leave holds items of ADJ_ITEM_BYTES, four per segment: 1.2M at 512x512, where the
+// automatic threshold uses 85 thousand.  A caller's threshold that asks for more
+// than there are splits the longest rays only (adjoint_split_kernel).
+constexpr size_t ADJ_SPLIT_LANE_BYTES = 1672, ADJ_SPLIT_RAY_BYTES = 384, ADJ_SPLIT_RAYS = 8192;
+constexpr size_t ADJ_ITEM_BYTES = 8 * sizeof(double) + sizeof(uint32_t);
+static_assert(ADJ_MAX_RECORDS * sizeof(AdjLong) <= ADJ_SPLIT_LANE_BYTES * static_cast<size_t>(ADJ_MAX_LANES) &&
+                  sizeof(AdjLong) <= ADJ_SPLIT_LANE_BYTES,
+              "the records must leave room for items");
 
 // log2 of kt_integrator.checkpoint_every (0 selects 64); -1 unless a power
 // of two in [1, 1024].
@@ -266,15 +276,18 @@ inline int adj_ck_shift(int32_t every) {
 }
 
 struct AdjLayout {
-    size_t stats, hist, partials, params, ckpt, seg, keys, list, grad, longs, owner, items, long_store, total;
+    size_t stats, hist, partials, params, keys, list, grad, longs, owner, items, ckpt, seg, total;
     int32_t n_lanes, max_ckpt, max_long;
-    uint32_t long_cap, item_cap;
+    uint32_t item_cap;
 };
 
 // Byte offsets in the first 256 bytes of the adjoint's workspace.
 constexpr size_t ADJ_WS_TICKET = 0, ADJ_WS_COUNTERS = 16;
 
-// split: room for split backward sweeps (kt_integrator.split_above >= 0).
+// split: room for split backward sweeps (kt_integrator.split_above >= 0).  `total`
+// is the least workspace.  The checkpoints and segment slots of the one-lane path
+// come last; the stored forward passes, done with before that path starts, share
+// their memory and take what a larger workspace has behind it (adj_store_cap).
 inline AdjLayout adj_layout(size_t n_rays, int64_t max_steps, int ck_shift, bool split) {
     AdjLayout w;
     size_t lanes = (n_rays + 255) / 256 * 256;
@@ -290,30 +303,29 @@ inline AdjLayout adj_layout(size_t n_rays, int64_t max_steps, int ck_shift, bool
     w.hist = 256;
     w.partials = align256(w.hist + 4u * (SORT_BINS + 1));
     w.params = align256(w.partials + 3u * ADJ_RED_BLOCKS * sizeof(double));
-    // the checkpoints and segment slots of the one-lane path; the stored
-    // forward passes, done with before that path starts, share their memory
-    w.ckpt = align256(w.params + WS_PARAMS_MAX);
-    w.seg = align256(w.ckpt + static_cast<size_t>(ck) * 6u * lanes * sizeof(double));
-    size_t end = w.seg + (size_t{1} << ck_shift) * 6u * lanes * sizeof(double);
-    size_t store = n_rays * ADJ_STEPS_PER_PIXEL * ADJ_ENTRY * sizeof(double);
-    if (store > ADJ_STORE_MAX_BYTES) store = ADJ_STORE_MAX_BYTES;
-    if (end < w.ckpt + store) end = w.ckpt + store;
-    w.keys = align256(end);
+    w.keys = align256(w.params + WS_PARAMS_MAX);
     w.list = align256(w.keys + 2u * n_rays);
     w.grad = align256(w.list + 4u * n_rays);
-    w.long_store = w.ckpt;
-    w.long_cap = split ? static_cast<uint32_t>((end - w.ckpt) / (6u * sizeof(double))) : 0u;
-    w.max_long = split ? static_cast<int32_t>(n_rays < ADJ_MAX_RECORDS ? n_rays : ADJ_MAX_RECORDS) : 0;
-    // records, and in the rest of this room (68 bytes each) segment items
-    const size_t few = n_rays < size_t{8192} ? n_rays : size_t{8192};
-    const size_t room = split ? lanes * 1672u + few * 384u : 0u;
     w.longs = align256(w.grad + 3u * sizeof(double) * n_rays);
+    w.max_long = split ? static_cast<int32_t>(n_rays < ADJ_MAX_RECORDS ? n_rays : ADJ_MAX_RECORDS) : 0;
     const size_t recs = static_cast<size_t>(w.max_long) * sizeof(AdjLong);
-    w.item_cap = split ? static_cast<uint32_t>((room - recs + 271u) / 272u * 4u) : 0u;
+    const size_t few = n_rays < ADJ_SPLIT_RAYS ? n_rays : ADJ_SPLIT_RAYS;
+    const size_t room = lanes * ADJ_SPLIT_LANE_BYTES + few * ADJ_SPLIT_RAY_BYTES;
+    const size_t seg_items = 4u * ADJ_ITEM_BYTES;  // those of one segment, rounded up
+    w.item_cap = split ? static_cast<uint32_t>((room - recs + seg_items - 1u) / seg_items * 4u) : 0u;
     w.owner = align256(w.longs + recs);
-    w.items = align256(w.owner + 4u * static_cast<size_t>(w.item_cap));
-    w.total = align256(w.items + 8u * sizeof(double) * w.item_cap);
+    w.items = align256(w.owner + sizeof(uint32_t) * w.item_cap);
+    w.ckpt = align256(w.items + 8u * sizeof(double) * w.item_cap);
+    w.seg = align256(w.ckpt + static_cast<size_t>(ck) * 6u * lanes * sizeof(double));
+    w.total = align256(w.seg + (size_t{1} << ck_shift) * 6u * lanes * sizeof(double));
     return w;
+}
+
+// The store's size in a workspace of so many bytes, in 6 doubles.
+inline uint32_t adj_store_cap(const AdjLayout& w, size_t workspace_bytes) {
+    const size_t least = w.total - w.ckpt, most = least > ADJ_STORE_MAX_BYTES ? least : ADJ_STORE_MAX_BYTES;
+    const size_t room = workspace_bytes - w.ckpt;
+    return static_cast<uint32_t>((room < most ? room : most) / (6u * sizeof(double)));
 }
 
 // Leave msg for kt_last_error() on this host thread and return code (kt_api.cpp).

@@ -199,6 +199,19 @@ def kt_adjoint_workspace_bytes(camera, integ):
     return _lib.kt_adjoint_workspace_bytes(C.byref(camera), C.byref(integ))
 
 
+ADJOINT_ROOM_PER_PIXEL, ADJOINT_ROOM_MAX = 10240, 8 << 30  # KT_ADJOINT_ROOM_*
+
+
+def adjoint_room(camera, integ):
+    """The workspace size with which kt_adjoint, given n_steps, stores every
+    differentiated ray's forward pass; the least size where no pass is stored
+    (split_above -1) or that is larger; 0 on bad input."""
+    least = kt_adjoint_workspace_bytes(camera, integ)
+    if least == 0 or integ.split_above < 0:
+        return least
+    return max(least, min(ADJOINT_ROOM_PER_PIXEL * camera.nx * camera.ny, ADJOINT_ROOM_MAX))
+
+
 def kt_adjoint(camera, spacetime, disk, integ, fate_ptr, r_hit_ptr, cot_ptr, grad_a_ptr, grad_incl_ptr,
                grad_rin_ptr, stats_ptr, workspace_ptr, workspace_bytes, stream_ptr, n_steps_ptr=None,
                grad_sum_ptr=None):
