@@ -353,10 +353,10 @@ __device__ __forceinline__ unsigned long long block_scan(unsigned long long v, u
 // ADJ_STORE_SHARE of the listed steps is left empty: the one-lane path then has most
 // of the work to do after it, and with so many lanes' work gains nothing from having
 // the longest rays done.  ms of the adjoint with and without stored passes, by the
-// share that the store held: 600x600 at 45 degrees (0.51) 6.35 and 11.0, 1400x1400
-// (0.70) 26.2 and 28.0, 700x700 (0.37) 9.0 and 12.9, 2048x2048 (0.36) 57.5 and 57.9,
-// 850x850 (0.25) 14.2 and 12.1, 1024x1024 (0.17) 18.9 and 15.5, 1400x1400 (0.09) 31.6
-// and 28.0; at 20 degrees 600x600 (0.37) 8.46 and 8.21, 850x850 (0.19) 17.1 and 14.9.
+// share that the store held: 1400x1400 at 45 degrees (0.70) 23.9 and 28.0, 600x600
+// (0.51) 6.4 and 10.9, 700x700 (0.37) 9.0 and 13.0, 2048x2048 (0.36) 53.5 and 57.9,
+// 850x850 (0.25) 12.0 and 11.5, 1400x1400 (0.09) 29.9 and 28.1, 2048x2048 (0.04) 60.8
+// and 58.0; at 20 degrees 600x600 (0.37) 8.3 and 8.1, 850x850 (0.19) 14.9 and 14.8.
 // A split sweep takes four step VJPs per step instead of one, in pieces of
 // ADJ_SEG steps instead of the ray's length.  The longest bins are split until
 // the longest sweep left is no longer than the sweep kernel's work per lane,

@@ -145,12 +145,6 @@ Shape launch_shape(const kt::Params& p, const kt_launch& ln, int64_t n_rays, int
     return s;
 }
 
-// Waves per SIMD of the adjoint's stored passes.
-int adjoint_waves(int64_t n_rays) {
-    const int64_t lanes = static_cast<int64_t>(device_cus()) * 4 * 64;
-    return n_rays <= 8 * lanes ? 1 : 2;
-}
-
 double horizon(const kt_spacetime* st) {
     if (st->metric == KT_METRIC_Q) return 2.0 * st->M;
     return st->M + std::sqrt(st->M * st->M - st->a * st->a);
@@ -707,10 +701,15 @@ int kt_adjoint(const kt_camera* camera, const kt_spacetime* spacetime, const kt_
     p.owner = reinterpret_cast<uint32_t*>(ws + w.owner);
     p.items = reinterpret_cast<double*>(ws + w.items);
     p.params = reinterpret_cast<kt::Params*>(ws + w.params);
-    // waves per SIMD of the forward pass and of the sweep: see adjoint_waves
-    const int waves = adjoint_waves(static_cast<int64_t>(n));
-    p.trace_blocks = device_cus() * waves;
-    p.grid_lanes = device_cus() * waves * 256;
+    // One wave per SIMD for the stored passes: their end is a chain of steps of the
+    // longest rays, which a second wave slows, and a lane that has twice the rays
+    // leaves fewer sweeps to split (four step VJPs for one).  ms of the adjoint at 1
+    // and 2 waves, disks at 20, 45 and 70 degrees:
+    //   512x512    3.84/5.05  3.03/4.35  2.99/4.01    700x700    7.04/7.40  6.63/6.15  3.19/4.58
+    //   850x850    10.6/10.8  7.97/8.70  4.60/5.73    1024x1024  16.8/16.9  11.0/11.7  6.63/7.27
+    //   1400x1400  32.5/33.4  23.2/25.7  11.3/11.8    2048x2048  76.8/76.7  52.9/54.8  28.2/32.7
+    p.trace_blocks = device_cus();
+    p.grid_lanes = device_cus() * 256;
     if (kt::launch_adjoint(p, hip_stream))
         return fail(KT_EDEVICE, "adjoint launch failed: %s", hipGetErrorString(hipGetLastError()));
     return KT_OK;
