@@ -350,7 +350,7 @@ __device__ __forceinline__ unsigned long long block_scan(unsigned long long v, u
 // entries).  Bin 0, which has no such bound, and bins of more steps than the
 // one-lane path's checkpoints cover are left to that path, which counts such
 // rays as it does without step counts.  A store that holds less than one in
-// ADJ_STORE_SHARE of the listed steps is left empty: the one-lane path then has most
+// ADJ_STORE_SHARE of those bins' steps is left empty: the one-lane path then has most
 // of the work to do after it, and with so many lanes' work gains nothing from having
 // the longest rays done.  ms of the adjoint with and without stored passes, by the
 // share that the store held: 1400x1400 at 45 degrees (0.70) 23.9 and 28.0, 600x600
@@ -399,11 +399,10 @@ __global__ void __launch_bounds__(SORT_BLOCK) adjoint_split_kernel(const AdjPara
         }
     }
     __syncthreads();
-    unsigned long long listed = 0;
+    unsigned long long listed = 0;  // steps of the bins that can be stored
     for (int i = 0; i < PER; ++i) {
         const int k = t * PER + i;
-        listed += static_cast<unsigned long long>(P.hist[k] - (k > 0 ? P.hist[k - 1] : 0u)) *
-                  static_cast<unsigned long long>(4 * (SORT_BINS - 1 - k) + 2);
+        listed += static_cast<unsigned long long>(cnt[i]) * static_cast<unsigned long long>(4 * (SORT_BINS - 1 - k) + 2);
     }
     listed = block_scan(listed, part);
     // steps and segment items of the stored bins, and the bins to split

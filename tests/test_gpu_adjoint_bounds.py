@@ -72,3 +72,77 @@ def test_budget_smaller_than_the_renders(K, max_steps, every):
     for a, b in zip(got, want):
         if want_st[0] > 0:
             _assert_split_close(a, b)
+
+
+def _compare(K, r, out, params, n_steps, more, split_above):
+    """The stored passes' counters, after comparing them with the one-lane path."""
+    want, want_st, _ = _adjoint(K, r, out, K.make_structs(**dict(params, split_above=-1))[4], out["n_steps"])
+    got, st, c = _adjoint(K, r, out, K.make_structs(**dict(params, split_above=split_above))[4], n_steps, more)
+    assert st.tolist() == want_st.tolist() and want_st[1:].tolist() == [0, 0, 0]
+    for a, b in zip(got, want):
+        _assert_split_close(a, b)
+    listed, split, stored = int(want_st[0]), int(c[0]), int(c[4]) - int(c[3])
+    print(f"[adjoint] listed {listed} stored {stored} split {split} store {c[1]} items {c[2]} redone {c[7]}", flush=True)
+    return listed, stored, split, int(c[3])
+
+
+@pytest.mark.parametrize("split_above", [0, 1, 400, 1 << 20])
+@pytest.mark.parametrize("inflate", [1500, 2500, 3700])
+def test_store_that_holds_some_of_the_rays(K, inflate, split_above):
+    """Step counts of every second ray so much too large that the store is full
+    before the shorter bins: those take the one-lane path, in the memory that the
+    store had."""
+    import torch
+    params = W.differentiable_disk(n=33)
+    _announce("adjoint part of the rays stored", inflate, split_above)
+    r, out = _forward(K, params)
+    n = out["n_steps"]
+    steps = torch.where(torch.arange(r.n, device=n.device) % 2 == 0, n + inflate, n).contiguous()
+    listed, stored, _, _ = _compare(K, r, out, params, steps, 0, split_above)
+    assert 0 < stored < listed
+
+
+def test_store_that_holds_too_few_of_the_rays_is_left_empty(K):
+    """Every ray's count at the store's bin limit: it would hold a quarter of them."""
+    import torch
+    params = W.differentiable_disk(n=33)
+    _announce("adjoint store left empty")
+    r, out = _forward(K, params)
+    listed, stored, split, _ = _compare(K, r, out, params, torch.full_like(out["n_steps"], 4080), 0, 0)
+    assert stored == split == 0
+
+
+@pytest.mark.parametrize("every", [1, 64, 1024])
+def test_longest_rays_ahead_of_the_stored_ones(K, every):
+    """Counts beyond the bins' range (4092 steps) for every third ray: those take the
+    one-lane path and the stored rays start behind them in the list."""
+    import torch
+    params = dict(W.differentiable_disk(n=33), checkpoint_every=every)
+    _announce("adjoint long rays ahead", every)
+    r, out = _forward(K, params)
+    n = out["n_steps"]
+    steps = torch.where(torch.arange(r.n, device=n.device) % 3 == 0, torch.full_like(n, 5000), n).contiguous()
+    listed, stored, _, first = _compare(K, r, out, params, steps, 64 << 20, 0)
+    assert first > 0 and first + stored == listed
+
+
+def test_items_for_some_of_the_splits(K):
+    """A threshold that asks for more segments than there is room for: the longest
+    rays are split, the others swept whole (the longest ray's count is beyond the bins)."""
+    import torch
+    params = W.differentiable_disk(n=33)
+    _announce("adjoint segment items")
+    r, out = _forward(K, params)
+    listed, stored, split, _ = _compare(K, r, out, params, out["n_steps"] + 3500, 128 << 20, 1)
+    assert 0 < split < stored == listed - 1
+
+
+def test_more_rays_than_records(K):
+    """1024x1024 at 20 degrees: 600 thousand rays, of which 524288 have a record,
+    with a workspace that holds every pass."""
+    params = dict(W.differentiable_disk(n=1024, incl_deg=20.0))
+    _announce("adjoint more rays than records")
+    r, out = _forward(K, params)
+    least = K.kt_adjoint_workspace_bytes(r.cam, r.integ)
+    listed, stored, _, _ = _compare(K, r, out, params, out["n_steps"], K.adjoint_room(r.cam, r.integ) - least, 0)
+    assert listed > 524288 >= stored > 400000
