@@ -466,7 +466,8 @@ trace_kernel(const Hot hp) {
     constexpr bool S_TIME = (METHOD == KT_RK4_S);
     constexpr bool MIXED = (PREC == KT_MIXED) && (METHOD == KT_DP45) && !QMET;
     constexpr bool LONG_STEPS = METHOD == KT_BS || METHOD == KT_BS_RAT;
-    constexpr bool PIN_SHIFT = !LONG_STEPS && METHOD != KT_RK4_S, PIN_THETA = LONG_STEPS && !QMET && KT_WAVES_PER_EU < 3;
+    constexpr bool PIN_SHIFT = !LONG_STEPS && METHOD != KT_RK4_S;
+    constexpr bool PIN_THETA = METHOD == KT_BS && !QMET && !BATCH && KT_WAVES_PER_EU < 3;
     constexpr int PIN_COEFS =
         KT_WAVES_PER_EU < 3 && METHOD == KT_DP45 && !QMET && !MIXED && FEAT >= 0 ? ((FEAT & FEAT_SRC) ? 8 : 20) : 0;
     constexpr bool MAY_DISK = FEAT < 0 ? !QMET : (FEAT & FEAT_DISK) != 0;
@@ -520,10 +521,15 @@ trace_kernel(const Hot hp) {
     // waits for each scalar move that sets one up, ~40 in 626 instructions of an
     // attempt: 96x96 ring 2.71 -> 2.64 ms, 512x512 lensing 3.24 -> 3.06; with three
     // waves per SIMD others fill in); those of the shift from the base point,
-    // which every Runge-Kutta stage needs; of sin/cos of theta itself, which
-    // each Bulirsch-Stoer substep needs, only where the registers reach (2
-    // waves: norm check of 625x625 rays 3.64 ms without, 3.51 with; 3 waves:
-    // 1200x1000 rays 15.1 without, 15.9 with).
+    // which every Runge-Kutta stage needs; of sin/cos of theta itself, which each
+    // Bulirsch-Stoer substep needs, only for single Kerr images by polynomials in
+    // the 2-wave build.  There the loop keeps them although the kernel then has
+    // 116 bytes of scratch per lane (20 without them), none of it touched inside
+    // the step loop: norm check of 625x625 rays 3.30 ms, 3.42 without, with half
+    // of them 3.36; 512x512 ring 3.38 and 3.49, 768x768 7.12 and 7.34.  By rational
+    // functions the times are equal (512x512 4.62 and 4.60) and scratch is 28 bytes
+    // instead of 124; a batch of 3.6M rays takes 26.4 ms without them, 26.9 with,
+    // by rational functions 35.9 and 36.5; with 3 waves 1200x1000 rays 15.1 and 15.9.
     const Elem<PIN_SHIFT, PIN_THETA, PIN_COEFS> el;
     int32_t ray = -1;
     int fl = 0;
