@@ -167,7 +167,6 @@ struct Diag {
     double Kabs;    // |2 Sigma H| (|2H| for the q-metric)
     double D;       // the sum of the magnitudes of its terms: |H|_rel = Kabs / D
     double s, c;    // sin, cos of theta
-    __device__ double rel() const { return Kabs * rcp(D); }
 };
 
 // ---------------------------------------------------------------------------

@@ -1,7 +1,6 @@
 // kt_dual.h -- forward-mode dual numbers for the adjoint: a value and N
 // directional derivatives, carried through + - * / sqrt sin cos.  Used on the
-// device for Hessian-vector products of the Hamiltonian and for the
-// derivatives of the disk observables, and on the host for the derivatives
+// device for the derivatives of the disk observables and on the host for those
 // of the camera constants.
 #pragma once
 
@@ -28,12 +27,6 @@ struct Dual {
     __host__ __device__ static Dual var(double x, int k) {
         Dual r(x);
         r.d[k] = 1.0;
-        return r;
-    }
-    // a value with the given tangent along every direction
-    __host__ __device__ static Dual with(double x, const double* t) {
-        Dual r(x);
-        for (int i = 0; i < N; ++i) r.d[i] = t[i];
         return r;
     }
 };
@@ -91,13 +84,6 @@ __host__ __device__ inline Dual<N> operator/(const Dual<N>& a, double b) { retur
 template <int N>
 __host__ __device__ inline Dual<N> operator/(double a, const Dual<N>& b) { return Dual<N>(a) / b; }
 
-// 1/x for plain and dual numbers
-__host__ __device__ inline double recip(double x) { return rcp(x); }
-template <int N>
-__host__ __device__ inline Dual<N> recip(const Dual<N>& x) {
-    return 1.0 / x;
-}
-
 template <int N>
 __host__ __device__ inline Dual<N> dsqrt(const Dual<N>& a) {
     const double s = sqrt(a.v);
@@ -115,13 +101,6 @@ __host__ __device__ inline void dsincos(const Dual<N>& a, Dual<N>* s, Dual<N>* c
         s->d[i] = cv * a.d[i];
         c->d[i] = -sv * a.d[i];
     }
-}
-
-// plain doubles through the same interface
-__host__ __device__ inline double dsqrt(double a) { return sqrt(a); }
-__host__ __device__ inline void dsincos(double a, double* s, double* c) {
-    *s = sin(a);
-    *c = cos(a);
 }
 
 }  // namespace kt
