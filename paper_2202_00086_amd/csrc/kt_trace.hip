@@ -252,12 +252,15 @@ struct Vec5 {
 constexpr int FATE_NO_ROOM = 8;
 constexpr uint32_t NO_RECORD = 0xffffffffu;
 
-// The running maxima of |2H| and of |H|_rel = Kabs / D, the latter as its
-// two parts (ratios compared by cross products): no quotient per step.
+// The running maxima of |2H| and of |H|_rel = Kabs / D, the latter as its two
+// parts (ratios compared by cross products): no quotient per step.  Inside the
+// horizon, where a ray of a fixed step or without a capture buffer gets to, D may
+// be negative; rel_k carries the ratio's sign, so that the cross products compare
+// the ratios themselves there too.
 __device__ __forceinline__ void keep_max(const Diag& dg, double* max_h2, double* rel_k, double* rel_d) {
     *max_h2 = max_abs(dg.H2, *max_h2);
-    if (dg.Kabs * *rel_d > *rel_k * dg.D) {
-        *rel_k = dg.Kabs;
+    if (dg.Kabs * fabs(*rel_d) > *rel_k * dg.D) {
+        *rel_k = __builtin_copysign(dg.Kabs, dg.D);
         *rel_d = dg.D;
     }
 }
@@ -634,7 +637,7 @@ trace_kernel(const Hot hp) {
         o.fate[ray] = static_cast<uint8_t>(fate);
         P.rc_buf[ray] = r_c;
         if (o.max_abs_h) o.max_abs_h[ray] = 0.5 * max_h2;
-        const double max_rel = rel_k * rcp(rel_d);
+        const double max_rel = rel_k * rcp(fabs(rel_d));
         if (o.max_rel_h) o.max_rel_h[ray] = max_rel;
         if (o.psi) o.psi[ray] = psi;
         if (o.deflection) o.deflection[ray] = defl;
@@ -731,7 +734,7 @@ trace_kernel(const Hot hp) {
                     ys = Vec5::of(y);
                     ks = Vec5::of(k1);
                     max_h2 = fabs(dg.H2);
-                    rel_k = dg.Kabs;
+                    rel_k = __builtin_copysign(dg.Kabs, dg.D);
                     rel_d = dg.D;
                     s0 = dg.s;
                     c0 = dg.c;
