@@ -15,13 +15,13 @@
 // With the forward step counts step 1 is the trace kernel itself (its STORE
 // form) with every accepted step written to a store, and step 3 reads the steps
 // back, one item per lane, partly by waves of the forward pass that have no ray
-// left (see sweep in kt_trace.hip).  A long ray's sweep is split: each 64-step segment is swept backward
-// from four basis cotangents (its transposed Jacobian, a linear map since the
-// steps are frozen), one lane each, and the last kernel applies the segments'
-// maps to the ray's seeded cotangent in order.  A sweep is otherwise one
-// lane's sequential work, and the longest would set the run time.
-// Rays beyond the store, and all of them without step counts or with split
-// sweeps off, take the one-lane path (adjoint_kernel): checkpoints every
+// left (see sweep in kt_trace.hip).  A long ray's sweep is split: each 64-step
+// segment is swept backward from four basis cotangents (its transposed Jacobian,
+// a linear map since the steps are frozen), one lane each, and the last kernel
+// applies the segments' maps to the ray's seeded cotangent in order.  A sweep is
+// otherwise one lane's sequential work, and the longest would set the run time.
+// Rays beyond the store, those that end there without a crossing, and all of them
+// without step counts or with split sweeps off, take the one-lane path (adjoint_kernel): checkpoints every
 // 2^ck_shift accepted steps and each segment between them recomputed.
 // The results are the per-pixel products cot_I * dI/d(a, incl, r_in) and,
 // on request, their three sums over the image (a fixed-order block-then-grid

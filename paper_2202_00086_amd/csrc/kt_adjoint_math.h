@@ -139,10 +139,11 @@ __host__ __device__ constexpr double dp_b(int j) {
 
 // Keeps a stage of the reverse pass to itself on the device: what parts_at
 // gave in the forward pass is recomputed from the stage state instead of kept
-// (13 values per stage), and the scheduler does not mix stages.  The step VJP
-// then fits 208 VGPRs, two waves per SIMD, without a spill; left to itself it
-// took 358 with 194 moves to and from the other half of the register file, or
-// 77 scratch accesses per step at two waves.
+// (13 values per stage), and the scheduler does not mix stages.  The kernel that
+// sweeps (the trace kernel's STORE form) then takes 249 VGPRs, two waves per SIMD,
+// without a spill; left to itself the step VJP alone took 358 with 194 moves to and
+// from the other half of the register file, or 77 scratch accesses per step at two
+// waves.
 template <bool PHI>
 __host__ __device__ inline __attribute__((always_inline)) void stage_fence(double Y[5]) {
 #ifdef __HIP_DEVICE_COMPILE__

@@ -99,6 +99,8 @@ double device_wall_khz() {
 //   768x768 (9)     7.08/6.15/7.02  4.99/5.73/6.30
 //   1024x1024 (16)  12.3/10.3/11.5  8.47/8.89/10.3
 //   1200x1200 (22)  16.8/13.9/15.5  11.5/10.7/12.8
+// No one line suits both: up to 9 rays per lane two waves would win 9-13% on rings
+// and lose 15-27% on edge-on images of fast spin, which the line is drawn for.
 constexpr int64_t ONE_WAVE_MAX_RAYS_PER_LANE = 4, THREE_WAVE_MIN_RAYS_PER_LANE = 32, BS_ONE_WAVE_MAX_RAYS_PER_LANE = 9;
 
 int waves_per_simd(int32_t method, int64_t n_rays) {
@@ -118,10 +120,12 @@ struct Shape {
     int grid, min_idle;
 };
 
-// One ray in six or fewer is re-run by KT_MIXED at budgets of use (13-18% of
-// the 1024x1024 ring at 1e-10, 3% of a 2048x2048 disk): its re-run pass is a
-// launch of that many rays, not of the image's.  At the image's shape, two
-// waves per SIMD, the 640x640 disk's pass took 2.7 ms, at one wave 1.7.
+// KT_MIXED's re-run pass is shaped for a sixth of the image's rays, about what it
+// takes at budgets of use (13-18% of the 1024x1024 ring at 1e-10, 3% of a 2048x2048
+// disk; only the device knows the number).  At the image's shape, two waves per
+// SIMD, the 640x640 disk's pass took 2.7 ms, at one wave 1.7.  A budget that no ray
+// meets re-runs every ray that used single precision: the 1024x1024 ring at 0 then
+// takes 23.4 ms in all, as at 1e-10 (23.2).
 constexpr int MIXED_RERUN_SHARE = 6;
 
 Shape launch_shape(const kt::Params& p, const kt_launch& ln, int64_t n_rays, int share = 1) {

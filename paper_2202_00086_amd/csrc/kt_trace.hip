@@ -198,11 +198,12 @@ __device__ __forceinline__ void take_step(const ST& st, const RayConst& rc, cons
     }
 }
 
-// The number of lanes below this one in a mask of the wave.
+// A value that is the same in all lanes, in a scalar register.
 __device__ __forceinline__ uint32_t uniform(uint32_t v) {
     return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(v)));
 }
 
+// The number of lanes below this one in a mask of the wave.
 __device__ __forceinline__ uint32_t lanes_below(unsigned long long m) {
     return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
                                      __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u));
@@ -449,9 +450,9 @@ constexpr int FEAT_DYN = -1;
 // FP64 instructions), so everything that is not that arithmetic counts:
 // with each test in a branch of its own, and the per-ray scalars in LDS, an
 // attempt took ~830 vector and ~215 scalar instructions, and a wave alone on
-// its SIMD, as in small images, needed 2.5 us for it.  It takes 584 and 19 now (a
-// disk, 2-wave build) and 1.45 us: 512x512 lensing 4.9 -> 3.1 ms, 1024x1024 ring
-// 18.1 -> 15.3.
+// its SIMD, as in small images, needed 2.5 us for it.  It takes 615 and ~40 now
+// (a Kerr disk, 2-wave build; 583 of them FP64; 580 without spin) and 1.45 us:
+// 512x512 lensing 4.9 -> 3.1 ms, 1024x1024 ring 18.1 -> 15.3.
 //
 // STORE: the adjoint's forward pass.  The rays come from its work list, every
 // accepted step and the located partial step go to the ray's range of the
@@ -485,28 +486,29 @@ trace_kernel(const Hot hp) {
     li.k = 0;
     const uint32_t lane = __lane_id();
     uint32_t n_total;
-    uint32_t adj_first = 0, own_from = NO_RECORD;  // STORE: the first stored ray in the list, the first that its lane sweeps
+    // STORE: the first stored ray in the list, and the first that its lane sweeps
+    uint32_t adj_first = 0, own_from = NO_RECORD;
 
     // this wave's queue of ray ids [q_next, q_end).  A persistent wave's
-    // first fetch takes hp.first ids, one per lane, in one atomic; later
-    // fetches take P.batch, or one per idle lane if those are more.  Taken in batch-sized pieces, the start of
-    // the launch was a burst of 64 / batch serial round trips per wave on one
-    // address, and the wave's first rays came from interleaved places in the
-    // dispatch order instead of one run of similar cost.
+    // first fetch takes 64 ids, one per lane, in one atomic; later fetches
+    // take P.batch, or one per idle lane if those are more.  Taken in
+    // batch-sized pieces, the start of the launch was a burst of 64 / batch
+    // serial round trips per wave on one address, and the wave's first rays
+    // came from interleaved places in the dispatch order instead of one run
+    // of similar cost.
     uint32_t q_next, q_end;
     bool exhausted;
     bool first_fetch;
     {
         const Params& P = cold_params(hp.cold);
-        if constexpr (STORE)
-            {
-                const uint32_t* c = P.adj.counters;
-                adj_first = uniform(c[ADJ_C_FIRST]);
-                own_from = uniform(c[ADJ_C_OVERLAP] != 0u ? c[ADJ_C_SPLIT] : NO_RECORD);
-                n_total = hp.sweep_only ? 0u : uniform(c[ADJ_C_END]) - adj_first;
-            }
-        else
+        if constexpr (STORE) {
+            const uint32_t* c = P.adj.counters;
+            adj_first = uniform(c[ADJ_C_FIRST]);
+            own_from = uniform(c[ADJ_C_OVERLAP] != 0u ? c[ADJ_C_SPLIT] : NO_RECORD);
+            n_total = hp.sweep_only ? 0u : uniform(c[ADJ_C_END]) - adj_first;
+        } else {
             n_total = P.from_list ? *P.fb_count : static_cast<uint32_t>(P.n_rays);
+        }
         first_fetch = P.persistent != 0;
     }
     if (first_fetch) {
@@ -669,8 +671,8 @@ trace_kernel(const Hot hp) {
                 const Params& P = cold_params(hp.cold);
                 const int leader = __ffsll(idle) - 1;
                 uint32_t base = 0;
-                const uint32_t take = first_fetch ? hp.first
-                                                  : max(static_cast<uint32_t>(P.batch), static_cast<uint32_t>(__popcll(idle)));
+                const uint32_t take =
+                    first_fetch ? 64u : max(static_cast<uint32_t>(P.batch), static_cast<uint32_t>(__popcll(idle)));
                 first_fetch = false;
                 if (static_cast<int>(lane) == leader) base = atomicAdd(P.ticket, take);
                 base = static_cast<uint32_t>(__shfl(static_cast<int>(base), leader));
@@ -689,10 +691,9 @@ trace_kernel(const Hot hp) {
                 if constexpr (STORE) {
                     rec = slot;
                     ray = static_cast<int32_t>(P.adj.list[adj_first + slot]);
-                } else
-                    ray = P.from_list ? static_cast<int32_t>(P.fb_list[slot])
-                      : P.perm    ? static_cast<int32_t>(P.perm[slot])
-                                  : static_cast<int32_t>(slot);
+                } else {
+                    ray = static_cast<int32_t>(P.from_list ? P.fb_list[slot] : P.perm ? P.perm[slot] : slot);
+                }
                 double y[5], E, L;
                 bool valid;
                 if constexpr (BATCH) {
@@ -1475,7 +1476,6 @@ static Hot make_hot(const Params& p) {
     hp.feat = image_features(im);
     hp.max_steps = static_cast<int32_t>(p.max_steps);
     hp.max_evals = static_cast<int32_t>(p.max_evals);
-    hp.first = 64;
     hp.min_idle = p.min_idle;
     hp.acc = p.acc;
     hp.store = p.adj.store;

@@ -3,7 +3,7 @@
 //
 // Built as kt_trace.hip is, constants of the polynomial series and of the
 // steppers stay in vector registers across the step loop, by hand and by the
-// compiler's machine loop-invariant code motion; the kernels then need 195 to
+// compiler's machine loop-invariant code motion; the kernels then need 201 to
 // 256 VGPRs and run 2 waves per SIMD.  This file is compiled with that pass off
 // (-mllvm -disable-machine-licm, set by the build) and the staged series'
 // constants in scalar registers: the others are set up by the scalar unit where
