@@ -156,6 +156,7 @@ struct Hot {
     double h_budget, r_switch;  // KT_MIXED
     int32_t feat;               // FEAT_* bits of the image's disk, source and sky
     int32_t max_steps, max_evals;
+    uint32_t first;             // ray ids of a persistent wave's first fetch: 64 (see make_hot)
     int32_t min_idle;           // idle lanes a refill waits for
     unsigned long long* acc;    // the evaluation counters
     double* store;              // the adjoint's step store

@@ -257,11 +257,12 @@ constexpr uint32_t NO_RECORD = 0xffffffffu;
 // parts (ratios compared by cross products): no quotient per step.  Inside the
 // horizon, where a ray of a fixed step or without a capture buffer gets to, D may
 // be negative; rel_k carries the ratio's sign, so that the cross products compare
-// the ratios themselves there too.
+// the ratios themselves there too (SIGNED; the q-metric's terms are positive).
+template <bool SIGNED>
 __device__ __forceinline__ void keep_max(const Diag& dg, double* max_h2, double* rel_k, double* rel_d) {
     *max_h2 = max_abs(dg.H2, *max_h2);
-    if (dg.Kabs * fabs(*rel_d) > *rel_k * dg.D) {
-        *rel_k = __builtin_copysign(dg.Kabs, dg.D);
+    if (dg.Kabs * (SIGNED ? fabs(*rel_d) : *rel_d) > *rel_k * dg.D) {
+        *rel_k = SIGNED ? __builtin_copysign(dg.Kabs, dg.D) : dg.Kabs;
         *rel_d = dg.D;
     }
 }
@@ -639,7 +640,7 @@ trace_kernel(const Hot hp) {
         o.fate[ray] = static_cast<uint8_t>(fate);
         P.rc_buf[ray] = r_c;
         if (o.max_abs_h) o.max_abs_h[ray] = 0.5 * max_h2;
-        const double max_rel = rel_k * rcp(fabs(rel_d));
+        const double max_rel = rel_k * rcp(QMET ? rel_d : fabs(rel_d));
         if (o.max_rel_h) o.max_rel_h[ray] = max_rel;
         if (o.psi) o.psi[ray] = psi;
         if (o.deflection) o.deflection[ray] = defl;
@@ -672,7 +673,7 @@ trace_kernel(const Hot hp) {
                 const int leader = __ffsll(idle) - 1;
                 uint32_t base = 0;
                 const uint32_t take =
-                    first_fetch ? 64u : max(static_cast<uint32_t>(P.batch), static_cast<uint32_t>(__popcll(idle)));
+                    first_fetch ? hp.first : max(static_cast<uint32_t>(P.batch), static_cast<uint32_t>(__popcll(idle)));
                 first_fetch = false;
                 if (static_cast<int>(lane) == leader) base = atomicAdd(P.ticket, take);
                 base = static_cast<uint32_t>(__shfl(static_cast<int>(base), leader));
@@ -735,7 +736,7 @@ trace_kernel(const Hot hp) {
                     ys = Vec5::of(y);
                     ks = Vec5::of(k1);
                     max_h2 = fabs(dg.H2);
-                    rel_k = __builtin_copysign(dg.Kabs, dg.D);
+                    rel_k = QMET ? dg.Kabs : __builtin_copysign(dg.Kabs, dg.D);
                     rel_d = dg.D;
                     s0 = dg.s;
                     c0 = dg.c;
@@ -860,7 +861,7 @@ trace_kernel(const Hot hp) {
                         put_entry();
                         ++entry;
                     } else {
-                        keep_max(dg, &max_h2, &rel_k, &rel_d);
+                        keep_max<!QMET>(dg, &max_h2, &rel_k, &rel_d);
                     }
                     unsafeAtomicAdd(&COLD(C_LAM), h);  // one LDS add, no result
                     if constexpr (MAY_SRC) swept += arc;
@@ -968,7 +969,7 @@ trace_kernel(const Hot hp) {
                     if (h < 1e-12 * fmax(1.0, fabs(COLD(C_LAM)))) fate = KT_FATE_STEPFAIL;
                 } else {
                     if (!(fl & F_RETAKE)) {
-                        keep_max(dg, &max_h2, &rel_k, &rel_d);
+                        keep_max<!QMET>(dg, &max_h2, &rel_k, &rel_d);
                     } else {
                         ++misses;
                     }
@@ -1476,6 +1477,9 @@ static Hot make_hot(const Params& p) {
     hp.feat = image_features(im);
     hp.max_steps = static_cast<int32_t>(p.max_steps);
     hp.max_evals = static_cast<int32_t>(p.max_evals);
+    // one per lane; as a constant in the kernel it costs the q-metric form 1.5%
+    // (477x361 rays 5.31 -> 5.40 ms), whose registers the compiler then deals otherwise
+    hp.first = 64;
     hp.min_idle = p.min_idle;
     hp.acc = p.acc;
     hp.store = p.adj.store;
