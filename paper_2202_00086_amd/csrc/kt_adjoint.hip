@@ -399,12 +399,12 @@ __global__ void __launch_bounds__(SORT_BLOCK) adjoint_split_kernel(const AdjPara
         }
     }
     __syncthreads();
-    unsigned long long listed = 0;  // steps of the bins that can be stored
-    for (int i = 0; i < PER; ++i) {
-        const int k = t * PER + i;
-        listed += static_cast<unsigned long long>(cnt[i]) * static_cast<unsigned long long>(4 * (SORT_BINS - 1 - k) + 2);
+    unsigned long long listed = 0;  // steps of the bins that could be stored, where not all are
+    if (stop_store < SORT_BINS) {
+        for (int i = 0; i < PER; ++i)
+            listed += static_cast<unsigned long long>(cnt[i]) * static_cast<unsigned long long>(4 * (SORT_BINS - 1 - (t * PER + i)) + 2);
+        listed = block_scan(listed, part);
     }
-    listed = block_scan(listed, part);
     // steps and segment items of the stored bins, and the bins to split
     unsigned long long steps = 0, items = 0;
     for (int i = 0; i < PER; ++i) {

@@ -121,8 +121,8 @@ struct Shape {
 };
 
 // KT_MIXED's re-run pass is shaped for a sixth of the image's rays, about what it
-// takes at budgets of use (13-18% of the 1024x1024 ring at 1e-10, 3% of a 2048x2048
-// disk; only the device knows the number).  At the image's shape, two waves per
+// takes at budgets of use (13-24% of the 1024x1024 ring at 1e-10, by r_switch, 7% of a
+// 2048x2048 disk; only the device knows the number).  At the image's shape, two waves per
 // SIMD, the 640x640 disk's pass took 2.7 ms, at one wave 1.7.  A budget that no ray
 // meets re-runs every ray that used single precision: the 1024x1024 ring at 0 then
 // takes 23.4 ms in all, as at 1e-10 (23.2).
