@@ -365,8 +365,9 @@ int kt_autotune_batch(int32_t n_images, const kt_image *images, const kt_integra
    the longest sweep left is no longer than a lane's share of the work, at least 64
    steps.  This cuts the sequential length of the longest rays, which otherwise set
    the adjoint's run time.  Stored and split rays' gradients equal the others' up to
-   rounding (the same products, fused or associated differently); they do not depend
-   on checkpoint_every.
+   rounding (the same products, fused or associated differently); in workspaces of
+   one size they do not depend on checkpoint_every, which otherwise moves the room
+   for the store and with it the rays that are stored.
    stats (device, 4 uint64, may be NULL): rays differentiated, rays that
    failed, rays beyond the checkpoint capacity (max(256, 2048 /
    checkpoint_every) checkpoints, i.e. at least 2048 accepted steps and
